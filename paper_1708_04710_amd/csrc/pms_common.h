@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <string.h>
 
 #include <string>
 #include <vector>
@@ -27,7 +28,7 @@ struct Buf {
 enum KernelId {
     K_INIT = 0, K_BETA, K_LOW, K_COLLIDE, K_SCAN, K_PIVOTS, K_XOR, K_COMPACT, K_FINAL, K_FILL, K_DEFRAG,
     K_LS_KEYS, K_SORT, K_LS_INDEX, K_BUILD_SCAN, K_LS_ROWS, K_VR_EDGES, K_VR_TRI, K_VR_INDEX, K_VR_ROWS,
-    K_BACKWARD, K_CHAIN, K_CHAIN_LANE, K_CHAIN_WIDE, K_C8, K_BUDGET, K_SOLVE, K_LS_LEFT,
+    K_BACKWARD, K_CHAIN, K_CHAIN_LANE, K_CHAIN_WIDE, K_C8, K_BUDGET, K_SOLVE, K_LS_LEFT, K_GRAPH,
     K_NUM
 };
 
@@ -68,6 +69,14 @@ inline bool tuning_valid(const pms_tuning &t)
            t.lane_steps_few <= (1 << 30) && t.lane_many >= 0 && t.lane_refill >= 1 && t.lane_refill <= 64 &&
            t.lane_flush >= 1 && t.lane_flush <= 64 && t.wide_blocks >= 1 && t.wide_blocks <= 65535 &&
            t.lane_cap >= 0 && t.lane_cap <= kLaneCap && t.solve >= 0 && t.solve <= (1 << 30);
+}
+
+// Whether the shapes are the built-in ones (a caller that sets others asks
+// for the chained rounds they shape).
+inline bool tuning_builtin(const pms_tuning &t)
+{
+    const pms_tuning b = default_tuning();
+    return memcmp(&t, &b, sizeof(t)) == 0;
 }
 
 struct Ctx {

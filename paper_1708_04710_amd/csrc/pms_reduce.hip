@@ -117,6 +117,9 @@ struct Counters {
     int32_t dbg_flags;   // debug_invariants: the invariants found broken (DbgBit)
     int32_t dbg_col;     // a column or row that broke one
     int32_t bad_info[4]; // where k_chain set bad_source: column, low, previous low, step
+    int32_t n_dim[8];    // columns of dimension 0..6, and of 7 or more (with dim)
+    int32_t not_graph;   // kGraph0 / kGraphTop: that block has a node set larger than two
+    int32_t beta_counted; // the pivots known from beta are counted (k_graph0_seed)
     unsigned long long trace[S_NUM];  // folded stripes (trace output)
 };
 
@@ -499,7 +502,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_sum2(int32_t *a, int32_t 
 __global__ void __launch_bounds__(kBlock) k_pivots(Dev d, const int32_t *act, const I4 *agg, int compression)
 {
     const int32_t nA = d.cnt->n_cur;
-    const int count_beta = d.cnt->round == 0;
+    const int count_beta = d.cnt->round == 0 && !d.cnt->beta_counted;
     const int64_t tiles = ((int64_t)nA + kBlock - 1) / kBlock;
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const int64_t q = tile * kBlock + threadIdx.x;
@@ -2872,6 +2875,8 @@ __global__ void k_stats_fold(Dev d)
     }
 }
 
+#include "pms_graph.h"
+
 // Self-test of the DPP wave reductions against __shfl-based ones on a few
 // patterns; writes the number of mismatches.
 __global__ void k_selftest(int32_t *bad)
@@ -3196,6 +3201,14 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
         PMS_LAUNCH(c, K_FILL, 0, k_fill_i32, gm, kBlock, d.dbg_erem, m, 0x7FFFFFFF);
         PMS_LAUNCH(c, K_FILL, 0, k_dbg_round, gm, kBlock, d, opt->compression, 1, 0);
     }
+    const char *tr_env = getenv("PMS_TRACE");
+    const int trace = tr_env && tr_env[0] == '1';
+    // The blocks that are graphs are solved apart, unless an option asks for
+    // a schedule of the rounds (or to watch them), which then hold every column
+    const bool blocks = bnd->dim && opt->variant == 0 && opt->compression && opt->chain && opt->max_rounds == 0 &&
+                        opt->graph_rounds == 0 && !opt->sweep && opt->arena_entries == 0 && !diag && !dbg && !c8on &&
+                        !budget && tuning_builtin(c->tune) && d.arena_cap * sizeof(int32_t) >= (size_t)m * 8;
+    if (blocks) PMS_LAUNCH(c, K_GRAPH, dm, k_dim_count, grid_for(m, kBlock, 1024), kBlock, d);
     PMS_HIP(hipGetLastError());
 
     Counters *h = (Counters *)c->host_pinned;
@@ -3232,8 +3245,6 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     unsigned long long xor_bytes_prev = 0, chain_bytes_prev = 0, lane_bytes_prev = 0, wide_bytes_prev = 0;
     unsigned long long solve_bytes_prev = 0, pivot_bytes_prev = 0;
     unsigned long long ab_prev[5] = {0, 0, 0, 0, 0};
-    const char *tr_env = getenv("PMS_TRACE");
-    const int trace = tr_env && tr_env[0] == '1';
     unsigned long long tprev[S_NUM] = {};
     int32_t nA_prev = 0;
     int32_t *act = act0, *act_next = act1;
@@ -3415,6 +3426,33 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     if (sd >= 0) {
         const pms_status sb = stage_build(sd);
         if (sb != PMS_OK) return sb;
+    }
+    if (blocks && h->topdim >= 1 && h->topdim < 7) {
+        const int32_t top = h->topdim;
+        // a face with more than two cofaces is certain when the top simplices
+        // have more facets than two per face (Vietoris-Rips complexes: 16x and
+        // more); otherwise the cofaces are counted
+        const int do_top = top >= 2 && (int64_t)h->n_dim[top] * (top + 1) <= 2LL * h->n_dim[top - 1];
+        const double d1 = (double)h->n_dim[1], dt = (double)h->n_dim[top], df = (double)h->n_dim[top - 1];
+        PMS_LAUNCH(c, K_GRAPH, dm + 20.0 * d1, k_graph0_seed, gm, kBlock, d);
+        PMS_LAUNCH(c, K_GRAPH, dm + 28.0 * d1, k_graph0_walk, gm, kBlock, d);
+        if (do_top) {
+            unsigned long long *S2 = (unsigned long long *)d.arena;  // (no column has moved there yet)
+            PMS_LAUNCH(c, K_GRAPH, 8.0 * dm, k_fill_u64, gm, kBlock, S2, m, 0ull);
+            PMS_LAUNCH(c, K_GRAPH, dm + (12.0 + 12.0 * (top + 1)) * dt, k_cof_sum, gm, kBlock, d, S2, top);
+            PMS_LAUNCH(c, K_GRAPH, dm + 28.0 * df, k_graph_top_seed, gm, kBlock, d, S2, top);
+            PMS_LAUNCH(c, K_GRAPH, dm + 28.0 * df, k_graph_top_walk, gm, kBlock, d, S2, top);
+        }
+        PMS_LAUNCH(c, K_GRAPH, dm + 20.0 * ((double)h->n_dim[0] + (do_top ? dt : 0)), k_graph_apply, gm, kBlock, d, top,
+                   do_top, opt->compression);
+        PMS_LAUNCH(c, K_COMPACT, 2 * dm, k_mix_count, gm, kBlock, d, keep, top, do_top);
+        PMS_LAUNCH(c, K_SCAN, 8.0 * nblk, k_scan_sum, 1, kScanThreads, keep, nblk, nullptr, &d.cnt->n_next);
+        PMS_LAUNCH(c, K_COMPACT, 2 * dm, k_mix_compact, gm, kBlock, d, keep, act0, top, do_top);
+        PMS_LAUNCH(c, K_FILL, 0, k_mix_start, 1, 1, d, top, do_top);
+        PMS_HIP(hipGetLastError());
+        PMS_HIP(hipMemcpyAsync(h, d.cnt, sizeof(Counters), hipMemcpyDeviceToHost, st));
+        PMS_HIP(hipStreamSynchronize(st));
+        nA = h->n_cur;
     }
     for (;;) {
     if (graph_k > 0 && nA > 0) {
@@ -3649,7 +3687,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
         const pms_status sdb = dbg_check("at the end, after round", (int32_t)round);
         if (sdb != PMS_OK) return sdb;
     }
-    res->rounds = (int32_t)round;
+    res->rounds = (int32_t)round + (blocks ? 1 : 0);  // (the graphs' pass is one)
     res->additions = (int64_t)h->additions;
     res->xor_entries = (int64_t)h->xor_entries;
     res->active_sum = (int64_t)h->active_sum;
@@ -3829,7 +3867,7 @@ static const char *const kKernelNames[pms::K_NUM] = {
     "k_init", "k_beta", "k_low", "k_collide", "k_scan", "k_pivots", "k_xor", "k_compact", "k_finalize", "k_fill",
     "k_defrag", "k_ls_keys", "k_sort", "k_ls_index", "k_build_scan", "k_ls_rows", "k_vr_edges", "k_vr_tri",
     "k_vr_index", "k_vr_rows", "k_backward", "k_chain", "k_chain_lane", "k_chain_wide", "k_c8", "k_budget",
-    "k_chain_solve", "k_ls_left"};
+    "k_chain_solve", "k_ls_left", "k_graph"};
 
 pms_status pms_profile_enable(pms_ctx *c, int enable)
 {
