@@ -1,5 +1,8 @@
 // Vietoris-Rips filtrations (dimension <= 3) of batches of point clouds,
-// built on the GPU.
+// built on the GPU by sorting every simplex: the build for the batches the
+// edge-order build (pms_build_vr_edges.hip) does not take, which are those
+// with many edges of one value (points on a coarse lattice) or more clouds
+// than its one-word key has room for.
 //
 // A simplex of a cloud is present when its squared diameter is at most the
 // cloud's threshold (Sec. 2.2: diam <= 2r is monotone in the squared
@@ -651,6 +654,19 @@ static pms_status build_vr(Ctx *c, const void *pts, bool f32, const int32_t *n, 
 pms_status build_vr_batch(Ctx *c, const void *pts, bool f32, const int32_t *n, const int32_t *D, const int64_t *pt_off,
                           const void *thr, int32_t B, int32_t maxdim, Filtration **out, int64_t *inst_col_off)
 {
+    if (!out || !n || !D || !pt_off || B < 1 || maxdim < 0 || maxdim > 3)
+        return set_err(c, PMS_ERR_INVALID_ARG, "bad Vietoris-Rips arguments (maxdim must be 0..3)");
+    const int nmax = f32 ? 1023 : 511;  // n^3 must fit the sorted build's lex field
+    int64_t points = 0;
+    for (int b = 0; b < B; b++) {
+        if (n[b] < 0 || n[b] > nmax || D[b] < 1 || pt_off[b] < 0 || (n[b] > 0 && !pts))
+            return set_err(c, PMS_ERR_INVALID_ARG, "cloud size out of range (n <= 511 for int32, 1023 for FP32)");
+        points += n[b];
+    }
+    if (points >= 0x7FFFFFFF) return set_err(c, PMS_ERR_INVALID_ARG, "too many points");
+    int done = 0;
+    const pms_status st = build_vr_edges(c, pts, f32, n, D, pt_off, thr, B, maxdim, out, inst_col_off, &done);
+    if (st != PMS_OK || done) return st;
     return build_vr(c, pts, f32, n, D, pt_off, thr, B, maxdim, out, inst_col_off);
 }
 

@@ -29,16 +29,74 @@ static void filtration_release(Filtration *f)
     f->cap_m = f->cap_nnz = 0;
 }
 
+static Filtration *filtration_get(Ctx *c, Filtration **pf)
+{
+    if (!*pf) {
+        *pf = new (std::nothrow) Filtration();
+        if (*pf) (*pf)->device = c->device;
+    }
+    return *pf;
+}
+
+static void filtration_vr_release(Filtration *f)
+{
+    f->vr_count = 0;
+    for (auto &b : f->vr) {
+        (void)hipFree(b.p);
+        b = Buf();
+    }
+}
+
+pms_status filtration_vr_reserve(Ctx *c, Filtration **pf, int id, size_t bytes)
+{
+    Filtration *f = filtration_get(c, pf);
+    if (!f) return set_err(c, PMS_ERR_OOM, "filtration");
+    f->vr_count = 0;  // until the builder is done
+    if (f->device != c->device) {
+        (void)hipStreamSynchronize(c->stream);
+        filtration_release(f);
+        filtration_vr_release(f);
+        f->m = f->nnz = 0;
+        f->device = c->device;
+    }
+    Buf &b = f->vr[id];
+    if (b.bytes >= bytes) return PMS_OK;
+    (void)hipStreamSynchronize(c->stream);
+    (void)hipFree(b.p);
+    b = Buf();
+    PMS_HIP(hipMalloc(&b.p, bytes));
+    b.bytes = bytes;
+    return PMS_OK;
+}
+
+VeView filtration_vr_view(const Filtration *f)
+{
+    VeView v{};
+    const int32_t d = f->vr_maxdim;
+    v.cl = (const VeCloud *)f->vr[VR_CLOUDS].p;
+    v.ev = (const uint32_t *)f->vr[VR_EV].p;
+    v.erank = (const int32_t *)f->vr[VR_ERANK].p;
+    v.eidx = (const int32_t *)f->vr[VR_EIDX].p;
+    v.rec = (const uint2 *)f->vr[VR_REC].p;
+    v.gst = (const int32_t *)f->vr[VR_GST].p;
+    v.gend = (const int32_t *)f->vr[VR_GEND].p;
+    v.tscan = (const int32_t *)f->vr[VR_TSCAN].p;
+    v.app = (const int32_t *)f->vr[VR_APP].p;
+    if (d >= 3) {  // (a buffer kept from an earlier build to dimension 3 is stale)
+        v.q2 = (const int64_t *)f->vr[VR_Q2].p;
+        v.recd = (const uint32_t *)f->vr[VR_RECD].p;
+        v.rec2 = (const uint2 *)f->vr[VR_REC2].p;
+        v.appt = (const int32_t *)f->vr[VR_APPT].p;
+    }
+    return v;
+}
+
 pms_status filtration_reserve(Ctx *c, Filtration **pf, int64_t m, int64_t nnz, int f32)
 {
-    Filtration *f = *pf;
-    if (!f) {
-        f = new (std::nothrow) Filtration();
-        if (!f) return set_err(c, PMS_ERR_OOM, "filtration");
-        f->device = c->device;
-        *pf = f;
-    }
+    Filtration *f = filtration_get(c, pf);
+    if (!f) return set_err(c, PMS_ERR_OOM, "filtration");
     f->has_left_beta = 0;  // until a builder writes them
+    f->vr_count = 0;
     if (f->cap_m >= m && f->cap_nnz >= nnz && f->device == c->device) return PMS_OK;
     (void)hipStreamSynchronize(c->stream);
     filtration_release(f);
@@ -195,6 +253,7 @@ void pms_filtration_free(pms_filtration *f)
     (void)hipSetDevice(pf->device);
     (void)hipDeviceSynchronize();
     pms::filtration_release(pf);
+    pms::filtration_vr_release(pf);
     delete pf;
 }
 
