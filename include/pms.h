@@ -419,6 +419,14 @@ pms_status pms_build_vr_f32(pms_ctx *ctx, const float *pts, int32_t count, const
                             int64_t *inst_col_off);
 /* Device pointers of a built filtration (valid until it is rebuilt or freed). */
 pms_status pms_filtration_view_get(const pms_filtration *f, pms_filtration_view *v);
+/* Reduce a built filtration: the matrix of its view, with the results,
+ * options and statuses of pms_reduce (inst_col_off NULL) or
+ * pms_reduce_batched (count, inst_col_off and the outputs after res as
+ * there).  With what the builder knows beyond the matrix some filtrations are
+ * reduced faster this way (Vietoris-Rips: without reading the matrix). */
+pms_status pms_reduce_filtration(pms_ctx *ctx, const pms_filtration *f, int32_t count, const int64_t *inst_col_off,
+                                 const pms_options *opt, pms_result *res, int64_t *inst_pair_off,
+                                 int64_t *inst_ess_off, int32_t *pair_inst);
 /* Copy a built filtration into caller-owned device buffers on ctx's stream
  * (any pointer may be NULL to skip that array; value is float or int64 as
  * the view says; crit holds 2m and verts 4m entries).  Returns after the

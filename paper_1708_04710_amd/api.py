@@ -273,28 +273,40 @@ def _result(res, t, **extra) -> ReduceResult:
                         addition_bytes=res.addition_bytes, **extra)
 
 
-def _reduce_ptrs(dev, m, col_ptr_p, rows_p, dim_p, *, outputs=True, inst_col_off=None, noalloc=False,
-                 left_p=None, beta_p=None, **kw) -> ReduceResult:
+def _reduce_ptrs(dev, m, col_ptr_p, rows_p, dim_p, *, outputs=True, noalloc=False, left_p=None, beta_p=None,
+                 **kw) -> ReduceResult:
     lib = B.load()
     ctx = _ctx(dev)
     bnd = B.PmsBoundary(m, col_ptr_p, rows_p, dim_p, left_p, beta_p)
     opt = _options(**kw)
     res, t = _outputs(dev, m, outputs)
+    fn = lib.pms_reduce_noalloc if noalloc else lib.pms_reduce
+    B.check(ctx, fn(ctx, ctypes.byref(bnd), ctypes.byref(opt), ctypes.byref(res)))
     extra = {}
-    if noalloc:
-        if inst_col_off is not None:
-            raise ValueError("the allocation-free entry point reduces one matrix")
-        st = lib.pms_reduce_noalloc(ctx, ctypes.byref(bnd), ctypes.byref(opt), ctypes.byref(res))
-    elif inst_col_off is None:
-        st = lib.pms_reduce(ctx, ctypes.byref(bnd), ctypes.byref(opt), ctypes.byref(res))
+    if kw.get("diagnostics"):
+        extra.update(round_stats=round_stats(dev), essential_estimate=essential_estimate(m, dev))
+    return _result(res, t, **extra)
+
+
+def _reduce_built(f: Filtration, inst_col_off=None, *, outputs=True, **kw) -> ReduceResult:
+    """``pms_reduce_filtration``: the filtration itself rather than its
+    arrays, so that the library can use what its builder knows."""
+    lib = B.load()
+    dev, m = f.device, f.m
+    ctx = _ctx(dev)
+    opt = _options(**kw)
+    res, t = _outputs(dev, m, outputs)
+    extra = {}
+    if inst_col_off is None:
+        st = lib.pms_reduce_filtration(ctx, f.handle, 0, None, ctypes.byref(opt), ctypes.byref(res), None, None, None)
     else:
         nb = inst_col_off.numel() - 1
         poff = torch.empty(nb + 1, dtype=torch.int64, device=dev)
         eoff = torch.empty(nb + 1, dtype=torch.int64, device=dev)
         pinst = torch.empty(max(res.cap_pairs, 1), dtype=torch.int32, device=dev)
-        st = lib.pms_reduce_batched(ctx, nb, inst_col_off.data_ptr(), ctypes.byref(bnd), ctypes.byref(opt),
-                                    ctypes.byref(res), poff.data_ptr(), eoff.data_ptr(),
-                                    pinst.data_ptr() if outputs else None)
+        st = lib.pms_reduce_filtration(ctx, f.handle, nb, inst_col_off.data_ptr(), ctypes.byref(opt),
+                                       ctypes.byref(res), poff.data_ptr(), eoff.data_ptr(),
+                                       pinst.data_ptr() if outputs else None)
         extra = dict(inst_pair_off=poff, inst_ess_off=eoff, pair_inst=pinst[:res.n_pairs] if outputs else None)
     B.check(ctx, st)
     if kw.get("diagnostics"):
@@ -460,7 +472,10 @@ def reduce_filtration(f: Filtration, **kw) -> ReduceResult:
     matrices are those of compatible filtrations by construction."""
     kw.setdefault("validate", False)
     v = f.view
-    return _reduce_ptrs(f.device, int(v.m), v.col_ptr, v.rows, v.dim, left_p=v.left, beta_p=v.beta, **kw)
+    if kw.get("noalloc") or not f.handle:
+        return _reduce_ptrs(f.device, int(v.m), v.col_ptr, v.rows, v.dim, left_p=v.left, beta_p=v.beta, **kw)
+    kw.pop("noalloc", None)
+    return _reduce_built(f, **kw)
 
 
 def reduce_batched(f: Filtration, col_off, **kw) -> ReduceResult:
@@ -470,6 +485,6 @@ def reduce_batched(f: Filtration, col_off, **kw) -> ReduceResult:
     (count + 1 entries, host list or int64 tensor)."""
     kw.setdefault("validate", False)
     off = torch.as_tensor(col_off, dtype=torch.int64).to(f.device)
-    v = f.view
-    return _reduce_ptrs(f.device, int(v.m), v.col_ptr, v.rows, v.dim, inst_col_off=off, left_p=v.left,
-                        beta_p=v.beta, **kw)
+    if kw.pop("noalloc", False):
+        raise ValueError("the allocation-free entry point reduces one matrix")
+    return _reduce_built(f, off, **kw)

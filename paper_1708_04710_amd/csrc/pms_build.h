@@ -9,7 +9,7 @@ namespace pms {
 // Arrays a Vietoris-Rips filtration built by edge order keeps (pms_vr_edges.h)
 enum VrBuf {
     VR_CLOUDS = 0, VR_EV, VR_ERANK, VR_EIDX, VR_REC, VR_GST, VR_GEND, VR_TSCAN, VR_Q2, VR_APP, VR_RECD, VR_REC2,
-    VR_APPT, VR_NUM
+    VR_APPT, VR_TRIP, VR_MASK, VR_APC, VR_NUM
 };
 
 // Device arrays of one filtration in compatible order (owned by the library).
@@ -32,6 +32,8 @@ struct Filtration {
     int32_t vr_maxdim = 0;
     int64_t vr_edges = 0;        // entries of its edge arrays
     int64_t vr_max_m = 0;        // simplices of its largest cloud
+    int64_t vr_max_t = 0;        // most triangles of a cloud
+    int32_t vr_max_n = 0;        // most points of a cloud
 };
 
 // (Re)allocate *f for m simplices and nnz facets; reuses it when big enough.
@@ -48,6 +50,9 @@ pms_status build_vr_batch(Ctx *c, const void *pts, bool f32, const int32_t *n, c
 pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, const int32_t *D, const int64_t *pt_off,
                           const void *thr, int32_t B, int32_t maxdim, Filtration **out, int64_t *inst_col_off,
                           int *done);
+
+pms_status reduce_vr(Ctx *c, const Filtration *f, pms_result *res, int32_t count, const int64_t *inst_col_off,
+                     int64_t *inst_pair_off, int64_t *inst_ess_off, int32_t *pair_inst, int *done);
 
 // In-place exclusive scan of n int64 on ctx's stream; *total receives the
 // sum (the call synchronises).  tmp holds ceil(n / kBlock) + 2 entries.

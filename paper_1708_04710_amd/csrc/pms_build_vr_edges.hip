@@ -204,7 +204,7 @@ __global__ void __launch_bounds__(kBlock) k_ve_ranks(VeCloud *cl, int lexb, int 
 __global__ void __launch_bounds__(kBlock) k_ve_masks(const VeCloud *cl, int maxdim, const uint32_t *ev_s,
                                                      const int32_t *gst_s, const int32_t *gend_s, const int32_t *erank,
                                                      uint32_t *ev, int32_t *gst, int32_t *gend, uint2 *rec,
-                                                     int32_t *tcnt, int32_t *app)
+                                                     uint64_t *mask, int32_t *tcnt, int32_t *apc)
 {
     const VeCloud I = cl[blockIdx.y];
     const int lane = threadIdx.x & (kWave - 1);
@@ -229,6 +229,7 @@ __global__ void __launch_bounds__(kBlock) k_ve_masks(const VeCloud *cl, int maxd
                 uint2 *r = rec + I.woff + (int64_t)e * I.W + 2 * w;
                 r[0].x = (uint32_t)m;
                 if (2 * w + 1 < I.W) r[1].x = (uint32_t)(m >> 32);
+                mask[I.moff + (int64_t)e * I.M + w] = m;
             }
             t += __popcll(m);
         }
@@ -238,7 +239,7 @@ __global__ void __launch_bounds__(kBlock) k_ve_masks(const VeCloud *cl, int maxd
             gst[o] = gst_s[I.cap_off + e];
             gend[o] = ge;
             tcnt[o] = t;
-            app[o] = first_in ? first : -1;  // its third vertex; an index after k_ve_emit
+            apc[o] = first_in ? first : -1;
         }
     }
 }
@@ -346,7 +347,7 @@ __global__ void __launch_bounds__(kBlock) k_ve_emit(VeView v, VeOut o, int maxdi
                     make_int4(pb + a, pb + b, -1, -1));
         o.rows[cp] = (int32_t)I.col_base + a;
         o.rows[cp + 1] = (int32_t)I.col_base + b;
-        const int apc = v.app[oe];
+        const int apc = v.apc[oe];
         uint2 *r = rec + I.woff + (int64_t)e * I.W;
         uint32_t *rd = recd ? recd + I.woff + (int64_t)e * I.W : nullptr;
         int32_t run = 0, at = -1;
@@ -365,7 +366,7 @@ __global__ void __launch_bounds__(kBlock) k_ve_emit(VeView v, VeOut o, int maxdi
 // writes; the gathers (masks, the other edges' indices) stay in one cloud's
 // tables and hit L2.
 template <bool F32>
-__global__ void __launch_bounds__(kBlock) k_ve_tris(VeView v, VeOut o, const unsigned long long *eval, int32_t *appt)
+__global__ void __launch_bounds__(kBlock) k_ve_tris(VeView v, VeOut o, const unsigned long long *eval, int32_t *trip, int32_t *appt)
 {
     const VeCloud I = v.cl[blockIdx.y];
     const int32_t pb = (int32_t)I.pbase, cb = (int32_t)I.col_base;
@@ -396,7 +397,10 @@ __global__ void __launch_bounds__(kBlock) k_ve_tris(VeView v, VeOut o, const uns
         o.rows[cp] = cb + min(r0, r1);
         o.rows[cp + 1] = cb + max(r0, r1);
         o.rows[cp + 2] = cb + I.n + e + ts[g0] + qs;
-        if (appt) appt[p] = -1;
+        if (appt) {
+            trip[I.toff + ts[g0] + r] = (int32_t)(p - cb);
+            appt[p] = -1;
+        }
     }
 }
 
@@ -583,6 +587,7 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
         I.n = n[b];
         I.D = D[b];
         I.W = maxdim >= 2 ? (n[b] + 31) / 32 : 0;
+        I.M = maxdim >= 2 ? (n[b] + 63) / 64 : 0;
         I.pt_off = pt_off[b];
         I.pbase = pbase;
         I.slot_base = slots;
@@ -687,7 +692,7 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
         st = read_clouds();
         if (st != PMS_OK) return st;
     }
-    int64_t E = 0, words = 0;
+    int64_t E = 0, words = 0, mwords = 0;
     for (int b = 0; b < B; b++) {
         VeCloud &I = h[(size_t)b];
         if (maxdim >= 2 && I.gmax > (maxdim >= 3 ? kVeMaxTies3 : kVeMaxTies)) return PMS_OK;
@@ -696,11 +701,13 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
         I.woff = words;
         E += I.E + 1;
         words += (int64_t)I.E * I.W;
+        I.moff = mwords;
+        mwords += (int64_t)I.E * I.M;
     }
-    const int ids[] = {VR_CLOUDS, VR_EV, VR_GST, VR_GEND, VR_TSCAN, VR_APP, VR_REC, VR_RECD};
+    const int ids[] = {VR_CLOUDS, VR_EV, VR_GST, VR_GEND, VR_TSCAN, VR_APP, VR_APC, VR_REC, VR_MASK, VR_RECD};
     const size_t sz[] = {(size_t)B * sizeof(VeCloud), (size_t)E * 4, (size_t)E * 4, (size_t)E * 4, (size_t)E * 4,
-                         (size_t)E * 4, (size_t)words * 8, maxdim >= 3 ? (size_t)words * 4 : 0};
-    for (int k = 0; k < 8; k++)
+                         (size_t)E * 4, (size_t)E * 4, (size_t)words * 8, (size_t)mwords * 8, maxdim >= 3 ? (size_t)words * 4 : 0};
+    for (int k = 0; k < 10; k++)
         if ((st = filtration_vr_reserve(c, &f, ids[k], sz[k])) != PMS_OK) return st;
     f->vr_maxdim = maxdim;
     uint32_t *ev = (uint32_t *)f->vr[VR_EV].p;
@@ -718,7 +725,8 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
                     (unsigned)B);
     };
     PMS_LAUNCH(c, K_VR_TRI, 8.0 * words + 28.0 * E, k_ve_masks, grid(emax, kWavesPerBlock), kBlock, cl, maxdim, ev_s,
-               gst_s, gend_s, erank, ev, gst, gend, rec, tscan, app);
+               gst_s, gend_s, erank, ev, gst, gend, rec, (uint64_t *)f->vr[VR_MASK].p, tscan,
+               (int32_t *)f->vr[VR_APC].p);
     PMS_LAUNCH(c, K_BUILD_SCAN, 8.0 * E, k_ve_scan, (unsigned)B, 1024, cl, tscan);
     PMS_HIP(hipGetLastError());
     PMS_HIP(hipMemcpyAsync(h.data(), cl, (size_t)B * sizeof(VeCloud), hipMemcpyDeviceToHost, s));
@@ -770,6 +778,9 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
     f->nnz = nnz;
     f->value_is_f32 = f32 ? 1 : 0;
     if (maxdim >= 3 && (st = filtration_vr_reserve(c, &f, VR_APPT, (size_t)m * 4)) != PMS_OK) return st;
+    if (maxdim >= 3 && (st = filtration_vr_reserve(c, &f, VR_TRIP, (size_t)T * 4)) != PMS_OK) return st;
+    f->vr_max_t = tmax;
+    f->vr_max_n = (int32_t)nmax;
     PMS_HIP(hipMemcpyAsync(cl, h.data(), (size_t)B * sizeof(VeCloud), hipMemcpyHostToDevice, s));
     if (m == 0) {
         const int64_t zero = 0;
@@ -779,12 +790,13 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
         const VeOut o{m, nnz, f->col_ptr, f->rows, f->dim, f->value, f->crit, f->verts};
         uint2 *rec2 = (uint2 *)f->vr[VR_REC2].p;
         int32_t *appt = maxdim >= 3 ? (int32_t *)f->vr[VR_APPT].p : nullptr;
+        int32_t *trip = maxdim >= 3 ? (int32_t *)f->vr[VR_TRIP].p : nullptr;
         const double pb = f32 ? 37.0 : 41.0;
         if (f32) PMS_LAUNCH(c, K_VR_INDEX, (pb + 8) * E, k_ve_emit<true>, grid(std::max(emax, nmax), kBlock), kBlock, v, o, maxdim, eval, eidx, rec, app, recd);
         else PMS_LAUNCH(c, K_VR_INDEX, (pb + 8) * E, k_ve_emit<false>, grid(std::max(emax, nmax), kBlock), kBlock, v, o, maxdim, eval, eidx, rec, app, recd);
         if (T > 0) {
-            if (f32) PMS_LAUNCH(c, K_VR_ROWS, (pb + 12) * T, k_ve_tris<true>, grid(tmax, 2 * kBlock), kBlock, v, o, eval, appt);
-            else PMS_LAUNCH(c, K_VR_ROWS, (pb + 12) * T, k_ve_tris<false>, grid(tmax, 2 * kBlock), kBlock, v, o, eval, appt);
+            if (f32) PMS_LAUNCH(c, K_VR_ROWS, (pb + 12) * T, k_ve_tris<true>, grid(tmax, 2 * kBlock), kBlock, v, o, eval, trip, appt);
+            else PMS_LAUNCH(c, K_VR_ROWS, (pb + 12) * T, k_ve_tris<false>, grid(tmax, 2 * kBlock), kBlock, v, o, eval, trip, appt);
         }
         if (maxdim >= 3 && T > 0) {
             PMS_LAUNCH(c, K_VR_INDEX, 8.0 * words2, k_ve_tindex, grid(tmax, kBlock), kBlock, v, tri, rec2, appt);

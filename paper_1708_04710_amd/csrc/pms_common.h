@@ -28,7 +28,7 @@ struct Buf {
 enum KernelId {
     K_INIT = 0, K_BETA, K_LOW, K_COLLIDE, K_SCAN, K_PIVOTS, K_XOR, K_COMPACT, K_FINAL, K_FILL, K_DEFRAG,
     K_LS_KEYS, K_SORT, K_LS_INDEX, K_BUILD_SCAN, K_LS_ROWS, K_VR_EDGES, K_VR_TRI, K_VR_INDEX, K_VR_ROWS,
-    K_BACKWARD, K_CHAIN, K_CHAIN_LANE, K_CHAIN_WIDE, K_C8, K_BUDGET, K_SOLVE, K_LS_LEFT, K_GRAPH,
+    K_BACKWARD, K_CHAIN, K_CHAIN_LANE, K_CHAIN_WIDE, K_C8, K_BUDGET, K_SOLVE, K_LS_LEFT, K_GRAPH, K_DUAL,
     K_NUM
 };
 
@@ -124,6 +124,7 @@ enum BufId {
     B_BUILD0, B_BUILD1, B_BUILD2, B_BUILD3, B_BUILD4, B_BUILD5, B_BUILD6, B_BUILD7,
     B_BUILD8, B_BUILD9, B_BUILD10, B_BUILD11, B_BUILD12, B_BUILD13, B_BUILD14, B_STATS, B_PART, B_CQN, B_PREC, B_WQ, B_WQ2, B_ESS,
     B_DBG_LOW, B_DBG_OFF, B_DBG_LEN, B_DBG_STATE, B_DBG_W, B_DBG_EREM, B_C8, B_INST, B_BUDH, B_BUDN,
+    B_DUAL0, B_DUAL1, B_DUAL2, B_DUAL3, B_DUAL4, B_DUAL5,
     B_NUM
 };
 static_assert(B_NUM <= 56, "Ctx::b holds 56 buffers");

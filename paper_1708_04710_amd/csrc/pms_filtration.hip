@@ -81,11 +81,14 @@ VeView filtration_vr_view(const Filtration *f)
     v.gst = (const int32_t *)f->vr[VR_GST].p;
     v.gend = (const int32_t *)f->vr[VR_GEND].p;
     v.tscan = (const int32_t *)f->vr[VR_TSCAN].p;
+    v.mask = (const uint64_t *)f->vr[VR_MASK].p;
+    v.apc = (const int32_t *)f->vr[VR_APC].p;
     v.app = (const int32_t *)f->vr[VR_APP].p;
     if (d >= 3) {  // (a buffer kept from an earlier build to dimension 3 is stale)
         v.q2 = (const int64_t *)f->vr[VR_Q2].p;
         v.recd = (const uint32_t *)f->vr[VR_RECD].p;
         v.rec2 = (const uint2 *)f->vr[VR_REC2].p;
+        v.trip = (const int32_t *)f->vr[VR_TRIP].p;
         v.appt = (const int32_t *)f->vr[VR_APPT].p;
     }
     return v;

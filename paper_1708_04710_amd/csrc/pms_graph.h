@@ -31,8 +31,6 @@
 // cofaces), not by the walks.
 #pragma once
 
-constexpr unsigned long long kGraphEmpty = ~0ull;
-constexpr int32_t kGraphOut = 0x7FFFFFFF;  // the node beyond a boundary face (top block)
 constexpr int32_t kNotGraph0 = 1, kNotGraphTop = 2;
 
 // Columns per dimension (7: that dimension and above).
@@ -54,47 +52,6 @@ __global__ void __launch_bounds__(kBlock) k_dim_count(Dev d)
     }
     __syncthreads();
     if (threadIdx.x < 8 && s_n[threadIdx.x]) atomicAdd(&d.cnt->n_dim[threadIdx.x], s_n[threadIdx.x]);
-}
-
-__device__ inline unsigned long long graph_load(const unsigned long long *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Places the edge (node pair u, v) of pivot order `ord`.  kTop: the node to
-// reduce is the smaller end and the other end grows (kGraphOut last), else
-// the larger end and the other end shrinks (-1, no vertex, last).  Long walks
-// shorten the pivots they pass (adding to a pivot an earlier one), so that a
-// path is walked in full only once.
-template <bool kTop>
-__device__ inline void graph_place(unsigned long long *P, uint32_t ord, int32_t u, int32_t v)
-{
-    for (int step = 0; u != v; step++) {
-        if (kTop ? u > v : u < v) {
-            const int32_t t = u;
-            u = v;
-            v = t;
-        }
-        // u is the node to reduce, v the other end
-        unsigned long long key = ((unsigned long long)ord << 32) | (uint32_t)(kTop ? v : v + 1);
-        unsigned long long cur = graph_load(&P[u]);
-        if (cur >= key) {
-            cur = atomicMin(&P[u], key);
-            if (cur == kGraphEmpty) return;
-            if (cur > key) {  // placed; the displaced pivot plus this one: (its other end, v)
-                ord = (uint32_t)(cur >> 32);
-                u = (int32_t)(uint32_t)cur - (kTop ? 0 : 1);
-                continue;
-            }
-        }
-        const int32_t w = (int32_t)(uint32_t)cur - (kTop ? 0 : 1);
-        if (step >= 16 && w != (kTop ? kGraphOut : -1)) {
-            const unsigned long long nx = graph_load(&P[w]);
-            if ((uint32_t)(nx >> 32) < (uint32_t)(cur >> 32))  // an earlier pivot (kGraphEmpty is later)
-                atomicMin(&P[u], (cur & 0xFFFFFFFF00000000ull) | (uint32_t)nx);
-        }
-        u = w;
-    }
 }
 
 // The rows of edge j as nodes (a missing one: -1); false when it has more than two.
@@ -244,46 +201,183 @@ __global__ void __launch_bounds__(kBlock) k_graph_apply(Dev d, int32_t top, int 
     }
 }
 
-// The first active list: live columns of the dimensions no graph has solved.
-__device__ inline bool mix_keep(const Dev &d, int64_t j, int32_t top, bool g0, bool gt)
+// ---------------------------------------------------------------- from the rows
+// The faces' cofaces as lists, for blocks reduced from their rows (pms_dual.h):
+// counted into end[face], scanned, and filled so that end[face] is the end of
+// its list (in no particular order: a column's cofaces only flip bits).
+// dims: bit b + 1 set: columns of dimension b + 1 are listed.
+__global__ void __launch_bounds__(kBlock) k_cof_count(Dev d, int32_t dims, int32_t *end)
 {
-    const int dj = d.dim[j];
-    return d.state[j] == ST_ACTIVE && !(dj == 1 && g0) && !(dj == top && gt);
+    for (int64_t j = blockIdx.x * (int64_t)kBlock + threadIdx.x; j < d.m; j += (int64_t)gridDim.x * kBlock) {
+        if (!((dims >> d.dim[j]) & 1)) continue;
+        const int32_t n = d.len[j];
+        const int64_t s = d.col_ptr[j];
+        for (int32_t k = 0; k < n; k++) atomicAdd(&end[d.rows[s + k]], 1);
+    }
 }
 
-__global__ void __launch_bounds__(kBlock) k_mix_count(Dev d, int32_t *keep_cnt, int32_t top, int do_top)
+__global__ void __launch_bounds__(kBlock) k_cof_fill(Dev d, int32_t dims, int32_t *end, int32_t *cof)
+{
+    for (int64_t j = blockIdx.x * (int64_t)kBlock + threadIdx.x; j < d.m; j += (int64_t)gridDim.x * kBlock) {
+        if (!((dims >> d.dim[j]) & 1)) continue;
+        const int32_t n = d.len[j];
+        const int64_t s = d.col_ptr[j];
+        for (int32_t k = 0; k < n; k++) cof[atomicAdd(&end[d.rows[s + k]], 1)] = (int32_t)j;
+    }
+}
+
+// The faces of dimension b: the apparent ones paired, those neither apparent
+// nor known negative listed.
+__global__ void __launch_bounds__(kBlock) k_dual_cand(Dev d, DualState s, int32_t b)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t tiles = (d.m + kBlock - 1) / kBlock;
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t i = tile * kBlock + threadIdx.x;
+        bool list = false;
+        if (i < d.m && d.dim[i] == b) {
+            const int32_t t = d.left[i];
+            s.vlen[i] = 0;
+            const bool app = t != 0x7FFFFFFF && last_row(d, t) == (int32_t)i;
+            if (app) s.low_star[t] = (int32_t)i;
+            list = !app && d.low_star[i] == -1 && d.beta[i] < 0;
+        }
+        const uint64_t mk = __ballot(list);
+        if (mk) {
+            int32_t at = 0;
+            if (lane == __ffsll((long long)mk) - 1) at = atomicAdd(&s.count[0], __popcll(mk));
+            at = __shfl(at, __ffsll((long long)mk) - 1, kWave) + __popcll(mk & ((1ull << lane) - 1ull));
+            if (list) s.list[0][at] = make_int2(0, (int32_t)i);
+        }
+    }
+}
+
+// Faces of a matrix over the columns that hold them.
+struct CsrProv {
+    const int32_t *end, *cof;
+    __device__ void bind(int32_t) {}
+    __device__ int64_t key(int32_t i) const { return i; }
+    __device__ int32_t face(int64_t k) const { return (int32_t)k; }
+    __device__ int64_t col(int32_t t) const { return t; }
+    __device__ int32_t apparent(int32_t, int32_t ls) const { return ls; }
+    // its list
+    __device__ void load(int32_t i, int32_t &d0, int32_t &d1) const
+    {
+        d0 = i > 0 ? end[i - 1] : 0;
+        d1 = end[i];
+    }
+    __device__ int flip(const DualMap &map, int32_t, int32_t d0, int32_t d1, int32_t, DualCand &) const
+    {
+        int n = 0;
+#pragma unroll 4
+        for (int32_t q = d0 + (int32_t)(threadIdx.x & (kWave - 1)); q < d1; q += kWave, n++) map.toggle(cof[q]);
+        return n;
+    }
+    __device__ int flip_many(const DualMap &map, const int32_t *faces, int32_t cnt) const
+    {
+        const int lane = threadIdx.x & (kWave - 1);
+        int n = 0;
+        for (int32_t k0 = 0; k0 < cnt; k0 += kWave) {
+            int32_t d0, d1;
+            load(faces[min(k0 + lane, cnt - 1)], d0, d1);
+            for (int32_t k = 0; k < min(cnt - k0, (int32_t)kWave); k += 4) {
+                int32_t a[4], z[4], t[4];
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    const int32_t q = min(k + u, (int32_t)kWave - 1);
+                    a[u] = __builtin_amdgcn_readlane(d0, q) + lane;
+                    z[u] = k0 + k + u < cnt ? __builtin_amdgcn_readlane(d1, q) : 0;
+                }
+                while (a[0] < z[0] || a[1] < z[1] || a[2] < z[2] || a[3] < z[3]) {
+#pragma unroll
+                    for (int u = 0; u < 4; u++) t[u] = a[u] < z[u] ? cof[a[u]] : -1;
+#pragma unroll
+                    for (int u = 0; u < 4; u++) {
+                        if (t[u] >= 0) {
+                            map.toggle(t[u]);
+                            n++;
+                        }
+                        a[u] += kWave;
+                    }
+                }
+            }
+        }
+        return n;
+    }
+};
+
+// A block reduced from its rows into the reduction's state (as k_graph_apply),
+// or, when it was given up, its claims withdrawn.
+__global__ void __launch_bounds__(kBlock) k_dual_apply(Dev d, int32_t b, int ok, int compression)
+{
+    for (int64_t j = blockIdx.x * (int64_t)kBlock + threadIdx.x; j < d.m; j += (int64_t)gridDim.x * kBlock) {
+        if (d.dim[j] != b + 1) continue;
+        const int32_t x = d.low_star[j];
+        if (x == -1) continue;
+        if (!ok) {
+            d.low_star[j] = -1;
+            continue;
+        }
+        const int32_t i = x < -1 ? -2 - x : x;
+        d.low_star[j] = i;
+        d.piv[i] = (int32_t)j;
+        d.state[i] = ST_ZERO;
+        d.len[i] = 0;
+        if (compression) {
+            d.prec[j].k = -1;
+            atomicOr(&d.neg[j >> 5], 1u << (j & 31));
+        }
+    }
+}
+
+// The first active list: live columns of the dimensions no graph has solved.
+__device__ inline bool mix_keep(const Dev &d, int64_t j, int32_t solved)
+{
+    return d.state[j] == ST_ACTIVE && !((solved >> d.dim[j]) & 1);
+}
+
+// The dimensions whose columns are solved: those the host knows (dual), and
+// the graphs that turned out to be such.
+__device__ inline int32_t mix_solved(const Dev &d, int32_t top, int do_top, int32_t dual)
 {
     const int32_t bad = d.cnt->not_graph;
-    const bool g0 = !(bad & kNotGraph0), gt = do_top && !(bad & kNotGraphTop);
+    return dual | (bad & kNotGraph0 ? 0 : 2) | (do_top && !(bad & kNotGraphTop) ? 1 << top : 0);
+}
+
+__global__ void __launch_bounds__(kBlock) k_mix_count(Dev d, int32_t *keep_cnt, int32_t top, int do_top, int32_t dual)
+{
+    const int32_t solved = mix_solved(d, top, do_top, dual);
     const int64_t tiles = (d.m + kBlock - 1) / kBlock;
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         const int64_t j = tile * kBlock + threadIdx.x;
         int32_t tk;
-        block_excl_sum32(j < d.m && mix_keep(d, j, top, g0, gt) ? 1 : 0, &tk);
+        block_excl_sum32(j < d.m && mix_keep(d, j, solved) ? 1 : 0, &tk);
         if (threadIdx.x == 0) keep_cnt[tile] = tk;
     }
 }
 
 __global__ void __launch_bounds__(kBlock) k_mix_compact(Dev d, const int32_t *keep_off, int32_t *act, int32_t top,
-                                                        int do_top)
+                                                        int do_top, int32_t dual)
 {
-    const int32_t bad = d.cnt->not_graph;
-    const bool g0 = !(bad & kNotGraph0), gt = do_top && !(bad & kNotGraphTop);
+    const int32_t solved = mix_solved(d, top, do_top, dual);
     const int64_t tiles = (d.m + kBlock - 1) / kBlock;
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         const int64_t j = tile * kBlock + threadIdx.x;
-        const int keep = j < d.m && mix_keep(d, j, top, g0, gt);
+        const int keep = j < d.m && mix_keep(d, j, solved);
         int32_t tot;
         const int32_t pos = block_excl_sum32(keep, &tot);
         if (keep) act[keep_off[tile] + pos] = (int32_t)j;
     }
 }
 
-// The reduction starts from that list; with the top block solved the
-// dimension below is the one whose columns nothing clears any more.
-__global__ void k_mix_start(Dev d, int32_t top, int do_top)
+// The reduction starts from that list; below solved top dimensions, the first
+// unsolved one holds the columns nothing clears any more.
+__global__ void k_mix_start(Dev d, int32_t top, int do_top, int32_t dual)
 {
+    const int32_t solved = mix_solved(d, top, do_top, dual);
+    int32_t t = top;
+    while (t > 0 && ((solved >> t) & 1)) t--;
     d.cnt->n_cur = d.cnt->n_next;
     d.cnt->beta_counted = 1;
-    d.cnt->topdim = do_top && !(d.cnt->not_graph & kNotGraphTop) ? top - 1 : top;
+    d.cnt->topdim = t;
 }

@@ -47,7 +47,10 @@
 #include <string>
 #include <vector>
 
+#include "pms_build.h"
 #include "pms_common.h"
+#include "pms_dual.h"
+#include "pms_graph_place.h"
 
 namespace pms {
 
@@ -3030,6 +3033,15 @@ static pms_status grow_arena(Ctx *c, Dev &d, Counters *h, const ScratchSource &S
     return PMS_OK;
 }
 
+// Whether a reduction may solve blocks apart from the rounds: not when an
+// option, or the context's tuning, chooses or watches the rounds' schedule.
+static bool blocks_ok(const Ctx *c, const pms_options &o)
+{
+    return o.variant == 0 && o.compression && o.chain && o.max_rounds == 0 && o.graph_rounds == 0 && !o.sweep &&
+           o.arena_entries == 0 && !o.diagnostics && !o.debug_invariants && !o.c8 && !o.round_budget &&
+           tuning_builtin(c->tune);
+}
+
 // the options added after the first ones: ranges, and dim where they need it
 static bool extra_options_ok(const pms_options &o, const pms_boundary *bnd)
 {
@@ -3203,11 +3215,8 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     }
     const char *tr_env = getenv("PMS_TRACE");
     const int trace = tr_env && tr_env[0] == '1';
-    // The blocks that are graphs are solved apart, unless an option asks for
-    // a schedule of the rounds (or to watch them), which then hold every column
-    const bool blocks = bnd->dim && opt->variant == 0 && opt->compression && opt->chain && opt->max_rounds == 0 &&
-                        opt->graph_rounds == 0 && !opt->sweep && opt->arena_entries == 0 && !diag && !dbg && !c8on &&
-                        !budget && tuning_builtin(c->tune) && d.arena_cap * sizeof(int32_t) >= (size_t)m * 8;
+    // blocks solved apart from the rounds, which then hold the columns of the others
+    const bool blocks = bnd->dim && blocks_ok(c, *opt) && d.arena_cap * sizeof(int32_t) >= (size_t)m * 8;
     if (blocks) PMS_LAUNCH(c, K_GRAPH, dm, k_dim_count, grid_for(m, kBlock, 1024), kBlock, d);
     PMS_HIP(hipGetLastError());
 
@@ -3427,6 +3436,8 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
         const pms_status sb = stage_build(sd);
         if (sb != PMS_OK) return sb;
     }
+    int32_t block_rounds = 0;
+    int64_t block_active = 0;
     if (blocks && h->topdim >= 1 && h->topdim < 7) {
         const int32_t top = h->topdim;
         // a face with more than two cofaces is certain when the top simplices
@@ -3445,10 +3456,65 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
         }
         PMS_LAUNCH(c, K_GRAPH, dm + 20.0 * ((double)h->n_dim[0] + (do_top ? dt : 0)), k_graph_apply, gm, kBlock, d, top,
                    do_top, opt->compression);
-        PMS_LAUNCH(c, K_COMPACT, 2 * dm, k_mix_count, gm, kBlock, d, keep, top, do_top);
+        // blocks with many more cofaces than faces, from their rows, while the
+        // bitmap fits LDS and the lists the arena (nothing has moved there yet):
+        // cofaces, list entries, sums; the rest of the arena remembers the sums
+        int32_t dual = 0, dual_r = 0;
+        int64_t dual_active = 0;
+        if (m <= kDualLdsBits) {
+            for (int32_t b = 1; b < top; b++)
+                if ((int64_t)h->n_dim[b + 1] >= 2LL * h->n_dim[b] && h->n_dim[b] > 0) dual |= 2 << b;
+        }
+        if (dual) {
+            const unsigned nb = 256;
+            DualState s{};
+            s.vcap = 4096;
+            const int64_t a_end = 0, a_cof = a_end + m + 1, a_list = (a_cof + nnz + 2) & ~1ll, a_keys = a_list + 4 * m,
+                          a_cnt = a_keys + 3 * m, a_tmp = a_cnt + kDualCounters, a_sum = a_tmp + (int64_t)nb * s.vcap;
+            s.arena_cap = std::min<int64_t>((int64_t)d.arena_cap - a_sum, 1 << 28);
+            if (s.arena_cap < (1 << 18)) {
+                dual = 0;
+            } else {
+                int32_t *ar = d.arena;
+                const CsrProv pv{ar + a_end, ar + a_cof};
+                s.low_star = d.low_star;
+                s.list[0] = (int2 *)(ar + a_list);
+                s.list[1] = s.list[0] + m;
+                s.vstart = ar + a_keys;
+                s.vlen = s.vstart + m;
+                s.klow = s.vlen + m;
+                dual_counters(s, ar + a_cnt);
+                s.vtmp = ar + a_tmp;
+                s.arena = ar + a_sum;
+                s.nw0 = dual_words(m);
+                s.nw1 = dual_summary_words(m);
+                s.adds = &d.stats[(unsigned)S_ADDS * kStripe * 16];
+                s.entries = &d.stats[(unsigned)S_XE * kStripe * 16];
+                PMS_LAUNCH(c, K_FILL, 4 * dm, k_fill_i32, gm, kBlock, ar + a_end, m + 1, 0);
+                PMS_LAUNCH(c, K_DUAL, dm + 8 * dz, k_cof_count, gm, kBlock, d, dual, ar + a_end);
+                PMS_LAUNCH(c, K_SCAN, 8 * dm, k_scan_sum, 1, kScanThreads, ar + a_end, m, nullptr, ar + a_end + m);
+                PMS_LAUNCH(c, K_DUAL, dm + 12 * dz, k_cof_fill, gm, kBlock, d, dual, ar + a_end, ar + a_cof);
+                for (int32_t b = 1; b < top; b++) {
+                    if (!((dual >> (b + 1)) & 1)) continue;
+                    PMS_LAUNCH(c, K_FILL, 0, k_dual_counters, 1, kBlock, s, 1, 0);
+                    PMS_LAUNCH(c, K_DUAL, 5 * dm, k_dual_cand, gm, kBlock, d, s, b);
+                    int ok = 0;
+                    pms_status sr = dual_map_lds(c, pv, s);
+                    if (sr == PMS_OK)
+                        sr = dual_rounds(c, pv, s, [&](int r) { dual_launch(c, pv, s, nb, r); }, K_DUAL, &dual_r,
+                                         &dual_active, &ok);
+                    if (sr != PMS_OK) return sr;
+                    PMS_LAUNCH(c, K_DUAL, 5 * dm, k_dual_apply, gm, kBlock, d, b, ok, opt->compression);
+                    if (!ok) dual &= ~(2 << b);
+                }
+            }
+        }
+        block_rounds = 1 + dual_r;
+        block_active = dual_active;
+        PMS_LAUNCH(c, K_COMPACT, 2 * dm, k_mix_count, gm, kBlock, d, keep, top, do_top, dual);
         PMS_LAUNCH(c, K_SCAN, 8.0 * nblk, k_scan_sum, 1, kScanThreads, keep, nblk, nullptr, &d.cnt->n_next);
-        PMS_LAUNCH(c, K_COMPACT, 2 * dm, k_mix_compact, gm, kBlock, d, keep, act0, top, do_top);
-        PMS_LAUNCH(c, K_FILL, 0, k_mix_start, 1, 1, d, top, do_top);
+        PMS_LAUNCH(c, K_COMPACT, 2 * dm, k_mix_compact, gm, kBlock, d, keep, act0, top, do_top, dual);
+        PMS_LAUNCH(c, K_FILL, 0, k_mix_start, 1, 1, d, top, do_top, dual);
         PMS_HIP(hipGetLastError());
         PMS_HIP(hipMemcpyAsync(h, d.cnt, sizeof(Counters), hipMemcpyDeviceToHost, st));
         PMS_HIP(hipStreamSynchronize(st));
@@ -3687,10 +3753,10 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
         const pms_status sdb = dbg_check("at the end, after round", (int32_t)round);
         if (sdb != PMS_OK) return sdb;
     }
-    res->rounds = (int32_t)round + (blocks ? 1 : 0);  // (the graphs' pass is one)
+    res->rounds = (int32_t)round + block_rounds;  // (the graphs' pass is one)
     res->additions = (int64_t)h->additions;
     res->xor_entries = (int64_t)h->xor_entries;
-    res->active_sum = (int64_t)h->active_sum;
+    res->active_sum = (int64_t)h->active_sum + block_active;
     res->addition_bytes =
         (int64_t)(h->abytes_xor + h->abytes_lane + h->abytes_wide + h->abytes_chain + h->abytes_solve);
     res->phase0_pivots = h->beta_pivots;
@@ -3815,7 +3881,7 @@ pms_status pms_create(pms_ctx **ctx, int device, void *stream)
     if (!c) return PMS_ERR_OOM;
     c->device = device;
     c->stream = (hipStream_t)stream;
-    if (hipHostMalloc(&c->host_pinned, 2 * sizeof(pms::Counters), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&c->host_pinned, std::max<size_t>(2 * sizeof(pms::Counters), 2048), hipHostMallocDefault) != hipSuccess) {
         delete c;
         return PMS_ERR_OOM;
     }
@@ -3867,7 +3933,7 @@ static const char *const kKernelNames[pms::K_NUM] = {
     "k_init", "k_beta", "k_low", "k_collide", "k_scan", "k_pivots", "k_xor", "k_compact", "k_finalize", "k_fill",
     "k_defrag", "k_ls_keys", "k_sort", "k_ls_index", "k_build_scan", "k_ls_rows", "k_vr_edges", "k_vr_tri",
     "k_vr_index", "k_vr_rows", "k_backward", "k_chain", "k_chain_lane", "k_chain_wide", "k_c8", "k_budget",
-    "k_chain_solve", "k_ls_left", "k_graph"};
+    "k_chain_solve", "k_ls_left", "k_graph", "k_dual"};
 
 pms_status pms_profile_enable(pms_ctx *c, int enable)
 {
@@ -4202,6 +4268,46 @@ pms_status pms_reduce_batched(pms_ctx *c, int32_t count, const int64_t *inst_col
     PMS_HIP(hipStreamSynchronize(c->stream));
     if (c->prof_on) pms::prof_flush(c);
     return PMS_OK;
+}
+
+// A filtration's matrix, for the entry points that take one.
+static pms_boundary filtration_boundary(const pms::Filtration *f)
+{
+    pms_boundary b{};
+    b.m = f->m;
+    b.col_ptr = f->col_ptr;
+    b.rows = f->rows;
+    b.dim = f->dim;
+    b.left = f->has_left_beta ? f->left : nullptr;
+    b.beta = f->has_left_beta ? f->beta : nullptr;
+    return b;
+}
+
+pms_status pms_reduce_filtration(pms_ctx *c, const pms_filtration *fh, int32_t count, const int64_t *inst_col_off,
+                                 const pms_options *opt, pms_result *res, int64_t *inst_pair_off, int64_t *inst_ess_off,
+                                 int32_t *pair_inst)
+{
+    if (!c) return PMS_ERR_INVALID_ARG;
+    c->err.clear();
+    const pms::Filtration *f = reinterpret_cast<const pms::Filtration *>(fh);
+    if (!f || !res || (inst_col_off && count < 1))
+        return pms::set_err(c, PMS_ERR_INVALID_ARG, "null filtration / result, or count < 1");
+    const pms_boundary bnd = filtration_boundary(f);
+    const pms_options o = opt ? *opt : pms_default_options();
+    if (f->vr_count > 0 && f->m > 0 && res->low_star && !o.validate && pms::blocks_ok(c, o) && o.priority >= 0 &&
+        o.priority <= 2 && o.reserved == 0) {
+        if (hipSetDevice(c->device) != hipSuccess) return pms::set_err(c, PMS_ERR_HIP, "hipSetDevice failed");
+        res->n_pairs = res->n_essential = 0;
+        res->rounds = res->phase0_pivots = 0;
+        res->additions = res->xor_entries = res->active_sum = res->addition_bytes = 0;
+        c->diag.clear();
+        c->diag_m = -1;
+        int done = 0;
+        const pms_status s = pms::reduce_vr(c, f, res, count, inst_col_off, inst_pair_off, inst_ess_off, pair_inst, &done);
+        if (s != PMS_OK || done) return s;
+    }
+    return inst_col_off ? pms_reduce_batched(c, count, inst_col_off, &bnd, opt, res, inst_pair_off, inst_ess_off, pair_inst)
+                        : pms_reduce(c, &bnd, opt, res);
 }
 
 }  // extern "C"

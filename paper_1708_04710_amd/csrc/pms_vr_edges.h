@@ -25,7 +25,8 @@ constexpr int32_t kVeMaxTies = 64, kVeMaxTies3 = 8;
 constexpr uint32_t kTied = 0x80000000u;     // rec.y of an edge in a tie group
 
 struct VeCloud {
-    int32_t n, D, W, has_thr;   // points, coordinates, 32-bit mask words per edge
+    int32_t n, D, W, M;         // points, coordinates, mask words of 32 and 64 per edge
+    int32_t has_thr, pad;
     int64_t thr_i;
     float thr_f;
     int32_t E;                  // edges
@@ -33,7 +34,7 @@ struct VeCloud {
     int64_t slot_base;          // start of its n x n matrices
     int64_t cap_off;            // start of its edges in the capacity-sized scratch
     int64_t eoff;               // start of its edges (E + 1 entries)
-    int64_t woff;               // start of its mask words (E W entries)
+    int64_t woff, moff;         // start of its mask words of 32 and 64 (E W and E M entries)
     int64_t T, Q;               // triangles, tetrahedra
     int64_t col_base, nnz_base; // first column, first row entry
     int64_t toff;               // its first triangle among all clouds' (dimension 3)
@@ -53,9 +54,12 @@ struct VeView {
     const int32_t *gst, *gend;// [edge] its tie group's ranks [gst, gend)
     const int32_t *tscan;     // [edge, E + 1] triangles before it
     const int64_t *q2;        // [triangle, T + 1] all clouds' tetrahedra before its own (dimension 3)
+    const uint64_t *mask;     // [moff + edge M + c / 64] rec's x in words of 64
+    const int32_t *apc;       // [edge] the third vertex of that triangle, -1: none
     const int32_t *app;       // [edge] index of the triangle it forms an apparent pair with, -1: none
     const uint32_t *recd;     // [edge W + c / 32] dense number of the first triangle of the word (dimension 3)
     const uint2 *rec2;        // [(toff + dense) W2 + d / 32] like rec for the tetrahedra (e, c, d), d > c
+    const int32_t *trip;      // [toff + k] index within the cloud of its k-th triangle (dimension 3)
     const int32_t *appt;      // [column] index of the tetrahedron a triangle is apparent with, -1: none
 };
 
