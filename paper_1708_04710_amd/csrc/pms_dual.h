@@ -18,13 +18,14 @@
 // state before it); of the faces that claim one coface the last one owns it
 // and the others, a displaced owner among them, are active again.
 //
-// One wavefront per face.  The column is a bitmap over the cofaces, with a
-// summary of one bit per word: lows only grow, so the next one is found by a
-// scan from the last, an addition is one atomic per coface and costs the same
-// for any fill-in (36 000 cofaces of 342 000 on a circle), and a column is
-// remembered as the list of faces it is the sum of, not as its cofaces.
-// Bound by the latency of one addition (two dependent loads, the flips, the
-// scan) times the longest chain of them.
+// One workgroup per face.  The column is a bitmap over the cofaces in LDS,
+// with a summary of one bit per word: lows only grow, so the next one is found
+// by a scan from the last, an addition is one LDS atomic per coface and costs
+// the same for any fill-in (36 000 cofaces of 342 000 on a circle), and a
+// column is remembered as the list of faces it is the sum of, not as its
+// cofaces.  Cofaces beyond the bitmap's reach wait in a list until the lows
+// get there and the bitmap moves on.  Bound by the latency of one addition
+// (dependent loads, the flips, the scan) times the longest chain of them.
 #pragma once
 
 #include "pms_common.h"
@@ -33,11 +34,10 @@ namespace pms {
 
 constexpr int kDualRounds = 256;  // rounds the counters have room for
 constexpr int kDualCounters = 2 * kDualRounds + 3;
-// Bits of a bitmap in LDS: with its summary 148 KB of a CU's 160 KB.
+// Most bits of a bitmap: with its summary 148 KB of a CU's 160 KB.
 constexpr int64_t kDualLdsBits = 1150000;
 inline int64_t dual_words(int64_t bits) { return (bits + 31) / 32; }
-// LDS bytes of a workgroup: the words (when in LDS) and the summary, padded
-// to whole wavefronts of words.
+// Words of its summary, whole wavefronts of them.
 inline int64_t dual_summary_words(int64_t bits) { return ((dual_words(bits) + 31) / 32 + kWave - 1) / kWave * kWave; }
 
 struct DualState {
@@ -54,7 +54,8 @@ struct DualState {
     int64_t arena_cap;
     int32_t *vtmp;             // [workgroup, vcap] the sum being built
     int32_t vcap;
-    uint32_t *words;           // [workgroup, nw0] bitmaps beyond LDS (all zero between faces), or null
+    int32_t *ovf;              // [workgroup, ovf_cap] cofaces beyond the bitmap, or null (it holds the instance)
+    int32_t ovf_cap;
     int64_t nw0, nw1;          // words of a bitmap and of its summary
     unsigned long long *adds, *entries;
 };
@@ -67,29 +68,34 @@ inline void dual_counters(DualState &s, int32_t *p)
     s.head = s.count + kDualRounds + 1;
 }
 
+template <int kT>
 struct DualMap {
-    uint32_t *w;   // words (LDS or global)
-    uint32_t *s;   // summary (LDS): bit k: word k may be non-zero
-    bool lds;
-    int64_t nw1;
+    uint32_t *w;      // words (LDS)
+    uint32_t *s;      // summary (LDS): bit k: word k may be non-zero
+    int32_t *ovf;     // cofaces beyond the bitmap
+    int32_t *n_ovf;   // (LDS)
+    int32_t ovf_cap;
+    int32_t base;     // the first coface of the bitmap, a multiple of 1024
     uint32_t bits;
+    int32_t nw1;
     __device__ void toggle(int32_t t) const
     {
-        if ((uint32_t)t >= bits) return;  // never (cofaces of one instance); a bound, not a branch
-        atomicXor(&w[t >> 5], 1u << (t & 31));
-        atomicOr(&s[t >> 10], 1u << ((t >> 5) & 31));
+        const uint32_t k = (uint32_t)(t - base);  // (below base: cancels, nothing below the low is left)
+        if (k < bits) {
+            atomicXor(&w[k >> 5], 1u << (k & 31));
+            atomicOr(&s[k >> 10], 1u << ((k >> 5) & 31));
+        } else if (ovf && t >= base) {
+            const int32_t at = atomicAdd(n_ovf, 1);
+            if (at < ovf_cap) ovf[at] = t;
+        }
     }
-    __device__ uint32_t load(int64_t k) const
-    {
-        return lds ? w[k] : __hip_atomic_load(&w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // The smallest set coface >= from, -1 when none; the whole wavefront, all
-    // lanes' flips before it done (__syncthreads).
-    __device__ int32_t next(int32_t from) const
+    // The smallest set coface >= from in the bitmap, -1 when none; every
+    // wavefront by itself, all flips before it done.
+    __device__ int32_t scan(int32_t from) const
     {
         const int lane = threadIdx.x & (kWave - 1);
-        const int32_t w0 = from >> 5;  // words before it are zero from here on
-        for (int64_t b = (w0 >> 5) / kWave * kWave; b < nw1; b += kWave) {
+        const int32_t f = max(from - base, 0), w0 = f >> 5;  // words before it are zero from here on
+        for (int32_t b = (w0 >> 5) / kWave * kWave; b < nw1; b += kWave) {
             uint32_t x = s[b + lane];
             if (b + lane < (w0 >> 5)) x = 0;
             else if (b + lane == (w0 >> 5)) x &= ~0u << (w0 & 31);
@@ -98,33 +104,56 @@ struct DualMap {
                 const int l = __ffsll((long long)m) - 1;
                 const uint32_t xs = (uint32_t)__builtin_amdgcn_readlane((int)x, l);
                 int32_t k = -1;  // the words of this summary word, one per lane
-                if (lane < 32 && ((xs >> lane) & 1u)) k = (int32_t)(((b + l) << 5) + lane);
-                uint32_t v = k >= 0 ? load(k) : 0u;
-                if (k >= 0 && k == w0) v &= ~0u << (from & 31);
+                if (lane < 32 && ((xs >> lane) & 1u)) k = ((b + l) << 5) + lane;
+                uint32_t v = k >= 0 ? w[k] : 0u;
+                if (k == w0) v &= ~0u << (f & 31);
                 const uint64_t z = __ballot(v != 0);
                 if (z) {
-                    const int f = __ffsll((long long)z) - 1;
-                    const uint32_t vf = (uint32_t)__builtin_amdgcn_readlane((int)v, f);
-                    return (int32_t)((((b + l) << 5) + f) * 32 + __ffs((int)vf) - 1);
+                    const int g = __ffsll((long long)z) - 1;
+                    const uint32_t vg = (uint32_t)__builtin_amdgcn_readlane((int)v, g);
+                    return base + (((b + l) << 5) + g) * 32 + __ffs((int)vg) - 1;
                 }
                 m &= m - 1;
             }
         }
         return -1;
     }
-    // Every word back to zero.
+    // The smallest set coface >= from, moving the bitmap on when it is used up.
+    __device__ int32_t next(int32_t from, int32_t *s_min)
+    {
+        for (;;) {
+            const int32_t t = scan(from);
+            __syncthreads();  // scanned by every wavefront before it changes
+            if (t >= 0 || !ovf) return t;
+            const int32_t n = min(*n_ovf, ovf_cap);
+            if (n == 0) return -1;
+            clear();
+            if (threadIdx.x == 0) *s_min = 0x7FFFFFFF;
+            __syncthreads();
+            int32_t mn = 0x7FFFFFFF;
+            for (int32_t k = threadIdx.x; k < n; k += kT) mn = min(mn, ovf[k]);
+            atomicMin(s_min, mn);
+            __syncthreads();
+            base = *s_min & ~1023;
+            __syncthreads();
+            if (threadIdx.x == 0) *n_ovf = 0;
+            __syncthreads();
+            // what stays beyond is moved down, behind the entries read
+            for (int32_t k0 = 0; k0 < n; k0 += kT) {
+                const int32_t x = k0 + (int32_t)threadIdx.x < n ? ovf[k0 + threadIdx.x] : -1;
+                __syncthreads();
+                if (x >= 0) toggle(x);
+                __syncthreads();
+            }
+        }
+    }
+    // Every word back to zero (each thread the words of its summary words).
     __device__ void clear() const
     {
-        const int lane = threadIdx.x & (kWave - 1);
-        for (int64_t b = 0; b < nw1; b += kWave) {
-            uint32_t x = s[b + lane];
-            if (x) s[b + lane] = 0;
-            while (x) {
-                const int64_t k = ((b + lane) << 5) + __ffs((int)x) - 1;
-                x &= x - 1;
-                if (lds) w[k] = 0;
-                else __hip_atomic_store(&w[k], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+        for (int32_t b = threadIdx.x; b < nw1; b += kT) {
+            uint32_t x = s[b];
+            if (x) s[b] = 0;
+            for (; x; x &= x - 1) w[(b << 5) + __ffs((int)x) - 1] = 0;
         }
     }
 };
@@ -137,34 +166,41 @@ struct DualCand {
     int32_t t, f, d0, d1;
 };
 
-// kLds: the bitmap's words are in LDS.  P: the cofaces of a face
-//   bind(instance), key(face), face(key); col(t): the column of coface t
+// P: the cofaces of a face, for workgroups of P::kT threads
+//   bind(instance), key(face), face(key); col(t): the column of coface t;
+//   floor(face): no coface of it is smaller
 //   load(face, d0, d1): the data flip needs
-//   int flip(map, face, d0, d1, cur, cand): flips the face's cofaces, returns
-//     their number in this lane and fills cand (cofaces beyond cur)
+//   int flip(map, face, d0, d1, cur, cand): flips the face's cofaces (the whole
+//     workgroup), returns their number in this lane and fills cand (cofaces beyond cur)
 //   int flip_many(map, faces, n): the same for a list, several faces' loads in flight
 //   int32_t apparent(t, v): the face of coface t whose low_star is v >= 0 (-1: no such face)
-template <class P, bool kLds>
-__global__ void __launch_bounds__(kWave) k_dual(P prov, DualState s, int round)
+template <class P>
+__global__ void __launch_bounds__(P::kT) k_dual(P prov, DualState s, int round)
 {
+    constexpr int kT = P::kT;
     extern __shared__ uint32_t s_map[];
+    __shared__ int32_t s_q, s_ovf, s_min, s_at, s_cand[4];
     const int32_t n = s.count[round];
     if ((int32_t)blockIdx.x >= n || *s.fail) return;
-    const int lane = threadIdx.x;
-    DualMap map;
-    map.lds = kLds;
+    const int tid = threadIdx.x;
+    DualMap<kT> map;
     map.s = s_map;
-    map.nw1 = s.nw1;
+    map.w = s_map + s.nw1;
+    map.nw1 = (int32_t)s.nw1;
     map.bits = (uint32_t)(s.nw0 * 32);
-    map.w = kLds ? s_map + s.nw1 : s.words + (int64_t)blockIdx.x * s.nw0;
-    for (int64_t k = lane; k < s.nw1 + (kLds ? s.nw0 : 0); k += kWave) s_map[k] = 0;
-    __syncthreads();
+    map.ovf = s.ovf ? s.ovf + (int64_t)blockIdx.x * s.ovf_cap : nullptr;
+    map.ovf_cap = s.ovf_cap;
+    map.n_ovf = &s_ovf;
+    for (int64_t k = tid; k < s.nw1 + s.nw0; k += kT) s_map[k] = 0;
     int32_t *v = s.vtmp + (int64_t)blockIdx.x * s.vcap;
     unsigned long long adds = 0, entries = 0;
     for (;;) {
-        int32_t q = 0;
-        if (lane == 0) q = atomicAdd(&s.head[round], 1);
-        q = bcast_first(q);
+        if (tid == 0) {
+            s_q = atomicAdd(&s.head[round], 1);
+            s_ovf = 0;
+        }
+        __syncthreads();
+        const int32_t q = bcast_first(s_q);
         if (q >= n) break;
         const int2 it = s.list[round & 1][q];
         const int32_t face = bcast_first(it.y);
@@ -175,30 +211,46 @@ __global__ void __launch_bounds__(kWave) k_dual(P prov, DualState s, int round)
         DualCand cand{0x7FFFFFFF, -1, 0, 0};
         if (n0 == 0) {
             int32_t d0, d1;
-            if (lane == 0) v[0] = face;
+            map.base = prov.floor(face) & ~1023;
+            if (tid == 0) v[0] = face;
             prov.load(face, d0, d1);
             entries += prov.flip(map, face, d0, d1, -1, cand);
         } else {
             const int32_t *a = s.arena + s.vstart[key];
             cur = s.klow[key];
+            map.base = cur & ~1023;
             nv = n0;
-            for (int32_t k = lane; k < n0; k += kWave) v[k] = a[k];
+            for (int32_t k = tid; k < n0; k += kT) v[k] = a[k];
             entries += prov.flip_many(map, a, n0);
         }
         int32_t t;
         bool full = false;
         for (;;) {
             __syncthreads();  // the flips are done
-            if (!kLds) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): also in memory
-            t = map.next(cur);
+            if (s_ovf > s.ovf_cap && s.ovf) { full = true; break; }
+            t = map.next(cur, &s_min);
             if (t < 0) break;
-            const uint64_t known = __ballot(cand.t == t);
             int32_t f = -1, d0 = 0, d1 = 0;
-            if (known) {
-                const int l = __ffsll((long long)known) - 1;
-                f = __builtin_amdgcn_readlane(cand.f, l);
-                d0 = __builtin_amdgcn_readlane(cand.d0, l);
-                d1 = __builtin_amdgcn_readlane(cand.d1, l);
+            if (kT == kWave) {
+                const uint64_t known = __ballot(cand.t == t);
+                if (known) {
+                    const int l = __ffsll((long long)known) - 1;
+                    f = __builtin_amdgcn_readlane(cand.f, l);
+                    d0 = __builtin_amdgcn_readlane(cand.d0, l);
+                    d1 = __builtin_amdgcn_readlane(cand.d1, l);
+                }
+            } else {
+                if (tid == 0) s_cand[0] = -1;
+                __syncthreads();
+                if (cand.t == t) {  // (one lane: a coface is flipped once per addition)
+                    s_cand[0] = cand.f;
+                    s_cand[1] = cand.d0;
+                    s_cand[2] = cand.d1;
+                }
+                __syncthreads();
+                f = bcast_first(s_cand[0]);
+                d0 = bcast_first(s_cand[1]);
+                d1 = bcast_first(s_cand[2]);
             }
             int64_t ko = -1;
             if (f < 0) {
@@ -217,7 +269,7 @@ __global__ void __launch_bounds__(kWave) k_dual(P prov, DualState s, int round)
             cand.t = 0x7FFFFFFF;
             if (ko < 0) {
                 if (nv >= s.vcap) { full = true; break; }
-                if (lane == 0) v[nv] = f;
+                if (tid == 0) v[nv] = f;
                 nv++;
                 entries += prov.flip(map, f, d0, d1, t, cand);
             } else {
@@ -225,34 +277,34 @@ __global__ void __launch_bounds__(kWave) k_dual(P prov, DualState s, int round)
                 if (nv + no > s.vcap) { full = true; break; }
                 if (s.vlen[ko] > 0) {
                     const int32_t *a = s.arena + s.vstart[ko];
-                    for (int32_t k = lane; k < no; k += kWave) v[nv + k] = a[k];
+                    for (int32_t k = tid; k < no; k += kT) v[nv + k] = a[k];
                     entries += prov.flip_many(map, a, no);
                 } else {
                     f = prov.face(ko);
-                    if (lane == 0) v[nv] = f;
+                    if (tid == 0) v[nv] = f;
                     prov.load(f, d0, d1);
                     entries += prov.flip(map, f, d0, d1, t, cand);
                 }
                 nv += no;
             }
-            adds++;
+            if (tid == 0) adds++;
         }
         // remember the sum (itself alone needs no list)
+        __syncthreads();
         if (!full && nv > 1 && t >= 0) {
-            int32_t at = 0;
-            if (lane == 0) at = atomicAdd(s.arena_top, nv);
-            at = bcast_first(at);
+            if (tid == 0) s_at = atomicAdd(s.arena_top, nv);
+            __syncthreads();  // (v is written, too)
+            const int32_t at = s_at;
             if (at < 0 || (int64_t)at + nv > s.arena_cap) full = true;
             else {
-                __syncthreads();  // v is written
-                for (int32_t k = lane; k < nv; k += kWave) s.arena[at + k] = v[k];
-                if (lane == 0) {
+                for (int32_t k = tid; k < nv; k += kT) s.arena[at + k] = v[k];
+                if (tid == 0) {
                     s.vstart[key] = at;
                     s.vlen[key] = nv;
                 }
             }
         }
-        if (lane == 0) {
+        if (tid == 0) {
             s.klow[key] = t;
             if (full) *s.fail = 1;
         }
@@ -263,7 +315,7 @@ __global__ void __launch_bounds__(kWave) k_dual(P prov, DualState s, int round)
     // entries are counted per lane
     long long e = (long long)entries;
     for (int o = kWave / 2; o > 0; o >>= 1) e += __shfl_xor(e, o, kWave);
-    if (lane == 0) {
+    if ((tid & (kWave - 1)) == 0) {
         if (adds) atomicAdd(s.adds, adds);
         if (e) atomicAdd(s.entries, (unsigned long long)e);
     }
@@ -309,17 +361,14 @@ static __global__ void k_dual_counters(DualState s, int first, int32_t n)
 template <class P>
 inline pms_status dual_map_lds(Ctx *c, const P &, const DualState &s)
 {
-    const int lds = (int)((s.nw1 + (s.words ? 0 : s.nw0)) * 4);
-    const void *fn = s.words ? (const void *)k_dual<P, false> : (const void *)k_dual<P, true>;
-    PMS_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    PMS_HIP(hipFuncSetAttribute((const void *)k_dual<P>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)((s.nw1 + s.nw0) * 4)));
     return PMS_OK;
 }
 template <class P>
 inline void dual_launch(Ctx *c, const P &prov, const DualState &s, unsigned blocks, int round)
 {
-    const size_t lds = (size_t)(s.nw1 + (s.words ? 0 : s.nw0)) * 4;
-    if (s.words) k_dual<P, false><<<blocks, kWave, lds, c->stream>>>(prov, s, round);
-    else k_dual<P, true><<<blocks, kWave, lds, c->stream>>>(prov, s, round);
+    k_dual<P><<<blocks, P::kT, (size_t)(s.nw1 + s.nw0) * 4, c->stream>>>(prov, s, round);
 }
 
 // Runs the rounds of one block, launch(r) issuing round r's additions.

@@ -254,7 +254,9 @@ __global__ void __launch_bounds__(kBlock) k_dual_cand(Dev d, DualState s, int32_
 
 // Faces of a matrix over the columns that hold them.
 struct CsrProv {
+    static constexpr int kT = kWave;
     const int32_t *end, *cof;
+    __device__ int32_t floor(int32_t i) const { return i; }
     __device__ void bind(int32_t) {}
     __device__ int64_t key(int32_t i) const { return i; }
     __device__ int32_t face(int64_t k) const { return (int32_t)k; }
@@ -266,14 +268,14 @@ struct CsrProv {
         d0 = i > 0 ? end[i - 1] : 0;
         d1 = end[i];
     }
-    __device__ int flip(const DualMap &map, int32_t, int32_t d0, int32_t d1, int32_t, DualCand &) const
+    __device__ int flip(const DualMap<kT> &map, int32_t, int32_t d0, int32_t d1, int32_t, DualCand &) const
     {
         int n = 0;
 #pragma unroll 4
         for (int32_t q = d0 + (int32_t)(threadIdx.x & (kWave - 1)); q < d1; q += kWave, n++) map.toggle(cof[q]);
         return n;
     }
-    __device__ int flip_many(const DualMap &map, const int32_t *faces, int32_t cnt) const
+    __device__ int flip_many(const DualMap<kT> &map, const int32_t *faces, int32_t cnt) const
     {
         const int lane = threadIdx.x & (kWave - 1);
         int n = 0;

@@ -222,8 +222,11 @@ __global__ void __launch_bounds__(kWave) k_vr_cocycle(VeView v, DualState s, int
     }
 }
 
-// Triangles (by index within their cloud) over tetrahedra.
+// Triangles (by index within their cloud) over tetrahedra: eight wavefronts, a
+// lane per fourth vertex (of the up to 512 at a time), so that an addition is
+// three dependent loads whatever the cloud's size; lists a face per wavefront.
 struct VrTriProv {
+    static constexpr int kT = 512;
     VeView v;
     const int4 *verts;
     VeCloud I;
@@ -231,6 +234,7 @@ struct VrTriProv {
     __device__ int64_t key(int32_t p) const { return I.col_base + p; }
     __device__ int32_t face(int64_t k) const { return (int32_t)(k - I.col_base); }
     __device__ int64_t col(int32_t t) const { return I.col_base + t; }
+    __device__ int32_t floor(int32_t p) const { return p; }
     __device__ int32_t apparent(int32_t, int32_t ls) const { return (int32_t)(ls - I.col_base); }
     // the triangle's vertices, 16 bits each
     __device__ void load(int32_t p, int32_t &d0, int32_t &d1) const
@@ -239,7 +243,9 @@ struct VrTriProv {
         d0 = (int32_t)((uint32_t)(q.x - I.pbase) << 16 | (uint32_t)(q.y - I.pbase));
         d1 = (int32_t)(q.z - I.pbase);
     }
-    __device__ int flip(const DualMap &map, int32_t, int32_t d0, int32_t d1, int32_t cur, DualCand &cand) const
+    // the cofaces with d = first, first + step, ..
+    __device__ int cofaces(const DualMap<kT> &map, int32_t d0, int32_t d1, int first, int step, int32_t cur,
+                           DualCand &cand) const
     {
         const int x = (int)((uint32_t)d0 >> 16), y = (int)((uint32_t)d0 & 0xFFFFu), z = d1;
         const int32_t *R = v.erank + I.slot_base;
@@ -249,23 +255,43 @@ struct VrTriProv {
         int n = 0;
         int32_t best = 0x7FFFFFFF, bl = 0;
         int bd = 0;
-#pragma unroll 2
-        for (int d = threadIdx.x & (kWave - 1); d < I.n; d += kWave) {
-            const int32_t xd = rx[d], yd = ry[d], zd = rz[d];
-            if (xd == kNoEdge || yd == kNoEdge || zd == kNoEdge) continue;
-            const int32_t l = max(max(xyz, xd), max(yd, zd));
-            int s = off, t = d;  // the two vertices off the latest edge
-            if (l != xyz) {
-                s = l == xd ? y : x;
-                t = l == zd ? y : z;
+        constexpr int kAhead = 4;
+        for (int e0 = first; e0 < I.n; e0 += kAhead * step) {
+            int32_t xd[kAhead], yd[kAhead], zd[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; u++) {
+                const int d = e0 + u * step < I.n ? e0 + u * step : x;  // (the diagonal is no edge)
+                xd[u] = rx[d];
+                yd[u] = ry[d];
+                zd[u] = rz[d];
             }
-            const int32_t p = ve_tet(v, I, l, min(s, t), max(s, t));
-            map.toggle(p);
-            n++;
-            if (p > cur && p < best) {
-                best = p;
-                bl = l;
-                bd = max(s, t);
+            int32_t l[kAhead], p[kAhead];
+            int s[kAhead], t[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; u++) {
+                const int d = e0 + u * step;
+                l[u] = -1;
+                s[u] = off;
+                t[u] = d;  // the two vertices off the latest edge
+                if (xd[u] == kNoEdge || yd[u] == kNoEdge || zd[u] == kNoEdge) continue;
+                l[u] = max(max(xyz, xd[u]), max(yd[u], zd[u]));
+                if (l[u] != xyz) {
+                    s[u] = l[u] == xd[u] ? y : x;
+                    t[u] = l[u] == zd[u] ? y : z;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; u++) p[u] = l[u] >= 0 ? ve_tet(v, I, l[u], min(s[u], t[u]), max(s[u], t[u])) : -1;
+#pragma unroll
+            for (int u = 0; u < kAhead; u++) {
+                if (p[u] < 0) continue;
+                map.toggle(p[u]);
+                n++;
+                if (p[u] > cur && p[u] < best) {
+                    best = p[u];
+                    bl = l[u];
+                    bd = max(s[u], t[u]);
+                }
             }
         }
         cand.t = best;
@@ -282,14 +308,18 @@ struct VrTriProv {
         }
         return n;
     }
-    __device__ int flip_many(const DualMap &map, const int32_t *faces, int32_t cnt) const
+    __device__ int flip(const DualMap<kT> &map, int32_t, int32_t d0, int32_t d1, int32_t cur, DualCand &cand) const
+    {
+        return cofaces(map, d0, d1, (int)threadIdx.x, kT, cur, cand);
+    }
+    __device__ int flip_many(const DualMap<kT> &map, const int32_t *faces, int32_t cnt) const
     {
         int n = 0;
         DualCand unused;
-        for (int32_t k = 0; k < cnt; k++) {
+        for (int32_t k = threadIdx.x / kWave; k < cnt; k += kT / kWave) {
             int32_t d0, d1;
             load(faces[k], d0, d1);
-            n += flip(map, faces[k], d0, d1, 0x7FFFFFFE, unused);
+            n += cofaces(map, d0, d1, (int)(threadIdx.x & (kWave - 1)), kWave, 0x7FFFFFFE, unused);
         }
         return n;
     }
@@ -528,23 +558,21 @@ pms_status reduce_vr(Ctx *c, const Filtration *f, pms_result *res, int32_t count
     // the bitmaps: in LDS when the largest cloud's fits (as many workgroups as
     // a CU's LDS holds), else in memory
     DualState s{};
-    // workgroups of one wavefront: as many as a CU's LDS holds.  Edges: a bit
-    // matrix of the points.  Triangles: a bitmap of the cloud, in LDS when it fits.
+    // workgroups: as many as the CUs' LDS holds.  Edges: a bit matrix of the
+    // points.  Triangles: a bitmap of the cloud, or of as much as fits.
     auto resident = [&](int64_t lds_bytes) {
         return 256 * std::max<int64_t>(1, std::min<int64_t>(16, 160 * 1024 / (lds_bytes + 512)));
     };
     unsigned blocks_of[2] = {1, 1};
     blocks_of[0] = (unsigned)std::min<int64_t>(resident((int64_t)f->vr_max_n * ((f->vr_max_n + 63) / 64) * 8),
                                                std::max<int64_t>(f->vr_edges, 1));
-    int64_t words_all = 0;
     if (maxdim >= 3) {
-        const bool lds = f->vr_max_m <= kDualLdsBits;
-        s.nw0 = dual_words(f->vr_max_m);
-        s.nw1 = dual_summary_words(f->vr_max_m);
-        const int64_t lds_bytes = (s.nw1 + (lds ? s.nw0 : 0)) * 4;
-        if (lds_bytes > 150 * 1024) return PMS_OK;  // (a summary alone beyond LDS: 39 M simplices in one cloud)
-        blocks_of[1] = (unsigned)std::min<int64_t>(lds ? resident(lds_bytes) : 512, std::max<int64_t>(nkey, 1));
-        if (!lds) words_all = (int64_t)blocks_of[1] * s.nw0;
+        const int64_t bits = std::min<int64_t>(f->vr_max_m, kDualLdsBits);
+        s.nw0 = dual_words(bits);
+        s.nw1 = dual_summary_words(bits);
+        blocks_of[1] = (unsigned)std::min<int64_t>(std::min<int64_t>(resident((s.nw1 + s.nw0) * 4), 1024),
+                                                   std::max<int64_t>(nkey, 1));
+        if (f->vr_max_m > kDualLdsBits) s.ovf_cap = 1 << 18;
     }
     const unsigned blocks = blocks_of[1];
     s.vcap = 8192;
@@ -558,8 +586,8 @@ pms_status reduce_vr(Ctx *c, const Filtration *f, pms_result *res, int32_t count
     uint32_t *bits = (uint32_t *)grow_scratch(c, B_NEG, (size_t)nwords * 4);
     int32_t *tile_d = (int32_t *)grow_scratch(c, B_AGG2, (size_t)tiles * 4);
     int32_t *tile_e = (int32_t *)grow_scratch(c, B_FLAGS, (size_t)tiles * 4);
-    s.words = words_all ? (uint32_t *)grow_scratch(c, B_DUAL5, (size_t)words_all * 4) : nullptr;
-    if (!cnt || !s.list[0] || !s.list[1] || !keys || !s.arena || !bits || !tile_d || !tile_e || (words_all && !s.words))
+    s.ovf = s.ovf_cap ? (int32_t *)grow_scratch(c, B_DUAL5, (size_t)blocks * s.ovf_cap * 4) : nullptr;
+    if (!cnt || !s.list[0] || !s.list[1] || !keys || !s.arena || !bits || !tile_d || !tile_e || (s.ovf_cap && !s.ovf))
         return set_err(c, PMS_ERR_OOM, "scratch allocation failed");
     VrTotals *tot = (VrTotals *)cnt;
     dual_counters(s, cnt + sizeof(VrTotals) / 4);
@@ -574,7 +602,6 @@ pms_status reduce_vr(Ctx *c, const Filtration *f, pms_result *res, int32_t count
     const double dm = (double)m;
     PMS_LAUNCH(c, K_FILL, 4 * dm + dm / 8, k_vr_fill, grid_for(m, kBlock * 4, 8192), kBlock, res->low_star, m, bits, nwords,
                tile_e, tiles, tot);
-    if (words_all) PMS_HIP(hipMemsetAsync(s.words, 0, (size_t)words_all * 4, st));
     PMS_LAUNCH(c, K_FILL, 0, k_dual_counters, 1, kBlock, s, 1, 0);
     PMS_LAUNCH(c, K_GRAPH, 24.0 * f->vr_edges, k_vr_h0, (unsigned)B, B >= 256 ? 256 : 1024, v, s, maxdim, face_col, tot);
     int32_t rounds = 0;
