@@ -96,7 +96,7 @@ struct Ctx {
     double prof_abytes[K_NUM] = {};
     int64_t prof_launches[K_NUM] = {};
     // named scratch buffers, grown on demand
-    Buf b[56];
+    Buf b[64];
     int32_t *arena = nullptr;
     uint64_t arena_cap = 0;  // entries
     void *host_pinned = nullptr;
@@ -124,10 +124,10 @@ enum BufId {
     B_BUILD0, B_BUILD1, B_BUILD2, B_BUILD3, B_BUILD4, B_BUILD5, B_BUILD6, B_BUILD7,
     B_BUILD8, B_BUILD9, B_BUILD10, B_BUILD11, B_BUILD12, B_BUILD13, B_BUILD14, B_STATS, B_PART, B_CQN, B_PREC, B_WQ, B_WQ2, B_ESS,
     B_DBG_LOW, B_DBG_OFF, B_DBG_LEN, B_DBG_STATE, B_DBG_W, B_DBG_EREM, B_C8, B_INST, B_BUDH, B_BUDN,
-    B_DUAL0, B_DUAL1, B_DUAL2, B_DUAL3, B_DUAL4, B_DUAL5,
+    B_DUAL0, B_DUAL1, B_DUAL2, B_DUAL3, B_DUAL4, B_DUAL5, B_SOLVE,
     B_NUM
 };
-static_assert(B_NUM <= 56, "Ctx::b holds 56 buffers");
+static_assert(B_NUM <= 64, "Ctx::b holds 64 buffers");
 
 // Grow-only scratch: returns the buffer, reallocating (contents dropped) when
 // it is smaller than `bytes`.

@@ -1529,9 +1529,12 @@ __device__ inline void wait_vmem()
 }
 
 // With solve_max > 0 and at most that many columns handed over, only those
-// k_chain_solve passes on (wq2); else the lane passes' hand-over queue (wq).
+// k_chain_solve passes on (wq2); else the lane passes' hand-over queue (wq),
+// at most busy_cap additions a column: the few that would go on have the next
+// round, where they are few enough for the sweeps (one of 1 000 columns of a
+// 128^3 field walked 1 848 additions, 2.0 ms, while the rest took 64 or less).
 template <bool kTrace>
-__global__ void __launch_bounds__(kChainWaves *kWave) k_chain(Dev d, int compression, int32_t solve_max)
+__global__ void __launch_bounds__(kChainWaves *kWave) k_chain(Dev d, int compression, int32_t solve_max, int32_t busy_cap)
 {
     __shared__ int32_t sW[kChainWaves][2][kCapW];
     __shared__ int32_t sS[kChainWaves][kCapS];
@@ -1548,8 +1551,10 @@ __global__ void __launch_bounds__(kChainWaves *kWave) k_chain(Dev d, int compres
     // trace: short, long, global, sum |W|, toggle / next / flush cycles, flushes, queued, lows from P, deletions
     unsigned long long tr[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     if (kTrace && gw == 0) tr[8] = (unsigned long long)total;
+    const int32_t cap_adds = fallback ? 0x7FFFFFFF : busy_cap;
     for (int32_t t = (int32_t)gw; t < total; t += (int32_t)nw) {
         const int32_t j = queue[t];
+        if (j < 0) continue;  // solved by the larger sweep kernel
         const int32_t L0 = d.len[j];
         by += 4 + 12 + 4 * (int64_t)L0;  // queue entry, header, column in
         const int32_t *g = col_base(d, d.off[j]);
@@ -1759,7 +1764,7 @@ __global__ void __launch_bounds__(kChainWaves *kWave) k_chain(Dev d, int compres
 
         refill();
         next();
-        while (i >= 0 && ls >= 0) {  // a low without a pivot ends the chain
+        while (i >= 0 && ls >= 0 && cadds < cap_adds) {  // a low without a pivot ends the chain
             const int32_t pi = i;
             const int32_t kk = lk - 1;
             cadds++;
@@ -1962,15 +1967,29 @@ __global__ void __launch_bounds__(kChainWaves *kWave) k_chain(Dev d, int compres
 // (compression deletes them), and a new row enters the list with its flags.
 // The result is written back sorted.  A column whose rows overfill the list
 // goes to k_chain.
-constexpr int kSolveThreads = 512;
-constexpr int kSolveH = 8192;            // hash slots (list positions, -1 = free)
-constexpr int kSolveMaxU = 6144;         // rows one column may touch (list length)
+//
+// Three sizes, each for what overfills the one before: 6 144 rows on 512
+// threads (two workgroups a CU); 12 288 rows on 1 024 threads (135 KB of LDS);
+// 49 152 rows with only the flags in LDS (a probe is then an access to L2: the
+// longest column of a 128^3 field takes 31 sweeps, 1.0 ms, where the serial
+// walk's 4 760 additions took 5).
 constexpr int kSolveDelta = 2048;        // membership changes applied per sweep
 constexpr int kSolveSweeps = 4096;       // a column still changing then goes to k_chain
 constexpr int kSolveLong = 64;           // long pivots a sweep spreads over the workgroup (more: per thread)
-constexpr int kSolvePer = kSolveMaxU / 4 / kSolveThreads;  // flag words (4 rows each) per thread
-static_assert(kSolveMaxU % (4 * kSolveThreads) == 0 && kSolveMaxU < kSolveH && (kSolveH & (kSolveH - 1)) == 0,
-              "k_chain_solve: whole flag words per thread; probes always end; the result sorts in the table");
+template <int kSize>
+struct SolveSize {
+    static constexpr int kThreads = kSize ? 1024 : 512;
+    static constexpr int kBits = kSize == 0 ? 13 : kSize == 1 ? 14 : 16;
+    static constexpr int kH = 1 << kBits;           // hash slots (list positions, -1 = free)
+    static constexpr int kMaxU = kH / 4 * 3;        // rows one column may touch (list length)
+    static constexpr int kPer = kMaxU / 4 / kThreads;  // flag words (4 rows each) per thread
+    static constexpr bool kMem = kSize == 2;        // hash table and list in memory
+    static constexpr int kLdsH = kMem ? 4 : kH, kLdsU = kMem ? 4 : kMaxU;
+    static_assert(kMaxU % (4 * kThreads) == 0,
+                  "k_chain_solve: whole flag words per thread; probes always end; the result sorts in the table");
+};
+constexpr unsigned kSolveMemBlocks = 64;  // workgroups of the size in memory, each with its table and list
+constexpr size_t kSolveMemBytes = (size_t)kSolveMemBlocks * (SolveSize<2>::kH + SolveSize<2>::kMaxU) * 4;
 // flags of a row
 constexpr uint32_t kSV = 1;   // v(r)
 constexpr uint32_t kSX = 2;   // r is in S
@@ -1985,9 +2004,10 @@ struct SolveLds {
     int32_t *fail;
 };
 
+template <class Z>
 __device__ inline uint32_t solve_hash(int32_t r)
 {
-    return ((uint32_t)r * 2654435761u) >> 19;  // 13 bits: kSolveH slots
+    return ((uint32_t)r * 2654435761u) >> (32 - Z::kBits);
 }
 
 // Toggles v(e), appending row e with flags fl when it is new.  A full list
@@ -1995,14 +2015,18 @@ __device__ inline uint32_t solve_hash(int32_t r)
 // entry is written before its position is published in the hash table, so a
 // thread that finds the position finds the row: LDS performs one wave's
 // operations in issue order, so only the compiler must keep them in order
-// (a fence would also wait for this thread's global loads in flight).
+// (a fence would also wait for this thread's global loads in flight); the
+// table in memory needs the fence, and probes that pass L1 by.
+template <class Z>
 __device__ inline void solve_toggle(const SolveLds &t, int32_t e, uint32_t fl)
 {
-    uint32_t h = solve_hash(e);
-    int32_t mine = -1;
+    uint32_t h = solve_hash<Z>(e);
+    int32_t mine = -1, x = -1;
     for (;;) {
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        const int32_t x = __hip_atomic_load(&t.hk[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (x < 0)
+            x = __hip_atomic_load(&t.hk[h], __ATOMIC_RELAXED,
+                                  Z::kMem ? __HIP_MEMORY_SCOPE_AGENT : __HIP_MEMORY_SCOPE_WORKGROUP);
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         if (x >= 0) {
             if (t.key[x] == e) {
@@ -2010,24 +2034,28 @@ __device__ inline void solve_toggle(const SolveLds &t, int32_t e, uint32_t fl)
                 atomicXor(&t.flag[x >> 2], kSV << (8 * (x & 3)));
                 return;
             }
-            h = (h + 1) & (kSolveH - 1);
+            h = (h + 1) & (Z::kH - 1);
+            x = -1;
             continue;
         }
         if (mine < 0) {
             mine = atomicAdd(t.n, 1);
-            if (mine >= kSolveMaxU) {
+            if (mine >= Z::kMaxU) {
                 atomicExch(t.fail, 1);
                 return;
             }
             t.key[mine] = e;
         }
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        const int32_t old = atomicCAS(&t.hk[h], -1, mine);
-        if (old == -1) {
+        if constexpr (Z::kMem)
+            __threadfence_block();
+        else
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        x = atomicCAS(&t.hk[h], -1, mine);
+        if (x == -1) {
             atomicXor(&t.flag[mine >> 2], (fl | kSV) << (8 * (mine & 3)));
             return;
         }
-        // the slot was taken meanwhile: look at it again
+        // the slot was taken meanwhile, by the row of entry x
     }
 }
 
@@ -2035,7 +2063,7 @@ __device__ inline void solve_toggle(const SolveLds &t, int32_t e, uint32_t fl)
 // known-negative bit (neg; both dense, so mostly cache hits) are loaded
 // together first (row 0 stands in for unused slots: the loads are
 // unconditional and the group waits once); known-negative rows are skipped.
-template <int kN>
+template <class Z, int kN>
 __device__ inline void solve_toggle_n(const Dev &d, const SolveLds &t, const int32_t (&rows)[kN], uint32_t use,
                                       int32_t j, int compression)
 {
@@ -2051,19 +2079,26 @@ __device__ inline void solve_toggle_n(const Dev &d, const SolveLds &t, const int
     for (int u = 0; u < kN; u++) {
         const bool negative = compression && ((nw[u] >> (rows[u] & 31)) & 1u);
         if (((use >> u) & 1u) && !negative)
-            solve_toggle(t, rows[u], pv[u] >= 0 ? (pv[u] < j ? kSP : (kSP | kSR)) : 0u);
+            solve_toggle<Z>(t, rows[u], pv[u] >= 0 ? (pv[u] < j ? kSP : (kSP | kSR)) : 0u);
     }
 }
 
 // The kernel takes the handed-over columns when there are at most solve_max
 // of them (a round of few, long chains, bound by its longest one); more
 // columns are walked by k_chain, whose waves hold more columns per CU.
-template <bool kTrace>
-__global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compression, int32_t solve_max)
+// kSize > 0: the columns the smaller sizes passed on (wq2), taken out of that
+// queue (-1) when solved.
+template <bool kTrace, int kSize>
+__global__ void __launch_bounds__(SolveSize<kSize>::kThreads) k_chain_solve(Dev d, int compression, int32_t solve_max,
+                                                                           int32_t *mem)
 {
-    __shared__ __align__(16) int32_t hk[kSolveH];        // hash table; then the result, sorted
-    __shared__ __align__(16) int32_t key[kSolveMaxU];    // the rows touched, in the order met (-1: dead)
-    __shared__ uint32_t flag[kSolveMaxU / 4];            // their flags, 4 per word
+    using Z = SolveSize<kSize>;
+    constexpr bool kBig = kSize > 0;
+    __shared__ __align__(16) int32_t s_hk[Z::kLdsH];     // hash table; then the result, sorted
+    __shared__ __align__(16) int32_t s_key[Z::kLdsU];    // the rows touched, in the order met (-1: dead)
+    int32_t *hk = Z::kMem ? mem + (size_t)blockIdx.x * (Z::kH + Z::kMaxU) : s_hk;
+    int32_t *key = Z::kMem ? hk + Z::kH : s_key;
+    __shared__ uint32_t flag[Z::kMaxU / 4];            // their flags, 4 per word
     __shared__ int32_t dl[kSolveDelta];                  // this sweep's changes of S: r (joins) or ~r (leaves)
     __shared__ int32_t s_n, s_fail, s_bad, s_L[2], s_nd[2];
     __shared__ long long s_o;
@@ -2072,8 +2107,8 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
     const SolveLds t{hk, key, flag, &s_n, &s_fail};
     const int4 *key4 = reinterpret_cast<const int4 *>(key);
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int32_t total = d.cq_n[kPart * 32];  // columns the lane passes handed over
-    if (total > solve_max) return;             // k_chain takes them all
+    if (d.cq_n[kPart * 32] > solve_max) return;  // k_chain takes all the lane passes handed over
+    const int32_t total = d.cq_n[(kBig ? kPart + 2 : kPart) * 32];
     int64_t adds = 0, pk = 0, by = 0, ab = 0, sweeps = 0;  // pk: entries read (column and added pivots)
     int32_t nsolved = 0, nfall = 0;
     // trace: set-up, pass A, pass B, toggles, out cycles; changes; long pivots, their entries;
@@ -2088,22 +2123,23 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
         }
     };
     auto hand_on = [&](int32_t j) {
-        if (tid == 0) d.wq2[atomicAdd(&d.cq_n[(kPart + 2) * 32], 1)] = j;
+        if (!kBig && tid == 0) d.wq2[atomicAdd(&d.cq_n[(kPart + 2) * 32], 1)] = j;
         nfall++;
     };
     for (int32_t q0 = (int32_t)blockIdx.x; q0 < total; q0 += (int32_t)gridDim.x) {
         __syncthreads();  // the previous column's last reads of LDS are done
-        const int32_t j = d.wq[q0];
+        const int32_t j = kBig ? d.wq2[q0] : d.wq[q0];
+        if (kBig && j < 0) continue;  // solved by the size before
         const int32_t L0 = d.len[j];
         const int32_t *g = col_base(d, d.off[j]);
-        if (L0 > kSolveMaxU / 2) {
+        if (L0 > Z::kMaxU / 2) {
             hand_on(j);
             continue;
         }
         if (kTrace) c0 = clock64();
         const long long w0 = kTrace ? wall_clock64() : 0;
-        for (int a = tid; a < kSolveH / 4; a += kSolveThreads) reinterpret_cast<int4 *>(hk)[a] = make_int4(-1, -1, -1, -1);
-        for (int a = tid; a < kSolveMaxU / 4; a += kSolveThreads) flag[a] = 0;
+        for (int a = tid; a < Z::kH / 4; a += Z::kThreads) reinterpret_cast<int4 *>(hk)[a] = make_int4(-1, -1, -1, -1);
+        for (int a = tid; a < Z::kMaxU / 4; a += Z::kThreads) flag[a] = 0;
         if (tid == 0) {
             s_n = 0;
             s_fail = 0;
@@ -2113,16 +2149,16 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
         }
         __syncthreads();
         // v = c
-        for (int32_t a0 = 0; a0 < L0; a0 += 4 * kSolveThreads) {
+        for (int32_t a0 = 0; a0 < L0; a0 += 4 * Z::kThreads) {
             int32_t rows[4];
             int32_t n = 0;
 #pragma unroll
             for (int u = 0; u < 4; u++) {
-                const int32_t a = a0 + u * kSolveThreads + tid;
+                const int32_t a = a0 + u * Z::kThreads + tid;
                 rows[u] = a < L0 ? g[a] : -1;
                 n += a < L0 ? 1 : 0;
             }
-            solve_toggle_n<4>(d, t, rows, (1u << n) - 1u, j, compression);
+            solve_toggle_n<Z, 4>(d, t, rows, (1u << n) - 1u, j, compression);
         }
         __syncthreads();
         tick(0);
@@ -2130,62 +2166,87 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
         int64_t cxe = 0;  // entries of the pivots in S (this thread's share)
         for (int it = 0;; it++) {
             const int p = it & 1;
-            const int32_t nwords = (min(s_n, kSolveMaxU) + 3) >> 2;
-            // this thread's rows, read once for both passes (nothing writes them in between)
-            uint32_t fw[kSolvePer];
-            int32_t kw[kSolvePer][4];
+            const int32_t nwords = (min(s_n, Z::kMaxU) + 3) >> 2;
+            // this thread's rows, read once for both passes (nothing writes them
+            // in between); from memory only those a pass needs
+            constexpr int kHeld = Z::kMem ? 1 : Z::kPer;
+            uint32_t fw[kHeld];
+            int32_t kw[kHeld][4];
+            int32_t lm = 0;  // L + 1 (0: no row with v = 1 lacks a pivot)
+            if constexpr (Z::kMem) {
+                for (int w = tid; w < nwords; w += Z::kThreads) {
+                    const uint32_t f = flag[w];
 #pragma unroll
-            for (int u = 0; u < kSolvePer; u++) {
-                const int w = u * kSolveThreads + tid;
-                fw[u] = 0;
-                kw[u][0] = kw[u][1] = kw[u][2] = kw[u][3] = -1;
-                if (w < nwords) {
-                    fw[u] = flag[w];
-                    const int4 k4 = key4[w];
-                    kw[u][0] = k4.x;
-                    kw[u][1] = k4.y;
-                    kw[u][2] = k4.z;
-                    kw[u][3] = k4.w;
+                    for (int b = 0; b < 4; b++)
+                        if (((f >> (8 * b)) & (kSV | kSP)) == kSV) lm = max(lm, key[4 * w + b] + 1);
                 }
+            } else {
+#pragma unroll
+                for (int u = 0; u < Z::kPer; u++) {
+                    const int w = u * Z::kThreads + tid;
+                    fw[u] = 0;
+                    kw[u][0] = kw[u][1] = kw[u][2] = kw[u][3] = -1;
+                    if (w < nwords) {
+                        fw[u] = flag[w];
+                        const int4 k4 = key4[w];
+                        kw[u][0] = k4.x;
+                        kw[u][1] = k4.y;
+                        kw[u][2] = k4.z;
+                        kw[u][3] = k4.w;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < Z::kPer; u++)
+#pragma unroll
+                    for (int b = 0; b < 4; b++)
+                        lm = ((fw[u] >> (8 * b)) & (kSV | kSP)) == kSV ? max(lm, kw[u][b] + 1) : lm;
             }
-            // L + 1 (0: no row with v = 1 lacks a pivot)
-            int32_t lm = 0;
-#pragma unroll
-            for (int u = 0; u < kSolvePer; u++)
-#pragma unroll
-                for (int b = 0; b < 4; b++)
-                    lm = ((fw[u] >> (8 * b)) & (kSV | kSP)) == kSV ? max(lm, kw[u][b] + 1) : lm;
             lm = wave_max_dpp(lm);
             if (lane == 0 && lm > 0) atomicMax(&s_L[p], lm);
             __syncthreads();
             tick(1);
             const int32_t Lp1 = s_L[p];
             // the membership test; at most kSolveDelta changes a sweep (the rest wait for the next)
-            uint32_t chg = 0;  // bit 4u + b: row b of word u changes
-#pragma unroll
-            for (int u = 0; u < kSolvePer; u++)
-#pragma unroll
-                for (int b = 0; b < 4; b++) {
-                    const uint32_t fb = fw[u] >> (8 * b);
-                    const bool want = (fb & (kSV | kSP)) == (kSV | kSP) && kw[u][b] >= Lp1;
-                    chg |= (uint32_t)(want != ((fb & kSX) != 0)) << (4 * u + b);
-                }
             if (tid == 0) s_nl = 0;
-            if (chg) {
-                int32_t q = atomicAdd(&s_nd[p], __popc(chg));
-                while (chg) {
-                    const int i = __builtin_ctz(chg);
-                    chg &= chg - 1;
-                    const int w = (i >> 2) * kSolveThreads + tid, b = i & 3;
-                    if (q < kSolveDelta) {
+            auto change = [&](int32_t q, int w, int b, int32_t r) {
+                if (q < kSolveDelta) {
+                    const bool has = ((flag[w] >> (8 * b)) & kSX) != 0;  // it leaves S, else joins
+                    dl[q] = has ? ~r : r;
+                    flag[w] ^= kSX << (8 * b);  // this thread's word: no other writer in this pass
+                } else if (kTrace) {
+                    tr[8]++;
+                }
+            };
+            if constexpr (Z::kMem) {
+                for (int w = tid; w < nwords; w += Z::kThreads) {
+                    const uint32_t f = flag[w];
+#pragma unroll
+                    for (int b = 0; b < 4; b++) {
+                        const uint32_t fb = (f >> (8 * b)) & (kSV | kSP | kSX);
+                        if (fb != (kSV | kSP) && !(fb & kSX)) continue;
                         const int32_t r = key[4 * w + b];
-                        const bool has = ((flag[w] >> (8 * b)) & kSX) != 0;  // it leaves S, else joins
-                        dl[q] = has ? ~r : r;
-                        flag[w] ^= kSX << (8 * b);  // this thread's word: no other writer in this pass
-                    } else if (kTrace) {
-                        tr[8]++;
+                        if (((fb & (kSV | kSP)) == (kSV | kSP) && r >= Lp1) != ((fb & kSX) != 0))
+                            change(atomicAdd(&s_nd[p], 1), w, b, r);
                     }
-                    q++;
+                }
+            } else {
+                uint32_t chg = 0;  // bit 4u + b: row b of word u changes
+#pragma unroll
+                for (int u = 0; u < Z::kPer; u++)
+#pragma unroll
+                    for (int b = 0; b < 4; b++) {
+                        const uint32_t fb = fw[u] >> (8 * b);
+                        const bool want = (fb & (kSV | kSP)) == (kSV | kSP) && kw[u][b] >= Lp1;
+                        chg |= (uint32_t)(want != ((fb & kSX) != 0)) << (4 * u + b);
+                    }
+                if (chg) {
+                    int32_t q = atomicAdd(&s_nd[p], __popc(chg));
+                    while (chg) {
+                        const int i = __builtin_ctz(chg);
+                        chg &= chg - 1;
+                        const int w = (i >> 2) * Z::kThreads + tid, b = i & 3;
+                        change(q++, w, b, key[4 * w + b]);
+                    }
                 }
             }
             __syncthreads();
@@ -2208,9 +2269,9 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
             // lanes of a row load its record together, then their entries' pivots
             // and known-negative bits, then toggle
             {
-                const int32_t G = nd <= kSolveThreads / 8 ? 8 : nd <= kSolveThreads / 4 ? 4
-                                : nd <= kSolveThreads / 2 ? 2 : 1;
-                const int32_t sub = tid & (G - 1), grp = tid / G, per = kSolveThreads / G;
+                const int32_t G = nd <= Z::kThreads / 8 ? 8 : nd <= Z::kThreads / 4 ? 4
+                                : nd <= Z::kThreads / 2 ? 2 : 1;
+                const int32_t sub = tid & (G - 1), grp = tid / G, per = Z::kThreads / G;
                 for (int32_t q0 = 0; q0 < nd; q0 += per) {
                     const int32_t q = q0 + grp;
                     const int32_t code = q < nd ? dl[q] : 0;
@@ -2230,7 +2291,7 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
                         ent[i] = x;
                         use |= (uint32_t)(inl && u < k - 1) << i;
                     }
-                    solve_toggle_n<kRecInline>(d, t, ent, use, j, compression);
+                    solve_toggle_n<Z, kRecInline>(d, t, ent, use, j, compression);
                     if (sub == 0 && sign) {
                         cxe += sign * k;
                         by += 32;
@@ -2255,7 +2316,7 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
                                         rows[u] = a0 + u < k - 1 ? pc[a0 + u] : -1;
                                         n += a0 + u < k - 1 ? 1 : 0;
                                     }
-                                    solve_toggle_n<4>(d, t, rows, (1u << n) - 1u, j, compression);
+                                    solve_toggle_n<Z, 4>(d, t, rows, (1u << n) - 1u, j, compression);
                                 }
                             }
                         }
@@ -2273,12 +2334,12 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
                 }
                 __syncthreads();
                 const int32_t tot = s_lpre[nl];
-                for (int32_t e0 = tid; e0 < tot; e0 += 4 * kSolveThreads) {
+                for (int32_t e0 = tid; e0 < tot; e0 += 4 * Z::kThreads) {
                     int32_t rows[4];
                     int32_t n = 0;
 #pragma unroll
                     for (int u = 0; u < 4; u++) {
-                        const int32_t ei = e0 + u * kSolveThreads;
+                        const int32_t ei = e0 + u * Z::kThreads;
                         const int32_t ec = min(ei, tot - 1);  // loaded unconditionally: one wait
                         int32_t lo = 0, hi = nl - 1;          // the pivot whose entries hold ec
                         while (lo < hi) {
@@ -2289,7 +2350,7 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
                         rows[u] = col_base(d, s_loff[lo])[ec - s_lpre[lo]];
                         n += ei < tot ? 1 : 0;
                     }
-                    solve_toggle_n<4>(d, t, rows, (1u << n) - 1u, j, compression);
+                    solve_toggle_n<Z, 4>(d, t, rows, (1u << n) - 1u, j, compression);
                 }
                 __syncthreads();
             }
@@ -2300,10 +2361,10 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
             continue;
         }
         // the result: the rows with v = 1 outside S, sorted
-        const int32_t nwords = (min(s_n, kSolveMaxU) + 3) >> 2;
+        const int32_t nwords = (min(s_n, Z::kMaxU) + 3) >> 2;
         int32_t nw = 0, ns = 0;
         bool bad = false;
-        for (int w = tid; w < nwords; w += kSolveThreads) {
+        for (int w = tid; w < nwords; w += Z::kThreads) {
             const uint32_t f = flag[w];
 #pragma unroll
             for (int b = 0; b < 4; b++) {
@@ -2315,8 +2376,8 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
         }
         if (bad) s_bad = 1;
         int32_t tot_w, tot_s;
-        int32_t o = block_excl_sum32<kSolveThreads>(nw, &tot_w);  // its barriers end every use of the hash table
-        block_excl_sum32<kSolveThreads>(ns, &tot_s);
+        int32_t o = block_excl_sum32<Z::kThreads>(nw, &tot_w);  // its barriers end every use of the hash table
+        block_excl_sum32<Z::kThreads>(ns, &tot_s);
         if (s_bad) {  // a pivot right of the column would be added: never expected
             if (tid == 0) {
                 d.cnt->bad_info[0] = j;
@@ -2328,8 +2389,9 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
             continue;
         }
         nsolved++;
+        if (kBig && tid == 0) d.wq2[q0] = -1;
         pk += cxe;
-        for (int w = tid; w < nwords; w += kSolveThreads) {
+        for (int w = tid; w < nwords; w += Z::kThreads) {
             const uint32_t f = flag[w];
             const int4 k4 = key4[w];
             const int32_t kk[4] = {k4.x, k4.y, k4.z, k4.w};
@@ -2338,13 +2400,13 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
                 if (((f >> (8 * b)) & (kSV | kSX)) == kSV) hk[o++] = kk[b];
         }
         int32_t n2 = 1;
-        while (n2 < tot_w) n2 <<= 1;  // <= kSolveMaxU rounded up <= kSolveH
-        for (int32_t a = tot_w + tid; a < n2; a += kSolveThreads) hk[a] = 0x7FFFFFFF;
+        while (n2 < tot_w) n2 <<= 1;  // <= Z::kMaxU rounded up <= Z::kH
+        for (int32_t a = tot_w + tid; a < n2; a += Z::kThreads) hk[a] = 0x7FFFFFFF;
         __syncthreads();
         // bitonic sort of hk[0, n2)
         for (int32_t kk = 2; kk <= n2; kk <<= 1)
             for (int32_t jj = kk >> 1; jj > 0; jj >>= 1) {
-                for (int32_t a = tid; a < n2; a += kSolveThreads) {
+                for (int32_t a = tid; a < n2; a += Z::kThreads) {
                     const int32_t b = a ^ jj;
                     if (b > a) {
                         const int32_t x = hk[a], y = hk[b];
@@ -2378,7 +2440,7 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
             if (tid == 0) atomicExch(&d.cnt->overflow, 1);
             continue;  // progress of this column is dropped; the stored column is still valid
         }
-        for (int32_t a = tid; a < tot_w; a += kSolveThreads) d.arena[oa + a] = hk[a];
+        for (int32_t a = tid; a < tot_w; a += Z::kThreads) d.arena[oa + a] = hk[a];
         tick(4);
         if (kTrace && tid == 0) atomicMax(&d.cnt->max_solve_us, (int32_t)((wall_clock64() - w0) / 100));  // 100 MHz
         if (tid == 0) {
@@ -2390,13 +2452,13 @@ __global__ void __launch_bounds__(kSolveThreads) k_chain_solve(Dev d, int compre
         }
     }
     // the additions' bytes as one multi-way sum: 4 (len c + the pivots' lengths + len out)
-    const int64_t b_adds = block_sum64<kSolveThreads>(adds), b_xe = block_sum64<kSolveThreads>(pk), b_by = block_sum64<kSolveThreads>(by);
-    const int64_t b_ab = block_sum64<kSolveThreads>(ab) + 4 * b_xe;
-    const int64_t b_sw = block_sum64<kSolveThreads>(sweeps) / kSolveThreads;
+    const int64_t b_adds = block_sum64<Z::kThreads>(adds), b_xe = block_sum64<Z::kThreads>(pk), b_by = block_sum64<Z::kThreads>(by);
+    const int64_t b_ab = block_sum64<Z::kThreads>(ab) + 4 * b_xe;
+    const int64_t b_sw = block_sum64<Z::kThreads>(sweeps) / Z::kThreads;
     if (kTrace) {  // per-thread counts (the cycle counts are thread 0's)
-        tr[6] = (unsigned long long)block_sum64<kSolveThreads>((int64_t)tr[6]);
-        tr[7] = (unsigned long long)block_sum64<kSolveThreads>((int64_t)tr[7]);
-        tr[8] = (unsigned long long)block_sum64<kSolveThreads>((int64_t)tr[8]);
+        tr[6] = (unsigned long long)block_sum64<Z::kThreads>((int64_t)tr[6]);
+        tr[7] = (unsigned long long)block_sum64<Z::kThreads>((int64_t)tr[7]);
+        tr[8] = (unsigned long long)block_sum64<Z::kThreads>((int64_t)tr[8]);
     }
     if (tid == 0) {
         stat_add(d, S_ADDS, (unsigned long long)b_adds, blockIdx.x);
@@ -3264,6 +3326,20 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     size_t xor_slot = 0, lane_slot = 0, wide_slot = 0, chain_slot = 0, solve_slot = 0, pivots_slot = 0;
     double pivots_base = 0;
     const pms_tuning tn = c->tune;
+    // Columns that overfill the sweep kernel's list come with large matrices:
+    // of three 64^3 fields (m = 1.5 M) with their graph blocks apart no column
+    // does, and the two empty launches a round cost 3% there (5.28 against
+    // 5.12 ms); of a 128^3 field (12.4 M) two or three a round do.
+    int32_t *solve_mem = nullptr;
+    if (m > (1 << 22) && tn.solve > 0 && !S.base) {
+        solve_mem = (int32_t *)S.get(B_SOLVE, kSolveMemBytes);
+        if (!solve_mem) return set_err(c, PMS_ERR_OOM, "scratch allocation failed");
+    }
+    // With blocks apart a round hands on fewer columns, and longer chains:
+    // sweeps up to twice the built-in number, and beyond it walks of 64 at most.
+    // At 128^3 with the larger sizes 25.1 ms, 39.3 before (k_chain 23 ms of the
+    // kernels' 48, one column of 4 760 additions at 1 us each): k_chain none left.
+    const int32_t solve_max = blocks ? 2 * tn.solve : tn.solve, busy_cap = blocks ? 64 : 0x7FFFFFFF;
     auto launch_round = [&](const int32_t *a, int32_t *an, int64_t grid_tiles, double dA) -> pms_status {
         const unsigned gT = (unsigned)(grid_tiles > 0 ? grid_tiles : 1);
         // the chaining kernels take queued columns (at most the active ones)
@@ -3326,20 +3402,35 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
             PMS_LAUNCH(c, K_CHAIN_WIDE, -1.0, k_chain_wide<false>, g_wide, kWideThreads, d, opt->compression, tn);
         wide_slot = c->pend.size() - 1;
         if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
-        if (tn.solve > 0) {  // few handed-over columns: by sweeps; what does not fit, serially
+        if (solve_max > 0) {  // few handed-over columns: by sweeps; what does not fit, serially
             if (trace)
-                PMS_LAUNCH(c, K_SOLVE, -1.0, k_chain_solve<true>, g_solve, kSolveThreads, d, opt->compression,
-                           tn.solve);
+                PMS_LAUNCH(c, K_SOLVE, -1.0, (k_chain_solve<true, 0>), g_solve, SolveSize<0>::kThreads, d,
+                           opt->compression, solve_max, nullptr);
             else
-                PMS_LAUNCH(c, K_SOLVE, -1.0, k_chain_solve<false>, g_solve, kSolveThreads, d, opt->compression,
-                           tn.solve);
+                PMS_LAUNCH(c, K_SOLVE, -1.0, (k_chain_solve<false, 0>), g_solve, SolveSize<0>::kThreads, d,
+                           opt->compression, solve_max, nullptr);
             solve_slot = c->pend.size() - 1;
+            if (solve_mem) {
+                const unsigned g1 = std::min(g_solve, 64u), g2 = std::min(g_solve, kSolveMemBlocks);
+                if (trace) {
+                    PMS_LAUNCH(c, K_SOLVE, 0, (k_chain_solve<true, 1>), g1, SolveSize<1>::kThreads, d,
+                               opt->compression, solve_max, nullptr);
+                    PMS_LAUNCH(c, K_SOLVE, 0, (k_chain_solve<true, 2>), g2, SolveSize<2>::kThreads, d,
+                               opt->compression, solve_max, solve_mem);
+                } else {
+                    PMS_LAUNCH(c, K_SOLVE, 0, (k_chain_solve<false, 1>), g1, SolveSize<1>::kThreads, d,
+                               opt->compression, solve_max, nullptr);
+                    PMS_LAUNCH(c, K_SOLVE, 0, (k_chain_solve<false, 2>), g2, SolveSize<2>::kThreads, d,
+                               opt->compression, solve_max, solve_mem);
+                }
+            }
             if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
         }
         if (trace)
-            PMS_LAUNCH(c, K_CHAIN, -1.0, k_chain<true>, g_chain, kChainWaves * kWave, d, opt->compression, tn.solve);
+            PMS_LAUNCH(c, K_CHAIN, -1.0, k_chain<true>, g_chain, kChainWaves * kWave, d, opt->compression, solve_max, busy_cap);
         else
-            PMS_LAUNCH(c, K_CHAIN, -1.0, k_chain<false>, g_chain, kChainWaves * kWave, d, opt->compression, tn.solve);
+            PMS_LAUNCH(c, K_CHAIN, -1.0, k_chain<false>, g_chain, kChainWaves * kWave, d, opt->compression, solve_max,
+                       busy_cap);
         chain_slot = c->pend.size() - 1;
         if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
         PMS_LAUNCH(c, K_COMPACT, 5 * dA, k_keep_count, gT, kBlock, d, a, keep, -1);
