@@ -831,24 +831,132 @@ __global__ void __launch_bounds__(kBlock) k_bud_apply(Dev d, const int32_t *act,
     }
 }
 
+// The same symmetric difference by the whole workgroup: pieces of
+// kXorPiece merged entries, both lists' next kXorPiece entries staged in LDS
+// (with one entry before and after: an equal pair may straddle two pieces or
+// two threads), thread t merging the kXorSeg entries from its diagonal on
+// (found by bisection in LDS).  An entry is dropped when the one before or
+// after it is equal, or its row is known negative.  Returns the length;
+// *last gets the largest row (-1: none).  Every thread calls it.
+constexpr int kXorSeg = 8, kXorPiece = kXorSeg * kBlock;
+
+__device__ inline int32_t block_merge_add(const int32_t *__restrict__ x, int32_t nx, const int32_t *__restrict__ y,
+                                          int32_t ny, int32_t *__restrict__ out, const uint32_t *neg, int compression,
+                                          int32_t (&sx)[kXorPiece + 2], int32_t (&sy)[kXorPiece + 2], int32_t *last)
+{
+    constexpr int32_t kEnd = 0x7FFFFFFF;
+    __shared__ int32_t s_cut, s_last;
+    int32_t a0 = 0, b0 = 0, k = 0;
+    if (threadIdx.x == 0) s_last = -1;
+    while (a0 < nx || b0 < ny) {
+        // sx[1 + i] = x[a0 + i]; before the first entry -1, past the last kEnd
+        for (int i = threadIdx.x; i < kXorPiece + 2; i += kBlock) {
+            const int32_t a = a0 + i - 1, b = b0 + i - 1;
+            sx[i] = a < 0 ? -1 : a < nx ? x[a] : kEnd;
+            sy[i] = b < 0 ? -1 : b < ny ? y[b] : kEnd;
+        }
+        __syncthreads();
+        // this thread's diagonal: how many of the piece's first `diag` entries come from x
+        const int32_t diag = min((int32_t)threadIdx.x * kXorSeg, nx - a0 + ny - b0);
+        int32_t lo = max(0, diag - (ny - b0)), hi = min(diag, nx - a0);
+        while (lo < hi) {
+            const int32_t mid = (lo + hi) >> 1;
+            if (sx[1 + mid] <= sy[diag - mid]) lo = mid + 1;  // x first among equals
+            else hi = mid;
+        }
+        int32_t i = lo, j = diag - lo;
+        int32_t prev = max(sx[i], sy[j]);
+        int32_t u = sx[1 + i], v = sy[1 + j];
+        int32_t e[kXorSeg];
+        uint32_t keep = 0;
+#pragma unroll
+        for (int t = 0; t < kXorSeg; t++) {
+            const bool fx = u <= v;
+            const int32_t w = fx ? u : v;
+            e[t] = w;
+            if (fx) {
+                i += u != kEnd ? 1 : 0;
+                u = u != kEnd ? sx[1 + i] : kEnd;
+            } else {
+                j++;
+                v = sy[1 + j];
+            }
+            keep |= (uint32_t)(w != kEnd && w != prev && w != min(u, v)) << t;
+            prev = w;
+        }
+        uint32_t nw[kXorSeg];
+#pragma unroll
+        for (int t = 0; t < kXorSeg; t++) nw[t] = neg[(e[t] != kEnd ? e[t] : 0) >> 5];
+        if (compression) {
+#pragma unroll
+            for (int t = 0; t < kXorSeg; t++) keep &= ~(((nw[t] >> (e[t] & 31)) & 1u) << t);
+        }
+        if (threadIdx.x == kBlock - 1) s_cut = i;
+        int32_t tot;
+        int32_t o = k + block_excl_sum32(__popc(keep), &tot);
+#pragma unroll
+        for (int t = 0; t < kXorSeg; t++)
+            if ((keep >> t) & 1u) out[o++] = e[t];
+        if (tot > 0 && keep && o == k + tot) {  // the piece's last kept entry
+            int32_t w = 0;
+#pragma unroll
+            for (int t = 0; t < kXorSeg; t++) w = (keep >> t) & 1u ? e[t] : w;
+            s_last = w;
+        }
+        k += tot;
+        const int32_t left = nx - a0 + ny - b0, cut = s_cut;  // read after block_excl_sum32's barriers
+        if (left <= kXorPiece) break;
+        a0 += cut;
+        b0 += kXorPiece - cut;
+        __syncthreads();  // the piece's reads of sx, sy and s_cut are done
+    }
+    __syncthreads();
+    *last = s_last;
+    __syncthreads();
+    return k;
+}
+
 // Phase II, first addition of every colliding column (one lane per
 // column: most columns are a few entries long).  A column that may keep
 // adding known pivots (chaining) and whose new low has one is queued for
-// k_chain.
+// k_chain.  A tile's long merges, when they are few, are made by the
+// whole workgroup (block_merge_add): a lane takes about 0.13 us an entry, the
+// workgroup about 5 us a merge of 2 000, so they are taken from the shortest
+// of three lengths at which one lane would take longer than all of them do
+// together.  With fewer columns than the grid's threads a tile is a part of
+// the 256 (a power of two, at least 4), so that the long merges of a tail
+// round of a few hundred columns spread over the chip.  By lanes only, tail
+// rounds of 20 to 400 columns of a 128^3 field took 130 to 490 us, now 16 to
+// 56 (all rounds: 3.4 ms, now 0.71); of a 32^3 field of noise 30 to 89 us, now
+// 12 to 34.  The first round is bound by its column and record reads (12.4 M
+// columns of a 128^3 field: 0.42 ms).
 constexpr int32_t kXorDefer = 128;  // merges longer than this go to the chain kernels in tail rounds
+constexpr int kXorJobs = 16;        // long merges of a tile the workgroup makes, at most
+constexpr unsigned kXorBlocks = 256;
+
+struct XorJob {
+    int64_t toff, soff, dst;
+    int32_t tlen, slen, k, last;
+};
 
 __global__ void __launch_bounds__(kBlock) k_xor(Dev d, const int32_t *act, int variant, int compression, int chain,
                                                 int tail)
 {
+    __shared__ int32_t s_x[kXorPiece + 2], s_y[kXorPiece + 2];
+    __shared__ XorJob s_job[kXorJobs];
+    __shared__ int32_t s_nl[4];  // merges longer than 64, 512, 4 096; the longest
     const int32_t nA = d.cnt->n_cur;
     const uint32_t round = d.cnt->round;
-    const int64_t tiles = ((int64_t)nA + kBlock - 1) / kBlock;
+    int32_t cols = kBlock;
+    while (cols > 4 && (int64_t)(cols >> 1) * gridDim.x >= nA) cols >>= 1;
+    const int64_t tiles = ((int64_t)nA + cols - 1) / cols;
     // strided: per-tile work varies widely (long merges cluster), so fixed parts would leave a tail
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const int64_t q = tile * kBlock + threadIdx.x;
+    const int64_t q = threadIdx.x < (unsigned)cols ? tile * cols + threadIdx.x : nA;
     int32_t j = -1, s = -1, tlen = 0, slen = 0;
     int64_t toff = 0, soff = 0;
     bool target = false, push = false;
+    if (threadIdx.x < 4) s_nl[threadIdx.x] = 0;
     if (q < nA) {
         j = act[q];
         if (d.state[j] == ST_ACTIVE && d.coll[q] == 1) {
@@ -881,11 +989,51 @@ __global__ void __launch_bounds__(kBlock) k_xor(Dev d, const int32_t *act, int v
     const int64_t bbase = s_base;
     if (threadIdx.x == 0 && bbase < 0) atomicExch(&d.cnt->overflow, 1);  // once per block: one flag for all
     if (target && bbase < 0) target = false;  // the column stays as it is this round
+    // the long ones: a workgroup's merge each, if few
+    const int32_t tot_len = target ? tlen + slen : 0;
+    if (tot_len > 64) {
+        atomicAdd(&s_nl[0], 1);
+        if (tot_len > 512) atomicAdd(&s_nl[1], 1);
+        if (tot_len > 4096) atomicAdd(&s_nl[2], 1);
+        atomicMax(&s_nl[3], tot_len);
+    }
+    __syncthreads();
+    int32_t from = 0x7FFFFFFF;  // merges longer than this: the workgroup's
+#pragma unroll
+    for (int l = 2; l >= 0; l--)
+        if (s_nl[l] <= kXorJobs && s_nl[l] * 32 <= s_nl[3]) from = 64 << (3 * l);
+    const bool coop = tot_len > from;
+    __syncthreads();
+    if (threadIdx.x == 0) s_nl[0] = 0;
+    __syncthreads();
+    int32_t job = -1, k = 0, nl = -1;
+    const int64_t dst = target ? bbase + excl : 0;
+    if (coop) {
+        job = atomicAdd(&s_nl[0], 1);
+        s_job[job] = XorJob{toff, soff, dst, tlen, slen, 0, -1};
+    } else if (target) {
+        k = merge_add_stream(col_base(d, toff), tlen, col_base(d, soff), slen, d.arena + dst, d.neg, compression);
+        if (k > 0) nl = d.arena[dst + k - 1];
+    }
+    __syncthreads();
+    const int32_t njobs = s_nl[0];
+    for (int32_t w = 0; w < njobs; w++) {
+        const XorJob J = s_job[w];
+        int32_t last;
+        const int32_t kj = block_merge_add(col_base(d, J.toff), J.tlen, col_base(d, J.soff), J.slen, d.arena + J.dst,
+                                           d.neg, compression, s_x, s_y, &last);
+        if (threadIdx.x == 0) {
+            s_job[w].k = kj;
+            s_job[w].last = last;
+        }
+    }
+    __syncthreads();
+    if (coop) {
+        k = s_job[job].k;
+        nl = s_job[job].last;
+    }
     int64_t adds = 0, xe = 0, by = q < nA ? 6 : 0, ab = 0;  // act, state, coll
     if (target) {
-        const int64_t dst = bbase + excl;
-        int32_t *out = d.arena + dst;
-        const int32_t k = merge_add_stream(col_base(d, toff), tlen, col_base(d, soff), slen, out, d.neg, compression);
         adds = 1;
         xe = (int64_t)tlen + slen;
         by += 42 + 4 * ((int64_t)tlen + slen + k) + 16;  // headers, low, piv/T, beta, dim; data in and out
@@ -897,7 +1045,6 @@ __global__ void __launch_bounds__(kBlock) k_xor(Dev d, const int32_t *act, int v
             d.low[j] = -1;
             d.state[j] = ST_ZERO;  // column j is positive
         } else {
-            const int32_t nl = out[k - 1];
             d.low[j] = nl;
             const bool chainable = chain && (d.beta[j] >= 0 || (d.dim && d.dim[j] == d.cnt->topdim) || nA < tail);
             push = chainable && d.piv[nl] >= 0;
@@ -907,7 +1054,7 @@ __global__ void __launch_bounds__(kBlock) k_xor(Dev d, const int32_t *act, int v
     __shared__ int32_t s_q;
     int32_t npush;
     const int32_t qpos = block_excl_sum32(push ? 1 : 0, &npush);
-    const unsigned qp = (unsigned)tile & (kPart - 1);
+    const unsigned qp = (unsigned)((tile * cols) / kBlock) & (kPart - 1);  // its slice takes whole tiles of kBlock
     if (threadIdx.x == 0) s_q = npush ? atomicAdd(&d.cq_n[qp * 32], npush) : 0;
     __syncthreads();
     if (push) d.cq[(int64_t)qp * d.cq_slice + s_q + qpos] = j;
@@ -3386,7 +3533,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
             PMS_LAUNCH(c, K_BUDGET, 0, k_bud_apply, gT, kBlock, d, a, va, pr, bud_n, bud_h, keep2);
             if (pr == 1) PMS_LAUNCH(c, K_BUDGET, 0, k_bud_ncount, gA, kBlock, d, a, va, bud_n, -1);
         }
-        PMS_LAUNCH(c, K_XOR, -1.0, k_xor, gT, kBlock, d, a, opt->variant, opt->compression, opt->chain,
+        PMS_LAUNCH(c, K_XOR, -1.0, k_xor, std::max(gT, kXorBlocks), kBlock, d, a, opt->variant, opt->compression, opt->chain,
                    opt->tail_active);
         xor_slot = c->pend.size() - 1;
         if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
