@@ -420,9 +420,11 @@ __device__ inline T block_seg_scan(T *a, int64_t n, T ident, Op op)
 }
 
 // Block-wide exclusive max-scan of I4 (identity -1); *total = block max.
+template <int kThreads = kBlock>
 __device__ inline I4 block_excl_max4(I4 v, I4 *total)
 {
-    __shared__ I4 s_w4[kWavesPerBlock];
+    constexpr int kW = kThreads / kWave;
+    __shared__ I4 s_w4[kW];
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     I4 inc = wave_incl_max4(v);
     // exclusive within the wave: shift by one lane
@@ -436,7 +438,7 @@ __device__ inline I4 block_excl_max4(I4 v, I4 *total)
     __syncthreads();
     I4 pre = i4_fill(-1), tot = i4_fill(-1);
 #pragma unroll
-    for (int w = 0; w < kWavesPerBlock; w++) {
+    for (int w = 0; w < kW; w++) {
         I4 t = s_w4[w];
         if (w < wid) pre = i4_max(pre, t);
         tot = i4_max(tot, t);

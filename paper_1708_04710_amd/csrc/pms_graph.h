@@ -374,12 +374,15 @@ __global__ void __launch_bounds__(kBlock) k_mix_compact(Dev d, const int32_t *ke
 
 // The reduction starts from that list; below solved top dimensions, the first
 // unsolved one holds the columns nothing clears any more.
-__global__ void k_mix_start(Dev d, int32_t top, int do_top, int32_t dual)
+__global__ void __launch_bounds__(kWave) k_mix_start(Dev d, int32_t top, int do_top, int32_t dual, Counters *host)
 {
     const int32_t solved = mix_solved(d, top, do_top, dual);
     int32_t t = top;
     while (t > 0 && ((solved >> t) & 1)) t--;
-    d.cnt->n_cur = d.cnt->n_next;
-    d.cnt->beta_counted = 1;
-    d.cnt->topdim = t;
+    if (threadIdx.x == 0) {
+        d.cnt->n_cur = d.cnt->n_next;
+        d.cnt->beta_counted = 1;
+        d.cnt->topdim = t;
+    }
+    publish(d, host);
 }

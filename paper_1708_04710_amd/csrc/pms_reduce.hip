@@ -501,6 +501,31 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_sum2(int32_t *a, int32_t 
     if (threadIdx.x == 0) *(blockIdx.x ? tb : ta) = tot;
 }
 
+// Column j becomes the pivot of row i; the bytes that takes.
+__device__ inline int64_t make_pivot(const Dev &d, int32_t j, int32_t i, int compression)
+{
+    d.piv[i] = j;
+    PivRec r;
+    r.s = j;
+    r.k = d.len[j];
+    int64_t pb = 4 + 32 + 8 + 4 + 1 + 4 + 2;
+    if (r.k - 1 <= kRecInline) {
+        const int32_t *c = col_base(d, d.off[j]);
+        for (int t = 0; t < r.k - 1; t++) r.e[t] = c[t];
+        pb += 4 * (int64_t)(r.k - 1);
+    }
+    d.prec[i] = r;
+    d.state[j] = ST_PIVOT;
+    dbg_write(d, j);
+    d.low_star[j] = i;
+    if (compression) d.prec[j].k = -1;
+    if (d.state[i] == ST_ACTIVE) {
+        d.state[i] = ST_CLEARED;  // clearing: sigma_i is positive
+        dbg_write(d, i);
+    }
+    return pb;
+}
+
 // Phase I + the beta test + clearing.
 __global__ void __launch_bounds__(kBlock) k_pivots(Dev d, const int32_t *act, const I4 *agg, int compression)
 {
@@ -534,25 +559,7 @@ __global__ void __launch_bounds__(kBlock) k_pivots(Dev d, const int32_t *act, co
         const bool by_beta = d.beta[j] == i;                  // beta_j = low(j): Thm. P.5
         const bool by_li = i > mc.v[slot_of(d, j)];           // low(j) > maxCollision
         if (by_beta || by_li) {
-            d.piv[i] = j;
-            PivRec r;
-            r.s = j;
-            r.k = d.len[j];
-            pb = 4 + 32 + 8 + 4 + 1 + 4 + 2;
-            if (r.k - 1 <= kRecInline) {
-                const int32_t *c = col_base(d, d.off[j]);
-                for (int t = 0; t < r.k - 1; t++) r.e[t] = c[t];
-                pb += 4 * (int64_t)(r.k - 1);
-            }
-            d.prec[i] = r;
-            d.state[j] = ST_PIVOT;
-            dbg_write(d, j);
-            d.low_star[j] = i;
-            if (compression) d.prec[j].k = -1;
-            if (d.state[i] == ST_ACTIVE) {
-                d.state[i] = ST_CLEARED;  // clearing: sigma_i is positive
-                dbg_write(d, i);
-            }
+            pb = make_pivot(d, j, i, compression);
             np = 1;
             nb = by_beta ? 1 : 0;
         }
@@ -571,6 +578,103 @@ __global__ void __launch_bounds__(kBlock) k_pivots(Dev d, const int32_t *act, co
         stat_add(d, S_PBYTES, (unsigned long long)bpb, (unsigned)tile);
     }
     __syncthreads();
+    }
+}
+
+// k_low, k_collide, the scan and k_pivots of a round of at most kOpenMax
+// columns, in one workgroup.  Such a round is bound by its launches: the four
+// kernels take 24 to 32 us however few columns there are (a launch and a
+// chain of loads each), one workgroup 12 us for some hundred columns and 20
+// for 1 500, but 33 for 3 000 and 60 for 4 000 (32^3 noise).  Each step is done for
+// all columns before the next, behind a barrier, as between launches; what
+// other threads' atomics wrote is read past L1.
+constexpr int kOpenThreads = 1024, kOpenPer = 2, kClosePer = 4;
+constexpr int32_t kOpenMax = kOpenThreads * kOpenPer, kCloseMax = kOpenThreads * kClosePer;
+
+__global__ void __launch_bounds__(kOpenThreads) k_round_open(Dev d, const int32_t *act, int compression)
+{
+    const int32_t nA = d.cnt->n_cur;
+    const uint32_t round = d.cnt->round;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int count_beta = round == 0 && !d.cnt->beta_counted;
+    if (threadIdx.x <= kPart + 2) d.cq_n[threadIdx.x * 32] = 0;
+    if (threadIdx.x == 0) d.cnt->max_chain = d.cnt->max_sweeps = d.cnt->max_solve_us = 0;
+    int32_t jj[kOpenPer], ii[kOpenPer];  // column (-1: none), low (-1: none)
+#pragma unroll
+    for (int u = 0; u < kOpenPer; u++) {  // k_low
+        const int32_t q = u * kOpenThreads + (int32_t)threadIdx.x;
+        int32_t j = -1, i = -1 - lane, pv = 0;
+        if (q < nA) {
+            j = act[q];
+            int32_t n = d.len[j];
+            const int32_t *c = col_base(d, d.off[j]);
+            while (n > 0 && is_neg(d.neg, c[n - 1])) n--;
+            d.len[j] = n;
+            if (n == 0) {
+                d.low[j] = -1;
+                d.state[j] = ST_ZERO;
+            } else {
+                i = c[n - 1];
+                d.low[j] = i;
+                pv = d.piv[i];
+            }
+        }
+        const int32_t prev_i = __shfl_up(i, 1, kWave);
+        if (i >= 0 && !(lane > 0 && prev_i == i) && pv < 0) atomicMin(&d.T[i], t_key(round, j));
+        jj[u] = j;
+        ii[u] = i;
+    }
+    __threadfence();
+    __syncthreads();
+    I4 carry = i4_fill(-1), mc[kOpenPer];
+    uint32_t live = 0, hit = 0;
+#pragma unroll
+    for (int u = 0; u < kOpenPer; u++) {  // k_collide and the scan
+        if (u * kOpenThreads >= nA) {
+            mc[u] = carry;
+            continue;
+        }
+        I4 e = i4_fill(-1);
+        const int32_t q = u * kOpenThreads + (int32_t)threadIdx.x;
+        if (q < nA) {
+            int8_t cl = kNotLive;
+            if (ii[u] >= 0 && d.state[jj[u]] == ST_ACTIVE) {
+                live |= 1u << u;
+                const unsigned long long T =
+                    __hip_atomic_load(&d.T[ii[u]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                cl = (d.piv[ii[u]] >= 0 || t_decode(T, round) != jj[u]) ? 1 : 0;
+                hit |= (uint32_t)cl << u;
+                if (cl) e.v[slot_of(d, jj[u])] = ii[u];
+            }
+            d.coll[q] = cl;
+        }
+        I4 tot;
+        mc[u] = i4_max(carry, block_excl_max4<kOpenThreads>(e, &tot));
+        carry = i4_max(carry, tot);
+    }
+    __syncthreads();
+    int32_t np = 0, nb = 0;
+    int64_t pb = 0;
+#pragma unroll
+    for (int u = 0; u < kOpenPer; u++) {  // k_pivots
+        if (u * kOpenThreads >= nA) continue;
+        bool made = false;
+        if ((live >> u) & ~(hit >> u) & 1u) {
+            const int32_t j = jj[u], i = ii[u];
+            const bool by_beta = d.beta[j] == i;
+            if (by_beta || i > mc[u].v[slot_of(d, j)]) {
+                pb += make_pivot(d, j, i, compression);
+                made = true;
+                np++;
+                nb += by_beta ? 1 : 0;
+            }
+        }
+        if (compression) mark_neg(d.neg, jj[u], made);
+    }
+    if (np) {
+        stat_add(d, S_NEWPIV, (unsigned long long)np, threadIdx.x);
+        stat_add(d, S_PBYTES, (unsigned long long)pb, threadIdx.x);
+        if (count_beta) stat_add(d, S_BETAPIV, (unsigned long long)nb, threadIdx.x);
     }
 }
 
@@ -2937,7 +3041,7 @@ __global__ void k_one_instance(int64_t *off, int64_t m)
 // End of a round: the compacted list is the next round's; a round that did
 // work advances the round number (the T table's stamp).
 // One wavefront: lane p reads partition p's fill.
-__global__ void __launch_bounds__(kWave) k_round_end(Dev d)
+__device__ inline void round_end(const Dev &d, int32_t n_next)
 {
     static_assert(kPart == kWave, "one lane per arena partition");
     const int p = threadIdx.x;
@@ -2950,9 +3054,61 @@ __global__ void __launch_bounds__(kWave) k_round_end(Dev d)
     if (p == 0) {
         d.cnt->active_sum += (unsigned long long)d.cnt->n_cur;
         if (d.cnt->n_cur > 0) d.cnt->round = d.cnt->round + 1;
-        d.cnt->n_cur = d.cnt->n_next;
+        d.cnt->n_cur = n_next;
         d.cnt->arena_free = fr;
     }
+}
+
+// The counters to the host's pinned buffer (null: not wanted), by the last
+// kernel before the host looks at them: a copy of their 0.6 KB is a launch of
+// 4 us of its own.  Every thread of the workgroup that wrote them last.
+__device__ inline void publish(const Dev &d, Counters *host)
+{
+    __syncthreads();
+    if (!host) return;
+    const unsigned long long *src = reinterpret_cast<const unsigned long long *>(d.cnt);
+    unsigned long long *dst = reinterpret_cast<unsigned long long *>(host);
+    for (int w = threadIdx.x; w < (int)(sizeof(Counters) / 8); w += blockDim.x) dst[w] = src[w];
+}
+
+__global__ void __launch_bounds__(kWave) k_round_end(Dev d, Counters *host)
+{
+    round_end(d, d.cnt->n_next);
+    publish(d, host);
+}
+
+// k_keep_count, the scan, k_compact and k_round_end of a round of at most
+// kCloseMax columns, in one workgroup: 5 us where the four launches take 18.
+__global__ void __launch_bounds__(kOpenThreads) k_round_close(Dev d, const int32_t *act, int32_t *act_next,
+                                                              Counters *host)
+{
+    const int32_t nA = d.cnt->n_cur;
+    int32_t base = 0;
+#pragma unroll
+    for (int u = 0; u < kClosePer; u++) {
+        if (u * kOpenThreads >= nA) continue;
+        const int32_t q = u * kOpenThreads + (int32_t)threadIdx.x;
+        int32_t j = -1;
+        bool keep = false;
+        if (q < nA) {
+            j = act[q];
+            const uint8_t st = d.state[j];
+            if (st == ST_CLEARED) {
+                d.state[j] = ST_ZERO;
+                d.len[j] = 0;
+                d.low[j] = -1;
+            }
+            keep = st == ST_ACTIVE;
+        }
+        int32_t tot;
+        const int32_t pos = base + block_excl_sum32<kOpenThreads>(keep ? 1 : 0, &tot);
+        if (keep) act_next[pos] = j;
+        base += tot;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) d.cnt->n_next = base;
+    if (threadIdx.x < kWave) round_end(d, base);
+    publish(d, host);
 }
 
 // Arena regrowth: copy every live arena column into a new arena.
@@ -3002,8 +3158,10 @@ __global__ void __launch_bounds__(kBlock) k_fin_count(Dev d, int32_t *cnt_pairs,
 }
 
 __global__ void __launch_bounds__(kBlock) k_fin_scatter(Dev d, const int32_t *off_pairs, const int32_t *off_ess,
-                                                        int32_t *birth, int32_t *death, int32_t *ess)
+                                                        int32_t *birth, int32_t *death, int64_t cap_pairs, int32_t *ess,
+                                                        int64_t cap_ess)
 {
+    if ((birth && d.cnt->n_pairs > cap_pairs) || (ess && d.cnt->n_ess > cap_ess)) return;  // the host refuses
     const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     int dp = 0, de = 0;
     int32_t ls = -1;
@@ -3059,7 +3217,7 @@ __global__ void k_part_init(Dev d)
 }
 
 // Fold the striped counters into the call's Counters.
-__global__ void k_stats_fold(Dev d)
+__global__ void k_stats_fold(Dev d, Counters *host)
 {
     __shared__ unsigned long long s_sum[S_NUM];
     if (threadIdx.x < S_NUM) s_sum[threadIdx.x] = 0;
@@ -3085,6 +3243,7 @@ __global__ void k_stats_fold(Dev d)
         d.cnt->beta_pivots = (int32_t)s_sum[S_BETAPIV];
         for (int q = 0; q < S_NUM; q++) d.cnt->trace[q] = s_sum[q];
     }
+    publish(d, host);
 }
 
 #include "pms_graph.h"
@@ -3487,7 +3646,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     // At 128^3 with the larger sizes 25.1 ms, 39.3 before (k_chain 23 ms of the
     // kernels' 48, one column of 4 760 additions at 1 us each): k_chain none left.
     const int32_t solve_max = blocks ? 2 * tn.solve : tn.solve, busy_cap = blocks ? 64 : 0x7FFFFFFF;
-    auto launch_round = [&](const int32_t *a, int32_t *an, int64_t grid_tiles, double dA) -> pms_status {
+    auto launch_round = [&](const int32_t *a, int32_t *an, int64_t grid_tiles, double dA, Counters *hout) -> pms_status {
         const unsigned gT = (unsigned)(grid_tiles > 0 ? grid_tiles : 1);
         // the chaining kernels take queued columns (at most the active ones)
         // in wavefront-sized chunks over any grid: with the active count known
@@ -3501,6 +3660,13 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
         const unsigned g_solve = chain_grid(tn.chain_blocks, 1), g_chain = chain_grid(tn.chain_blocks, kChainWaves);
         const unsigned gA = grid_for(grid_tiles * kBlock, kBlock, 65536);
         const double dt = (double)grid_tiles;
+        // few columns (the host's bound): each end of the round in one workgroup
+        const bool small_round = dA > 0 && dA <= (double)kCloseMax && !c8on && !budget && !dbg;
+        if (small_round && dA <= (double)kOpenMax) {
+            PMS_LAUNCH(c, K_PIVOTS, -1.0, k_round_open, 1, kOpenThreads, d, a, opt->compression);
+            pivots_slot = c->pend.size() - 1;
+            pivots_base = (32 + 23 + 15) * dA;
+        } else {
         // act, len, off, last row, low out, T atomic
         PMS_LAUNCH(c, K_LOW, 32 * dA, k_low, gA, kBlock, d, a);
         if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
@@ -3511,6 +3677,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
         PMS_LAUNCH(c, K_PIVOTS, -1.0, k_pivots, gT, kBlock, d, a, agg, opt->compression);
         pivots_slot = c->pend.size() - 1;
         pivots_base = 15 * dA + 16 * dt;  // act, coll, low, beta, dim, scan aggregates; + the new pivots' bytes
+        }
         if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
         if (c8on) {
             // the first unpaired rows (a scan from the last ones, usually short); act, dim, beta, state, low
@@ -3580,13 +3747,18 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
                        busy_cap);
         chain_slot = c->pend.size() - 1;
         if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
+        if (small_round) {
+            if (c->prof_on || trace || diag) PMS_LAUNCH(c, K_FILL, 0, k_stats_fold, 1, 256, d, nullptr);
+            PMS_LAUNCH(c, K_COMPACT, 14 * dA, k_round_close, 1, kOpenThreads, d, a, an, hout);
+            return PMS_OK;
+        }
         PMS_LAUNCH(c, K_COMPACT, 5 * dA, k_keep_count, gT, kBlock, d, a, keep, -1);
         PMS_LAUNCH(c, K_SCAN, 8 * dt, k_scan_sum, 1, kScanThreads, keep, 0, &d.cnt->n_cur, &d.cnt->n_next);
         // act, state, act_next
         PMS_LAUNCH(c, K_COMPACT, 9 * dA, k_compact, gT, kBlock, d, a, keep, an, -1);
         if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
-        if (c->prof_on || trace || diag) PMS_LAUNCH(c, K_FILL, 0, k_stats_fold, 1, 256, d);
-        PMS_LAUNCH(c, K_FILL, 0, k_round_end, 1, kWave, d);
+        if (c->prof_on || trace || diag) PMS_LAUNCH(c, K_FILL, 0, k_stats_fold, 1, 256, d, nullptr);
+        PMS_LAUNCH(c, K_FILL, 0, k_round_end, 1, kWave, d, hout);
         return PMS_OK;
     };
     // diagnostics after Phase 0 and after each round: low^l's l1 norm, the
@@ -3752,9 +3924,8 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
         PMS_LAUNCH(c, K_COMPACT, 2 * dm, k_mix_count, gm, kBlock, d, keep, top, do_top, dual);
         PMS_LAUNCH(c, K_SCAN, 8.0 * nblk, k_scan_sum, 1, kScanThreads, keep, nblk, nullptr, &d.cnt->n_next);
         PMS_LAUNCH(c, K_COMPACT, 2 * dm, k_mix_compact, gm, kBlock, d, keep, act0, top, do_top, dual);
-        PMS_LAUNCH(c, K_FILL, 0, k_mix_start, 1, 1, d, top, do_top, dual);
+        PMS_LAUNCH(c, K_FILL, 0, k_mix_start, 1, kWave, d, top, do_top, dual, h);
         PMS_HIP(hipGetLastError());
-        PMS_HIP(hipMemcpyAsync(h, d.cnt, sizeof(Counters), hipMemcpyDeviceToHost, st));
         PMS_HIP(hipStreamSynchronize(st));
         nA = h->n_cur;
     }
@@ -3798,7 +3969,8 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
             c->stream = gs;  // PMS_LAUNCH issues on c->stream
             pms_status sr = PMS_OK;
             for (int r = 0; r < graph_k && sr == PMS_OK; r++)
-                sr = (r & 1) ? launch_round(act1, act0, gtiles, 0.0) : launch_round(act0, act1, gtiles, 0.0);
+                sr = (r & 1) ? launch_round(act1, act0, gtiles, 0.0, nullptr)
+                             : launch_round(act0, act1, gtiles, 0.0, nullptr);
             c->stream = st;
             const hipError_t ec = hipStreamEndCapture(gs, &graph);
             if (sr != PMS_OK) {
@@ -3852,10 +4024,9 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     if (nA > 0 && !c->prof_on && !trace && !diag && !dbg && opt->max_rounds == 0 && !c8on && !budget) {
         Counters *hb[2] = {h, h + 1};
         auto queue = [&](const int32_t *a, int32_t *an, int32_t bound, int q) -> pms_status {
-            const pms_status sr = launch_round(a, an, (bound + kBlock - 1) / kBlock, (double)bound);
+            const pms_status sr = launch_round(a, an, (bound + kBlock - 1) / kBlock, (double)bound, hb[q]);
             if (sr != PMS_OK) return sr;
             PMS_HIP(hipGetLastError());
-            PMS_HIP(hipMemcpyAsync(hb[q], d.cnt, sizeof(Counters), hipMemcpyDeviceToHost, st));
             PMS_HIP(hipEventRecord(c->pipe_ev[q], st));
             return PMS_OK;
         };
@@ -3902,7 +4073,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
         }
         nA_prev = nA;
         const int64_t tiles = (nA + kBlock - 1) / kBlock;
-        pms_status sr = launch_round(act, act_next, tiles, (double)nA);
+        pms_status sr = launch_round(act, act_next, tiles, (double)nA, nullptr);
         if (sr != PMS_OK) return sr;
         if (diag) {
             sr = launch_diag();
@@ -3983,14 +4154,31 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     const pms_status sb = stage_build(sd);
     if (sb != PMS_OK) return sb;
     }
-    PMS_LAUNCH(c, K_FILL, 0, k_stats_fold, 1, 256, d);
-    if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_final, gm, kBlock, d);
-    PMS_HIP(hipMemcpyAsync(h, d.cnt, sizeof(Counters), hipMemcpyDeviceToHost, st));
-    PMS_HIP(hipStreamSynchronize(st));
-    {
+    if (dbg) {
+        PMS_LAUNCH(c, K_FILL, 0, k_dbg_final, gm, kBlock, d);
+        PMS_HIP(hipMemcpyAsync(h, d.cnt, sizeof(Counters), hipMemcpyDeviceToHost, st));
+        PMS_HIP(hipStreamSynchronize(st));
         const pms_status sdb = dbg_check("at the end, after round", (int32_t)round);
         if (sdb != PMS_OK) return sdb;
     }
+
+    // pairs and essential simplices, canonical order (nothing is written when
+    // either has more than its capacity), and the counters: one wait for all
+    int32_t *cp = keep, *ce = keep2;
+    const bool want_pairs = res->pair_birth && res->pair_death;
+    const bool want_ess = res->essential != nullptr;
+    PMS_LAUNCH(c, K_FINAL, 8 * dm, k_fin_count, (unsigned)nblk, kBlock, d, cp, ce);
+    PMS_LAUNCH(c, K_SCAN, 16.0 * nblk, k_scan_sum2, 2, kScanThreads, cp, ce, nblk, &d.cnt->n_pairs, &d.cnt->n_ess);
+    size_t fin_slot = 0;
+    if (want_pairs || want_ess) {
+        PMS_LAUNCH(c, K_FINAL, -1.0, k_fin_scatter, (unsigned)nblk, kBlock, d, cp, ce,
+                   want_pairs ? res->pair_birth : nullptr, want_pairs ? res->pair_death : nullptr, res->cap_pairs,
+                   res->essential, res->cap_essential);
+        fin_slot = c->pend.size() - 1;
+    }
+    PMS_LAUNCH(c, K_FILL, 0, k_stats_fold, 1, 256, d, h);
+    PMS_HIP(hipGetLastError());
+    PMS_HIP(hipStreamSynchronize(st));
     res->rounds = (int32_t)round + block_rounds;  // (the graphs' pass is one)
     res->additions = (int64_t)h->additions;
     res->xor_entries = (int64_t)h->xor_entries;
@@ -3998,27 +4186,12 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     res->addition_bytes =
         (int64_t)(h->abytes_xor + h->abytes_lane + h->abytes_wide + h->abytes_chain + h->abytes_solve);
     res->phase0_pivots = h->beta_pivots;
-
-    // pairs and essential simplices, canonical order
-    int32_t *cp = keep, *ce = keep2;
-    PMS_LAUNCH(c, K_FINAL, 8 * dm, k_fin_count, (unsigned)nblk, kBlock, d, cp, ce);
-    PMS_LAUNCH(c, K_SCAN, 16.0 * nblk, k_scan_sum2, 2, kScanThreads, cp, ce, nblk, &d.cnt->n_pairs, &d.cnt->n_ess);
-    PMS_HIP(hipGetLastError());
-    PMS_HIP(hipMemcpyAsync(h, d.cnt, sizeof(Counters), hipMemcpyDeviceToHost, st));
-    PMS_HIP(hipStreamSynchronize(st));
     res->n_pairs = h->n_pairs;
     res->n_essential = h->n_ess;
-    const bool want_pairs = res->pair_birth && res->pair_death;
-    const bool want_ess = res->essential != nullptr;
+    if (c->prof_on && (want_pairs || want_ess))
+        c->pend[fin_slot].bytes = 8 * dm + 8.0 * res->n_pairs + 4.0 * res->n_essential;
     if ((want_pairs && res->cap_pairs < res->n_pairs) || (want_ess && res->cap_essential < res->n_essential))
         return set_err(c, PMS_ERR_CAPACITY, "output capacity too small (n_pairs / n_essential hold the sizes)");
-    if (want_pairs || want_ess) {
-        PMS_LAUNCH(c, K_FINAL, 8 * dm + 8.0 * res->n_pairs + 4.0 * res->n_essential, k_fin_scatter,
-                   (unsigned)nblk, kBlock, d, cp, ce, want_pairs ? res->pair_birth : nullptr,
-                   want_pairs ? res->pair_death : nullptr, want_ess ? res->essential : nullptr);
-        PMS_HIP(hipGetLastError());
-        PMS_HIP(hipStreamSynchronize(st));
-    }
     if (c->prof_on) prof_flush(c);
     return PMS_OK;
 }
@@ -4119,7 +4292,7 @@ pms_status pms_create(pms_ctx **ctx, int device, void *stream)
     if (!c) return PMS_ERR_OOM;
     c->device = device;
     c->stream = (hipStream_t)stream;
-    if (hipHostMalloc(&c->host_pinned, std::max<size_t>(2 * sizeof(pms::Counters), 2048), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc(&c->host_pinned, std::max<size_t>(2 * sizeof(pms::Counters), 2048), hipHostMallocCoherent) != hipSuccess) {
         delete c;
         return PMS_ERR_OOM;
     }
