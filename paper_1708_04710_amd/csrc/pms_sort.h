@@ -16,6 +16,10 @@
 //                 running count per digit orders the rounds), places them in
 //                 LDS in digit order and writes every digit's run to its
 //                 global place with consecutive threads on consecutive keys.
+// A sort of few tiles is bound by its launches (3 to 9 us each, whatever the
+// tiles): up to kRsFewTiles the scatter sums the tiles' counts itself, and up
+// to kRsFewKeys tiles it counts the keys itself, one launch a pass (4 096
+// 32-bit keys with values: 36 us, three launches a pass 53).
 // Passes alternate between the two buffers; *in_b tells where the result is.
 #pragma once
 
@@ -27,6 +31,8 @@ constexpr int kRsThreads = 256;  // one thread per digit value in the per-digit 
 constexpr int kRsRounds = 8;     // keys per thread per tile
 constexpr int kRsTile = kRsThreads * kRsRounds;
 constexpr int kRsMaxPass = 8;
+constexpr int64_t kRsFewTiles = 32, kRsFewKeys = 4;
+enum RsMode { RS_OFFSETS, RS_COUNTS, RS_KEYS };  // what the scatter is given
 static_assert(kRsThreads == 256 && kRsThreads == kBlock, "a thread per digit; block scans of kBlock threads");
 
 template <typename K>
@@ -116,7 +122,7 @@ static __global__ void __launch_bounds__(kRsThreads) k_rs_offsets(uint32_t *cnt,
 }
 
 // One pass: every key (and value) to its stable place by digit `shift`.
-template <typename K, typename V, bool kVals>
+template <typename K, typename V, bool kVals, RsMode kMode>
 __global__ void __launch_bounds__(kRsThreads) k_rs_scatter(const K *__restrict__ kin, K *__restrict__ kout,
                                                            const V *__restrict__ vin, V *__restrict__ vout, int64_t n,
                                                            int shift, const uint32_t *__restrict__ off,
@@ -143,7 +149,29 @@ __global__ void __launch_bounds__(kRsThreads) k_rs_scatter(const K *__restrict__
         // digit tid's first place for this tile: the keys of smaller digits
         // plus those of its digit in the tiles before
         int32_t all;
-        goff[tid] = (uint32_t)block_excl_sum32((int32_t)dtot[tid], &all) + off[(int64_t)tid * ntiles + tile];
+        uint32_t mine = 0, before = 0;  // digit tid: in all tiles, in those before
+        if constexpr (kMode == RS_OFFSETS) {
+            mine = dtot[tid];
+            before = off[(int64_t)tid * ntiles + tile];
+        } else if constexpr (kMode == RS_COUNTS) {
+            for (int64_t t = 0; t < ntiles; t++) {
+                const uint32_t v = off[(int64_t)tid * ntiles + t];
+                mine += v;
+                before += t < tile ? v : 0u;
+            }
+        } else {
+            tstart[tid] = goff[tid] = 0u;
+            __syncthreads();
+            for (int64_t q = tid; q < n; q += kRsThreads) {
+                const uint32_t dg = rs_digit(kin[q], shift);
+                atomicAdd(&tstart[dg], 1u);
+                if (q < base) atomicAdd(&goff[dg], 1u);
+            }
+            __syncthreads();
+            mine = tstart[tid];
+            before = goff[tid];
+        }
+        goff[tid] = (uint32_t)block_excl_sum32((int32_t)mine, &all) + before;
         K kr[kRsRounds];
         V vr[kRsRounds];
         uint32_t rk[kRsRounds];
@@ -223,12 +251,21 @@ inline pms_status radix_sort(Ctx *c, K *a, K *b, V *va, V *vb, int64_t n, int en
     K *src = a, *dst = b;
     V *vsrc = va, *vdst = vb;
     for (int p = 0; p < npass; p++) {
-        k_rs_count<K><<<gt, kRsThreads, 0, s>>>(src, n, 8 * p, cnt, ntiles);
-        k_rs_offsets<<<256, kRsThreads, 0, s>>>(cnt, ntiles, dtot);
-        if (va)
-            k_rs_scatter<K, V, true><<<gt, kRsThreads, 0, s>>>(src, dst, vsrc, vdst, n, 8 * p, cnt, dtot, ntiles);
-        else
-            k_rs_scatter<K, V, false><<<gt, kRsThreads, 0, s>>>(src, dst, nullptr, nullptr, n, 8 * p, cnt, dtot, ntiles);
+        const RsMode mode = ntiles <= kRsFewKeys ? RS_KEYS : ntiles <= kRsFewTiles ? RS_COUNTS : RS_OFFSETS;
+        if (mode != RS_KEYS) k_rs_count<K><<<gt, kRsThreads, 0, s>>>(src, n, 8 * p, cnt, ntiles);
+        if (mode == RS_OFFSETS) k_rs_offsets<<<256, kRsThreads, 0, s>>>(cnt, ntiles, dtot);
+        auto scatter = [&](auto kernel, const V *vi, V *vo) {
+            kernel<<<gt, kRsThreads, 0, s>>>(src, dst, vi, vo, n, 8 * p, cnt, dtot, ntiles);
+        };
+        if (va) {
+            if (mode == RS_KEYS) scatter(k_rs_scatter<K, V, true, RS_KEYS>, vsrc, vdst);
+            else if (mode == RS_COUNTS) scatter(k_rs_scatter<K, V, true, RS_COUNTS>, vsrc, vdst);
+            else scatter(k_rs_scatter<K, V, true, RS_OFFSETS>, vsrc, vdst);
+        } else {
+            if (mode == RS_KEYS) scatter(k_rs_scatter<K, V, false, RS_KEYS>, nullptr, nullptr);
+            else if (mode == RS_COUNTS) scatter(k_rs_scatter<K, V, false, RS_COUNTS>, nullptr, nullptr);
+            else scatter(k_rs_scatter<K, V, false, RS_OFFSETS>, nullptr, nullptr);
+        }
         std::swap(src, dst);
         std::swap(vsrc, vdst);
         *in_b = !*in_b;
