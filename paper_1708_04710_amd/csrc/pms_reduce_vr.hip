@@ -48,9 +48,11 @@ struct VrEdgeProv {
 // 128 points 3.5 ms, 512 clouds 14.4 ms.  Here a column costs a pass over the
 // later edges, (E / 64) steps of a few hundred cycles, whatever it adds.
 //
-// Ties: triangles of a tie group interleave, so the group's edges are brought
-// into one step and the low is the smallest index among their odd triangles;
-// edges whose apparent triangle lies beyond it stay as they were.
+// Ties: triangles of a tie group interleave, so the group's edges (at most 64)
+// are brought into one step, a step that ends inside a group being cut before
+// it, and the low is the smallest index among their odd triangles; edges whose
+// apparent triangle lies beyond it stay as they were, and a column that goes on
+// from there takes the whole group again.
 __global__ void __launch_bounds__(kWave) k_vr_cocycle(VeView v, DualState s, int32_t *kedge, int round)
 {
     extern __shared__ uint64_t s_v[];  // [n][M]
@@ -69,6 +71,7 @@ __global__ void __launch_bounds__(kWave) k_vr_cocycle(VeView v, DualState s, int
         const int64_t eoff = I.eoff, key = eoff + face;
         const uint32_t *ev = v.ev + eoff;
         const uint64_t *mask = v.mask + I.moff;
+        const bool ties = I.gmax > 1;
         auto toggle = [&](uint32_t ab) {
             const int a = (int)(ab >> 16), b = (int)(ab & 0xFFFFu);
             atomicXor((unsigned long long *)&s_v[a * M + (b >> 6)], 1ull << (b & 63));
@@ -120,26 +123,33 @@ __global__ void __launch_bounds__(kWave) k_vr_cocycle(VeView v, DualState s, int
             const uint64_t odd = __ballot(first >= 0);
             __syncthreads();
             int32_t stop = kWave;  // lanes from here on stay as they were
-            int32_t again = l0;
+            int32_t again = l0 + kWave;
             low = -1;
             if (odd) {
                 const int f = __ffsll((long long)odd) - 1;
                 const int32_t lf = l0 + f;
                 const int32_t g1 = v.gend[eoff + lf];
-                if (g1 - v.gst[eoff + lf] == 1) {
+                const int32_t g0 = v.gst[eoff + lf];
+                if (g1 - g0 == 1) {
                     low = __builtin_amdgcn_readlane(in && first >= 0 ? ve_tri(v, I, l, first) : 0, f);
                     stop = f + 1;
                     again = lf;
-                } else if (g1 > l0 + kWave && f > 0) {  // the rest of the group into one step
-                    stop = f;
-                    again = lf;
+                } else if (g1 > l0 + kWave && g0 > l0) {  // the group into one step
+                    stop = g0 - l0;
+                    again = g0;
                 } else {
                     int32_t t = 0x7FFFFFFF;
                     if (first >= 0 && l < g1) t = ve_tri(v, I, l, first);
                     for (int o = kWave / 2; o > 0; o >>= 1) t = min(t, __shfl_xor(t, o, kWave));
                     low = bcast_first(t);
                     stop = g1 - l0;
-                    again = lf;
+                    again = g0;
+                }
+            } else if (ties && l0 + kWave < E) {  // (no group reaches past a step it starts)
+                const int32_t g0 = v.gst[eoff + l0 + kWave];
+                if (g0 > l0) {
+                    stop = g0 - l0;
+                    again = g0;
                 }
             }
             const bool undo = now != was && (lane >= stop || (low >= 0 && v.app[eoff + (in ? l : E - 1)] > low));
@@ -148,10 +158,6 @@ __global__ void __launch_bounds__(kWave) k_vr_cocycle(VeView v, DualState s, int
             adds += __popcll(joined);
             moved = moved || joined;
             __syncthreads();
-            if (!odd) {
-                l0 += kWave;
-                continue;
-            }
             if (low < 0) {
                 l0 = again;
                 continue;
