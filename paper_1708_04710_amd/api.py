@@ -200,21 +200,23 @@ def build_vr(clouds, thresholds=None, maxdim: int = 2, out: Filtration | None = 
     clouds = list(clouds)
     if not clouds:
         raise ValueError("no clouds")
-    dtype = clouds[0].dtype
+    dtype, dev = clouds[0].dtype, clouds[0].device
     if dtype not in (torch.int32, torch.float32) or any(c.dtype != dtype for c in clouds):
         raise TypeError("clouds must all be int32 or all float32")
-    if any(not c.is_cuda or c.dim() != 2 for c in clouds):
+    shapes = [c.shape for c in clouds]
+    if any(not c.is_cuda for c in clouds) or any(len(s) != 2 for s in shapes):
         raise ValueError("clouds must be 2-D device tensors [n, D]")
-    dev = clouds[0].device
+    if any(c.get_device() != dev.index for c in clouds):
+        raise RuntimeError("clouds must all be on one device")
     nb = len(clouds)
-    n = (ctypes.c_int32 * nb)(*[int(c.shape[0]) for c in clouds])
-    D = (ctypes.c_int32 * nb)(*[int(c.shape[1]) for c in clouds])
-    offs, o = [], 0
-    for c in clouds:
-        offs.append(o)
-        o += c.numel()
-    pt_off = (ctypes.c_int64 * nb)(*offs)
-    flat = torch.cat([c.reshape(-1) for c in clouds]) if o else torch.zeros(1, dtype=dtype, device=dev)
+    n = (ctypes.c_int32 * nb)(*[s[0] for s in shapes])
+    D = (ctypes.c_int32 * nb)(*[s[1] for s in shapes])
+    # read where they are, as offsets from the first in memory (a concatenation
+    # of 512 clouds takes 0.4 ms)
+    clouds = [c if c.is_contiguous() and not c.is_neg() else torch.cat([c.reshape(-1)]) for c in clouds]
+    ptrs = [c.data_ptr() for c in clouds]
+    base = min((p for p in ptrs if p), default=0)
+    pt_off = (ctypes.c_int64 * nb)(*[(p - base) // 4 if p else 0 for p in ptrs])
     f32 = dtype == torch.float32
     if thresholds is None:
         thresholds = [-1] * nb
@@ -224,10 +226,10 @@ def build_vr(clouds, thresholds=None, maxdim: int = 2, out: Filtration | None = 
     f = out if out is not None else Filtration(dev)
     ctx = _ctx(dev)
     fn = B.load().pms_build_vr_f32 if f32 else B.load().pms_build_vr_i32
-    st = fn(ctx, flat.data_ptr(), nb, n, D, pt_off, thr, maxdim, ctypes.byref(f.handle), col_off)
+    st = fn(ctx, base or None, nb, n, D, pt_off, thr, maxdim, ctypes.byref(f.handle), col_off)
     _binding_check(ctx, st)
     f._refresh()
-    return f, [int(x) for x in col_off]
+    return f, list(col_off)
 
 
 def _binding_check(ctx, st):

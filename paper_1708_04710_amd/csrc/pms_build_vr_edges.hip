@@ -244,6 +244,94 @@ __global__ void __launch_bounds__(kBlock) k_ve_masks(const VeCloud *cl, int maxd
     }
 }
 
+// The same with the cloud's ranks in LDS as pairs of 16-bit words (n <=
+// kLdsPoints: at most 32 640 edges), one lane per edge going through its ends'
+// rows: 3.5 instructions per 64 vertices and edge against 25 with a ballot, and
+// rows of an odd number of words, so that different rows start in different
+// banks.  Two rows per edge from L2, the kernel above takes 745 us for 512 clouds
+// of 32 to 256 points (1.9 M edges); with ballots over LDS 505; this one 218 (64
+// clouds of 128 points: 129, now 27).  Few edges leave most lanes idle and are
+// bound by one lane's chain (100 points: 13 us, a wavefront an edge 4).
+constexpr int kLdsPoints = 256, kVeMaskThreads = 1024;
+constexpr int64_t kVeManyEdges = 1 << 16;
+__host__ __device__ inline int ve_rank_row(int n) { return (n + 31) / 32 * 16 + 1; }
+
+__global__ void __launch_bounds__(kVeMaskThreads) k_ve_masks_lds(const VeCloud *cl, int maxdim, const uint32_t *ev_s,
+                                                                 const int32_t *gst_s, const int32_t *gend_s,
+                                                                 const int32_t *erank, uint32_t *ev, int32_t *gst,
+                                                                 int32_t *gend, uint2 *rec, uint64_t *mask,
+                                                                 int32_t *tcnt, int32_t *apc)
+{
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    extern __shared__ u16x2 s_rank[];
+    const VeCloud I = cl[blockIdx.y];
+    const int W = maxdim >= 2 ? I.W : 0, row = ve_rank_row(I.n);
+    if ((int32_t)blockIdx.x * kVeMaskThreads >= I.E) return;
+    if (W > 0) {
+        // (columns past n: no edge)
+        const int32_t words = I.n * row;
+        for (int32_t i0 = threadIdx.x; i0 < words; i0 += 4 * kVeMaskThreads) {
+            int32_t r[4][2];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const int32_t i = min(i0 + u * kVeMaskThreads, words - 1), a = i / row, c = 2 * (i - a * row);
+                const int32_t *ra = erank + I.slot_base + (int64_t)a * I.n;
+                r[u][0] = c < I.n ? ra[c] : kNoEdge;
+                r[u][1] = c + 1 < I.n ? ra[c + 1] : kNoEdge;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+                if (i0 + u * kVeMaskThreads < words)
+                    s_rank[i0 + u * kVeMaskThreads] =
+                        u16x2{(uint16_t)min(r[u][0], 0xFFFF), (uint16_t)min(r[u][1], 0xFFFF)};
+        }
+    }
+    __syncthreads();
+    for (int32_t e = (int32_t)blockIdx.x * kVeMaskThreads + (int32_t)threadIdx.x; e < I.E;
+         e += (int32_t)gridDim.x * kVeMaskThreads) {
+        const uint32_t ab = ev_s[I.cap_off + e];
+        const int32_t ge = gend_s[I.cap_off + e];
+        const u16x2 *ra = s_rank + (ab >> 16) * row, *rb = s_rank + (ab & 0xFFFFu) * row;
+        uint2 *r = rec + I.woff + (int64_t)e * I.W;
+        int32_t t = 0, first = -1;
+        bool first_in = false;
+        uint32_t even = 0;
+        for (int w = 0; w < W; w++, ra += 16, rb += 16) {
+            uint32_t m = 0;
+#pragma unroll
+            for (int k = 15; k >= 0; k--) {
+                const u16x2 z = __builtin_elementwise_max(ra[k], rb[k]);
+                m = m << 1 | (uint32_t)(z.y < e);
+                m = m << 1 | (uint32_t)(z.x < e);
+            }
+            uint32_t mv = m;  // cofaces of the edge's own value
+            if (ge - e > 1) {
+                mv = 0;
+                for (int k = 15; k >= 0; k--) {
+                    const u16x2 z = __builtin_elementwise_max(ra[k], rb[k]);
+                    mv = mv << 2 | (uint32_t)(z.y < ge) << 1 | (uint32_t)(z.x < ge);
+                }
+            }
+            if (first < 0 && mv) {
+                const int f = __ffs((int)mv) - 1;
+                first = w * 32 + f;
+                first_in = (m >> f) & 1u;
+            }
+            t += __popc(m);
+            r[w].x = m;
+            if (w & 1 || w == W - 1)
+                mask[I.moff + (int64_t)e * I.M + (w >> 1)] = w & 1 ? (uint64_t)m << 32 | even : (uint64_t)m;
+            even = m;
+        }
+        const int64_t o = I.eoff + e;
+        ev[o] = ab;
+        gst[o] = gst_s[I.cap_off + e];
+        gend[o] = ge;
+        tcnt[o] = t;
+        apc[o] = first_in ? first : -1;
+    }
+}
+
 __global__ void __launch_bounds__(1024) k_ve_scan(VeCloud *cl, int32_t *tcnt)
 {
     const VeCloud I = cl[blockIdx.x];
@@ -321,86 +409,161 @@ __device__ inline int ve_select(const uint2 *w, int W, int k)
     return q * 32 + __ffs((int)m) - 1;
 }
 
-// One lane per edge (and per vertex): index, column, rec's indices.
-template <bool F32>
-__global__ void __launch_bounds__(kBlock) k_ve_emit(VeView v, VeOut o, int maxdim, const unsigned long long *eval,
-                                                    int32_t *eidx, uint2 *rec, int32_t *app, uint32_t *recd)
+// Edges of a workgroup of k_ve_emit and k_ve_tris: their mask words pass
+// through LDS (kTileWords of them, fewer edges when a cloud has more words).
+// Few edges in all: 8 a workgroup (an edge of 100 points has up to 98 triangles;
+// 64 of the last ones hold a launch of 4 950 edges for 27 us, 8 for 7.6).
+constexpr int kVeTile = 64, kVeFewTile = 8, kTileWords = 2048;
+inline int ve_tile(int W, int64_t E)
 {
+    return std::min(E >= kVeManyEdges ? kVeTile : kVeFewTile, W <= 1 ? kVeTile : W < kTileWords ? kTileWords / W : 1);
+}
+
+// One lane per edge: its index, rec's indices.  The mask words are read and
+// written by the whole workgroup in their order.
+__global__ void __launch_bounds__(kBlock) k_ve_emit(VeView v, int maxdim, int per, int32_t *eidx, uint2 *rec, int32_t *app,
+                                                    uint32_t *recd)
+{
+    __shared__ uint32_t s_w[kTileWords], s_run[kTileWords];
     const VeCloud I = v.cl[blockIdx.y];
-    const int32_t pb = (int32_t)I.pbase;
-    for (int32_t x = blockIdx.x * kBlock + threadIdx.x; x < I.n; x += gridDim.x * kBlock)
-        ve_put<F32>(o, I.col_base + x, I.nnz_base, 0, 0, 0, make_int2(-1, -1), make_int4(pb + x, -1, -1, -1));
     const int W = maxdim >= 2 ? I.W : 0;
-    for (int32_t e = blockIdx.x * kBlock + threadIdx.x; e < I.E; e += gridDim.x * kBlock) {
-        const int64_t oe = I.eoff + e;
-        const uint32_t ab = v.ev[oe];
-        const int a = (int)(ab >> 16), b = (int)(ab & 0xFFFFu);
-        const int32_t g0 = v.gst[oe], g1 = v.gend[oe];
-        const int32_t ts = v.tscan[I.eoff + g0], qs = ve_q(v, I, g0);
-        const bool tied = g1 - g0 > 1;
-        const int32_t pe = I.n + e + ts + qs;
-        const int32_t tb = I.n + g1 + ts + qs;
-        const int64_t cp = I.nnz_base + 2LL * e + 3LL * ts + 4LL * qs;
-        eidx[I.slot_base + (int64_t)a * I.n + b] = pe;
-        eidx[I.slot_base + (int64_t)b * I.n + a] = pe;
-        ve_put<F32>(o, I.col_base + pe, cp, 2, 1, eval[I.cap_off + e], make_int2(pb + a, pb + b),
-                    make_int4(pb + a, pb + b, -1, -1));
-        o.rows[cp] = (int32_t)I.col_base + a;
-        o.rows[cp + 1] = (int32_t)I.col_base + b;
-        const int apc = v.apc[oe];
-        uint2 *r = rec + I.woff + (int64_t)e * I.W;
-        uint32_t *rd = recd ? recd + I.woff + (int64_t)e * I.W : nullptr;
-        int32_t run = 0, at = -1;
-        for (int w = 0; w < W; w++) {
-            const uint32_t m = r[w].x;
-            r[w].y = tied ? kTied : (uint32_t)(tb + run);
-            if (rd) rd[w] = (uint32_t)(v.tscan[oe] + run);
-            if (apc >= 0 && (apc >> 5) == w) at = tb + run + __popc(m & below(apc));
-            run += __popc(m);
+    const bool lds = W <= kTileWords;
+    for (int32_t e0 = blockIdx.x * per; e0 < I.E; e0 += gridDim.x * per) {
+        const int32_t ne = min(per, I.E - e0);
+        uint2 *r0 = rec + I.woff + (int64_t)e0 * I.W;
+        if (lds) {
+            for (int32_t k = threadIdx.x; k < ne * W; k += kBlock) s_w[k] = r0[k].x;
+            __syncthreads();
         }
-        app[oe] = apc >= 0 && tied ? tb + ve_tie_rank(v, I, e, apc) : at;
+        if ((int32_t)threadIdx.x < ne) {
+            const int32_t e = e0 + (int32_t)threadIdx.x;
+            const int64_t oe = I.eoff + e;
+            const uint32_t ab = v.ev[oe];
+            const int a = (int)(ab >> 16), b = (int)(ab & 0xFFFFu);
+            const int32_t g0 = v.gst[oe], g1 = v.gend[oe];
+            const int32_t ts = v.tscan[I.eoff + g0], qs = ve_q(v, I, g0), own = v.tscan[oe];
+            const bool tied = g1 - g0 > 1;
+            const int32_t pe = I.n + e + ts + qs;
+            const int32_t tb = I.n + g1 + ts + qs;
+            eidx[I.slot_base + (int64_t)a * I.n + b] = pe;
+            eidx[I.slot_base + (int64_t)b * I.n + a] = pe;
+            const int apc = v.apc[oe];
+            uint2 *r = r0 + (int64_t)threadIdx.x * I.W;
+            uint32_t *rd = recd ? recd + I.woff + (int64_t)e * I.W : nullptr;
+            int32_t run = 0, at = -1;
+            for (int w = 0; w < W; w++) {
+                const uint32_t m = lds ? s_w[threadIdx.x * W + w] : r[w].x;
+                const uint32_t y = tied ? kTied : (uint32_t)(tb + run);
+                if (lds) s_run[threadIdx.x * W + w] = y;
+                else r[w].y = y;
+                if (rd) rd[w] = (uint32_t)(own + run);
+                if (apc >= 0 && (apc >> 5) == w) at = tb + run + __popc(m & below(apc));
+                run += __popc(m);
+            }
+            app[oe] = apc >= 0 && tied ? tb + ve_tie_rank(v, I, e, apc) : at;
+        }
+        if (lds) {
+            __syncthreads();
+            for (int32_t k = threadIdx.x; k < ne * W; k += kBlock) r0[k].y = s_run[k];
+            __syncthreads();
+        }
     }
 }
 
-// One lane per triangle, in the order of (edge, third vertex).  Bound by the
-// writes; the gathers (masks, the other edges' indices) stay in one cloud's
-// tables and hit L2.
+// The columns of vertices, edges and triangles: one lane per triangle, in the
+// order of (edge, third vertex), a workgroup the triangles of kVeTile edges, and
+// the edges' own columns, which lie between them (written by a kernel of their
+// own, 1.6 M edges' scattered pieces of lines took 0.3 ms).  Which edge and
+// which vertex from the edges' counts and mask words in LDS.  Bound by the writes; the other edges' indices are
+// gathered from one cloud's table and hit L2.  (The same look-ups from memory,
+// a chain of up to twenty loads per triangle: 26 M triangles of 512 clouds 1.19
+// ms, 22 M of 64 clouds 0.58; now 0.68 and 0.37, 2.5 TB/s of writes.)
 template <bool F32>
-__global__ void __launch_bounds__(kBlock) k_ve_tris(VeView v, VeOut o, const unsigned long long *eval, int32_t *trip, int32_t *appt)
+__global__ void __launch_bounds__(kBlock) k_ve_tris(VeView v, VeOut o, int maxdim, int per, const unsigned long long *eval,
+                                                    int32_t *trip, int32_t *appt)
 {
+    __shared__ uint32_t s_w[kTileWords];
+    __shared__ int32_t s_ts[kVeTile + 1], s_ab[kVeTile], s_g0[kVeTile], s_g1[kVeTile], s_tg[kVeTile], s_qs[kVeTile];
+    __shared__ unsigned long long s_val[kVeTile];
     const VeCloud I = v.cl[blockIdx.y];
     const int32_t pb = (int32_t)I.pbase, cb = (int32_t)I.col_base;
     const int32_t *ts = v.tscan + I.eoff;
-    const int64_t tiles = (I.T + kBlock - 1) / kBlock;
-    const int64_t t0 = tiles * blockIdx.x / gridDim.x, t1 = tiles * (blockIdx.x + 1) / gridDim.x;
-    int64_t lo = 0;
-    for (int64_t tile = t0; tile < t1; tile++) {
-        lo = wave_last_le(ts, lo, I.E, tile * kBlock);
-        const int64_t hi = min((int64_t)I.E, lo + kBlock);  // not past it, unless edges without triangles lie between
-        const int64_t t = tile * kBlock + threadIdx.x;
-        if (t >= I.T) continue;
-        const int32_t e = (int32_t)lane_last_le(ts, lo, hi < I.E && ts[hi] <= t ? (int64_t)I.E : hi, t);
-        const int64_t oe = I.eoff + e;
-        const int c = ve_select(v.rec + I.woff + (int64_t)e * I.W, I.W, (int)(t - ts[e]));
-        const uint32_t ab = v.ev[oe];
-        const int a = (int)(ab >> 16), b = (int)(ab & 0xFFFFu);
-        const int32_t g0 = v.gst[oe], g1 = v.gend[oe];
-        const int32_t qs = ve_q(v, I, g0);
-        const int32_t r = g1 - g0 > 1 ? ve_tie_rank(v, I, e, c) : (int32_t)t - ts[g0];
-        const int64_t p = (int64_t)cb + I.n + g1 + ts[g0] + qs + r;
-        const int64_t cp = I.nnz_base + 2LL * g1 + 3LL * (ts[g0] + r) + 4LL * qs;
-        const int32_t *ix = v.eidx + I.slot_base;
-        const int32_t r0 = ix[(int64_t)a * I.n + c], r1 = ix[(int64_t)b * I.n + c];
-        const int x = min(a, c), z = max(b, c);
-        ve_put<F32>(o, p, cp, 3, 2, eval[I.cap_off + e], make_int2(pb + a, pb + b),
-                    make_int4(pb + x, pb + a + b + c - x - z, pb + z, -1));
-        o.rows[cp] = cb + min(r0, r1);
-        o.rows[cp + 1] = cb + max(r0, r1);
-        o.rows[cp + 2] = cb + I.n + e + ts[g0] + qs;
-        if (appt) {
-            trip[I.toff + ts[g0] + r] = (int32_t)(p - cb);
-            appt[p] = -1;
+    const int32_t *ix = v.eidx + I.slot_base;
+    for (int32_t x = blockIdx.x * kBlock + threadIdx.x; x < I.n; x += gridDim.x * kBlock)
+        ve_put<F32>(o, I.col_base + x, I.nnz_base, 0, 0, 0, make_int2(-1, -1), make_int4(pb + x, -1, -1, -1));
+    const int W = maxdim >= 2 ? I.W : 0;
+    const bool lds = W <= kTileWords;
+    for (int32_t e0 = blockIdx.x * per; e0 < I.E; e0 += gridDim.x * per) {
+        const int32_t ne = min(per, I.E - e0);
+        const uint2 *rec = v.rec + I.woff + (int64_t)e0 * W;
+        if ((int32_t)threadIdx.x <= ne) s_ts[threadIdx.x] = ts[e0 + threadIdx.x];
+        if ((int32_t)threadIdx.x < ne) {
+            const int32_t e = e0 + (int32_t)threadIdx.x;
+            const int64_t oe = I.eoff + e;
+            const int32_t g0 = v.gst[oe], tg = ts[g0], qs = ve_q(v, I, g0);
+            const uint32_t ab = v.ev[oe];
+            const unsigned long long val = eval[I.cap_off + e];
+            s_ab[threadIdx.x] = (int32_t)ab;
+            s_g0[threadIdx.x] = g0;
+            s_g1[threadIdx.x] = v.gend[oe];
+            s_tg[threadIdx.x] = tg;
+            s_qs[threadIdx.x] = qs;
+            s_val[threadIdx.x] = val;
+            const int a = (int)(ab >> 16), b = (int)(ab & 0xFFFFu);
+            const int64_t cp = I.nnz_base + 2LL * e + 3LL * tg + 4LL * qs;
+            ve_put<F32>(o, (int64_t)cb + I.n + e + tg + qs, cp, 2, 1, val, make_int2(pb + a, pb + b),
+                        make_int4(pb + a, pb + b, -1, -1));
+            o.rows[cp] = cb + a;
+            o.rows[cp + 1] = cb + b;
         }
+        if (lds)
+            for (int32_t k = threadIdx.x; k < ne * W; k += kBlock) s_w[k] = rec[k].x;
+        __syncthreads();
+        const int32_t t1 = s_ts[ne];
+        for (int32_t t = s_ts[0] + (int32_t)threadIdx.x; t < t1; t += kBlock) {
+            int i = 0, end = ne;  // the last edge with s_ts[i] <= t
+            while (end - i > 1) {
+                const int mid = (i + end) >> 1;
+                if (s_ts[mid] <= t) i = mid;
+                else end = mid;
+            }
+            const int32_t e = e0 + i;
+            int k = t - s_ts[i], q = 0;
+            uint32_t m = lds ? s_w[i * W] : rec[(int64_t)i * W].x;
+            while (__popc(m) <= k) {  // (the edge has more than k)
+                k -= __popc(m);
+                q++;
+                m = lds ? s_w[i * W + q] : rec[(int64_t)i * W + q].x;
+            }
+            int c = q * 32;  // the k-th bit of m
+#pragma unroll
+            for (int h = 16; h > 0; h >>= 1) {
+                const int below_h = __popc(m & ((1u << h) - 1u));
+                if (k >= below_h) {
+                    k -= below_h;
+                    c += h;
+                    m >>= h;
+                }
+            }
+            const uint32_t ab = (uint32_t)s_ab[i];
+            const int a = (int)(ab >> 16), b = (int)(ab & 0xFFFFu);
+            const int32_t ra = ix[(int64_t)a * I.n + c], rb = ix[(int64_t)b * I.n + c];
+            const int32_t g1 = s_g1[i], tg = s_tg[i], qs = s_qs[i];
+            const int32_t r = g1 - s_g0[i] > 1 ? ve_tie_rank(v, I, e, c) : t - tg;
+            const int64_t p = (int64_t)cb + I.n + g1 + tg + qs + r;
+            const int64_t cp = I.nnz_base + 2LL * g1 + 3LL * (tg + r) + 4LL * qs;
+            const int x = min(a, c), z = max(b, c);
+            ve_put<F32>(o, p, cp, 3, 2, s_val[i], make_int2(pb + a, pb + b),
+                        make_int4(pb + x, pb + a + b + c - x - z, pb + z, -1));
+            o.rows[cp] = cb + min(ra, rb);
+            o.rows[cp + 1] = cb + max(ra, rb);
+            o.rows[cp + 2] = cb + I.n + e + tg + qs;
+            if (appt) {
+                trip[I.toff + tg + r] = (int32_t)(p - cb);
+                appt[p] = -1;
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -579,7 +742,16 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
                           int *done)
 {
     *done = 0;
-    std::vector<VeCloud> h((size_t)B);
+    struct {
+        VeCloud *first;
+        int32_t n;
+        VeCloud *begin() const { return first; }
+        VeCloud *end() const { return first + n; }
+        VeCloud &operator[](size_t b) const { return first[b]; }
+        VeCloud *data() const { return first; }
+    } h{(VeCloud *)pinned_stage(c, (size_t)B * sizeof(VeCloud) + 64), B};
+    if (!h.first) return set_err(c, PMS_ERR_OOM, "pinned host memory");
+    int32_t &herr = *(int32_t *)(h.first + B);
     int64_t slots = 0, pairs = 0, pbase = 0, nmax = 1, maxpairs = 0;
     for (int b = 0; b < B; b++) {
         VeCloud &I = h[(size_t)b];
@@ -630,7 +802,6 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
     int32_t *erank = (int32_t *)f->vr[VR_ERANK].p, *eidx = (int32_t *)f->vr[VR_EIDX].p;
     PMS_HIP(hipMemcpyAsync(dcl, h.data(), (size_t)B * sizeof(VeCloud), hipMemcpyHostToDevice, s));
     PMS_HIP(hipMemsetAsync(err, 0, 4, s));
-    int32_t herr = 0;
     auto read_clouds = [&]() -> pms_status {
         PMS_HIP(hipMemcpyAsync(h.data(), dcl, (size_t)B * sizeof(VeCloud), hipMemcpyDeviceToHost, s));
         PMS_HIP(hipMemcpyAsync(&herr, err, 4, hipMemcpyDeviceToHost, s));
@@ -724,9 +895,26 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
         return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((units + per - 1) / per, std::max(16, 16384 / B))),
                     (unsigned)B);
     };
-    PMS_LAUNCH(c, K_VR_TRI, 8.0 * words + 28.0 * E, k_ve_masks, grid(emax, kWavesPerBlock), kBlock, cl, maxdim, ev_s,
-               gst_s, gend_s, erank, ev, gst, gend, rec, (uint64_t *)f->vr[VR_MASK].p, tscan,
-               (int32_t *)f->vr[VR_APC].p);
+    uint64_t *mask = (uint64_t *)f->vr[VR_MASK].p;
+    int32_t *apc = (int32_t *)f->vr[VR_APC].p;
+    if (nmax <= kLdsPoints && E >= kVeManyEdges) {
+        const size_t bytes = maxdim >= 2 ? (size_t)nmax * ve_rank_row((int)nmax) * 4 : 0;
+        const unsigned parts = (unsigned)std::max<int64_t>(
+            1, std::min<int64_t>((emax + kVeMaskThreads - 1) / kVeMaskThreads, std::max(1, 1024 / B)));
+        PMS_HIP(hipFuncSetAttribute((const void *)k_ve_masks_lds, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+        hipEvent_t e0 = nullptr;
+        if (c->prof_on) { e0 = prof_event(c); (void)hipEventRecord(e0, s); }
+        k_ve_masks_lds<<<dim3(parts, (unsigned)B), kVeMaskThreads, bytes, s>>>(cl, maxdim, ev_s, gst_s, gend_s, erank, ev,
+                                                                              gst, gend, rec, mask, tscan, apc);
+        if (c->prof_on) {
+            hipEvent_t e1 = prof_event(c);
+            (void)hipEventRecord(e1, s);
+            c->pend.push_back({K_VR_TRI, e0, e1, 8.0 * words + 28.0 * E, 0.0});
+        }
+    } else {
+        PMS_LAUNCH(c, K_VR_TRI, 8.0 * words + 28.0 * E, k_ve_masks, grid(emax, kWavesPerBlock), kBlock, cl, maxdim, ev_s,
+                   gst_s, gend_s, erank, ev, gst, gend, rec, mask, tscan, apc);
+    }
     PMS_LAUNCH(c, K_BUILD_SCAN, 8.0 * E, k_ve_scan, (unsigned)B, 1024, cl, tscan);
     PMS_HIP(hipGetLastError());
     PMS_HIP(hipMemcpyAsync(h.data(), cl, (size_t)B * sizeof(VeCloud), hipMemcpyDeviceToHost, s));
@@ -792,12 +980,10 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
         int32_t *appt = maxdim >= 3 ? (int32_t *)f->vr[VR_APPT].p : nullptr;
         int32_t *trip = maxdim >= 3 ? (int32_t *)f->vr[VR_TRIP].p : nullptr;
         const double pb = f32 ? 37.0 : 41.0;
-        if (f32) PMS_LAUNCH(c, K_VR_INDEX, (pb + 8) * E, k_ve_emit<true>, grid(std::max(emax, nmax), kBlock), kBlock, v, o, maxdim, eval, eidx, rec, app, recd);
-        else PMS_LAUNCH(c, K_VR_INDEX, (pb + 8) * E, k_ve_emit<false>, grid(std::max(emax, nmax), kBlock), kBlock, v, o, maxdim, eval, eidx, rec, app, recd);
-        if (T > 0) {
-            if (f32) PMS_LAUNCH(c, K_VR_ROWS, (pb + 12) * T, k_ve_tris<true>, grid(tmax, 2 * kBlock), kBlock, v, o, eval, trip, appt);
-            else PMS_LAUNCH(c, K_VR_ROWS, (pb + 12) * T, k_ve_tris<false>, grid(tmax, 2 * kBlock), kBlock, v, o, eval, trip, appt);
-        }
+        const int tile = ve_tile(maxdim >= 2 ? (int)((nmax + 31) / 32) : 0, E);
+        PMS_LAUNCH(c, K_VR_INDEX, 8.0 * words + 40.0 * E, k_ve_emit, grid(emax, tile), kBlock, v, maxdim, tile, eidx, rec, app, recd);
+        if (f32) PMS_LAUNCH(c, K_VR_ROWS, (pb + 8) * E + (pb + 12) * T, k_ve_tris<true>, grid(std::max(emax, nmax), tile), kBlock, v, o, maxdim, tile, eval, trip, appt);
+        else PMS_LAUNCH(c, K_VR_ROWS, (pb + 8) * E + (pb + 12) * T, k_ve_tris<false>, grid(std::max(emax, nmax), tile), kBlock, v, o, maxdim, tile, eval, trip, appt);
         if (maxdim >= 3 && T > 0) {
             PMS_LAUNCH(c, K_VR_INDEX, 8.0 * words2, k_ve_tindex, grid(tmax, kBlock), kBlock, v, tri, rec2, appt);
             if (f32) PMS_LAUNCH(c, K_VR_ROWS, (pb + 16) * Q, k_ve_tets<true>, grid(qmax, 2 * kBlock), kBlock, v, o, eval, tri);

@@ -100,6 +100,7 @@ struct Ctx {
     int32_t *arena = nullptr;
     uint64_t arena_cap = 0;  // entries
     void *host_pinned = nullptr;
+    Buf stage;  // pinned host memory of the builders (pinned_stage)
     // graph-mode rounds: captured and replayed on a stream of the context
     // (the caller's may be the legacy default stream, which cannot capture)
     hipStream_t graph_stream = nullptr;
@@ -128,6 +129,24 @@ enum BufId {
     B_NUM
 };
 static_assert(B_NUM <= 64, "Ctx::b holds 64 buffers");
+
+// Pinned host memory that the device copies from and to (a copy with pageable
+// memory waits for a staging copy, 30 to 80 us a piece of 70 KB); grow-only,
+// one use at a time, each ending with a wait for the stream.
+inline void *pinned_stage(Ctx *c, size_t bytes)
+{
+    if (c->stage.bytes < bytes) {
+        if (c->stage.p) (void)hipHostFree(c->stage.p);
+        c->stage.p = nullptr;
+        c->stage.bytes = 0;
+        if (hipHostMalloc(&c->stage.p, bytes, hipHostMallocDefault) != hipSuccess) {
+            c->stage.p = nullptr;
+            return nullptr;
+        }
+        c->stage.bytes = bytes;
+    }
+    return c->stage.p;
+}
 
 // Grow-only scratch: returns the buffer, reallocating (contents dropped) when
 // it is smaller than `bytes`.

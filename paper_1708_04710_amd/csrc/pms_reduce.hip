@@ -4332,6 +4332,7 @@ void pms_destroy(pms_ctx *c)
         if (b.p) (void)hipFree(b.p);
     if (c->arena) (void)hipFree(c->arena);
     if (c->host_pinned) (void)hipHostFree(c->host_pinned);
+    if (c->stage.p) (void)hipHostFree(c->stage.p);
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
     if (c->graph_ev) (void)hipEventDestroy(c->graph_ev);
     for (auto e : c->pipe_ev)
