@@ -201,7 +201,7 @@ __device__ inline int ls_select(const ulonglong2 m, int n)
 
 // The simplices of kV vertices in the sorted order, one thread a simplex:
 // neighbouring threads write neighbouring places (but for the index table, and
-// where vertices share a value).  Bound by those writes: 12.4 M simplices of a
+// where vertices share a value).  Bound by those writes: 53.7 M simplices of a
 // 128^3 field take 0.98 ms, of which the scattered index table is most; the 64-bit
 // sort of all simplices and its decoding took 4.8.  Fields of few vertices
 // take tiles of 32: the last vertices in the order have up to 75 simplices

@@ -24,6 +24,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "pms_build.h"
@@ -34,7 +35,7 @@
 namespace pms {
 
 constexpr int kVeThreads = 1024;
-constexpr int kLdsEdges = 16384;  // 64-bit keys sorted in one workgroup's LDS (128 KB)
+constexpr int kLdsEdges = 16 * kVeThreads;  // 64-bit keys sorted in one workgroup's LDS (128 KB)
 constexpr int kVeValueBitsF = 31, kVeValueBitsI = 35;
 
 // Squared distance of points a, b (FP32: rounded step by step in coordinate
@@ -103,6 +104,86 @@ __device__ inline void ve_place(VeCloud *cl, const VeCloud &I, int lexb, const u
     erank[I.slot_base + (int64_t)b * I.n + a] = r;
 }
 
+// x of the lane whose number differs in bit kM.
+template <int kM>
+__device__ inline unsigned long long lane_xor(unsigned long long x)
+{
+    uint32_t h[2] = {(uint32_t)x, (uint32_t)(x >> 32)};
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        if constexpr (kM == 1) h[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h[k], 0xB1, 0xF, 0xF, true);  // quad_perm 1 0 3 2
+        else if constexpr (kM == 2) h[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h[k], 0x4E, 0xF, 0xF, true);  // quad_perm 2 3 0 1
+        else if constexpr (kM == 8) h[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h[k], 0x128, 0xF, 0xF, true);  // row_ror 8
+        else h[k] = (uint32_t)__shfl_xor((int)h[k], kM, kWave);
+    }
+    return (unsigned long long)h[1] << 32 | h[0];
+}
+
+// E <= kE * kVeThreads keys sorted in place by the workgroup: bitonic, element
+// t kE + r in thread t's register r.  Partners in the thread's own registers or
+// in another lane of its wavefront need no barrier: of the 91 steps of 8 192
+// keys 10 go through LDS (with all of them there k_ve_edges took 82 us for one cloud
+// of 100 points, now 46; 512 clouds 368 and 274).
+template <int kE>
+__device__ inline void ve_sort(unsigned long long *key, int32_t E)
+{
+    const int t = threadIdx.x;
+    unsigned long long v[kE];
+#pragma unroll
+    for (int r = 0; r < kE; r++) v[r] = r * kVeThreads + t < E ? key[r * kVeThreads + t] : ~0ull;
+    auto own = [&](int r, int j, bool asc) {
+        const unsigned long long x = v[r], y = v[r | j];
+        const bool sw = (x > y) == asc;
+        v[r] = sw ? y : x;
+        v[r | j] = sw ? x : y;
+    };
+    auto other = [&](int r, unsigned long long y, bool least) {
+        const bool sw = (v[r] > y) == least;
+        v[r] = sw ? y : v[r];
+    };
+#pragma unroll
+    for (int k = 2; k < kE; k <<= 1)
+#pragma unroll
+        for (int j = k >> 1; j > 0; j >>= 1)
+#pragma unroll
+            for (int r = 0; r < kE; r++)
+                if (!(r & j)) own(r, j, !(r & k));
+    for (int k = kE < 2 ? 2 : kE; k <= kVeThreads * kE; k <<= 1) {
+        const bool asc = ((t * kE) & k) == 0;
+        for (int j = k >> 1; j >= kWave * kE; j >>= 1) {
+            const int m = j / kE;
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kE; r++) key[r * kVeThreads + t] = v[r];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kE; r++) other(r, key[r * kVeThreads + (t ^ m)], ((t & m) == 0) == asc);
+        }
+        auto lanes = [&](auto mask) {
+            constexpr int kM = decltype(mask)::value;
+            if (k < 2 * kM * kE) return;
+            const bool least = ((t & kM) == 0) == asc;
+#pragma unroll
+            for (int r = 0; r < kE; r++) other(r, lane_xor<kM>(v[r]), least);
+        };
+        lanes(std::integral_constant<int, 32>());
+        lanes(std::integral_constant<int, 16>());
+        lanes(std::integral_constant<int, 8>());
+        lanes(std::integral_constant<int, 4>());
+        lanes(std::integral_constant<int, 2>());
+        lanes(std::integral_constant<int, 1>());
+#pragma unroll
+        for (int j = kE >> 1; j > 0; j >>= 1)
+#pragma unroll
+            for (int r = 0; r < kE; r++)
+                if (!(r & j)) own(r, j, asc);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kE; r++) key[t * kE + r] = v[r];
+    __syncthreads();
+}
+
 template <bool F32>
 __global__ void __launch_bounds__(kVeThreads) k_ve_edges(VeCloud *cl, const void *pts, int lexb, int32_t cap,
                                                          uint32_t *ev, unsigned long long *eval, int32_t *erank,
@@ -141,22 +222,11 @@ __global__ void __launch_bounds__(kVeThreads) k_ve_edges(VeCloud *cl, const void
         cl[blockIdx.x].gmax = 1;
     }
     if (E > cap) return;  // the host takes the device-wide sort
-    int32_t P = 2;
-    while (P < E) P <<= 1;
-    for (int32_t i = E + tid; i < P; i += kVeThreads) s_key[i] = ~0ull;
-    __syncthreads();
-    for (int32_t k = 2; k <= P; k <<= 1)
-        for (int32_t j = k >> 1; j > 0; j >>= 1) {
-            for (int32_t i = tid; i < (P >> 1); i += kVeThreads) {
-                const int32_t x = 2 * i - (i & (j - 1)), y = x + j;
-                const unsigned long long u = s_key[x], w = s_key[y];
-                if ((u > w) == ((x & k) == 0)) {
-                    s_key[x] = w;
-                    s_key[y] = u;
-                }
-            }
-            __syncthreads();
-        }
+    if (E <= kVeThreads) ve_sort<1>(s_key, E);
+    else if (E <= 2 * kVeThreads) ve_sort<2>(s_key, E);
+    else if (E <= 4 * kVeThreads) ve_sort<4>(s_key, E);
+    else if (E <= 8 * kVeThreads) ve_sort<8>(s_key, E);
+    else ve_sort<16>(s_key, E);
     for (int32_t r = tid; r < E; r += kVeThreads)
         ve_place(&cl[blockIdx.x], I, lexb, s_key, E, r, ev, eval, erank, gst, gend);
 }
@@ -816,7 +886,7 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
     bool lds = maxpairs <= 8 * kLdsEdges;
     for (auto &I : h) lds = lds && (I.has_thr || (int64_t)I.n * (I.n - 1) / 2 <= kLdsEdges);
     if (lds) {
-        int32_t cap = 2;
+        int32_t cap = kVeThreads;  // (a sort has at least one key a thread)
         while (cap < kLdsEdges && cap < maxpairs) cap <<= 1;
         const size_t bytes = (size_t)cap * 8;
         const void *fn = f32 ? (const void *)k_ve_edges<true> : (const void *)k_ve_edges<false>;

@@ -3633,11 +3633,11 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     double pivots_base = 0;
     const pms_tuning tn = c->tune;
     // Columns that overfill the sweep kernel's list come with large matrices:
-    // of three 64^3 fields (m = 1.5 M) with their graph blocks apart no column
-    // does, and the two empty launches a round cost 3% there (5.28 against
-    // 5.12 ms); of a 128^3 field (12.4 M) two or three a round do.
+    // of three 64^3 fields (m = 6.6 M, 1.5 M in the rounds) no column does, and
+    // the two empty launches a round cost 3% there (5.28 against 5.12 ms); of a
+    // 128^3 field (m = 54 M) two or three a round do.
     int32_t *solve_mem = nullptr;
-    if (m > (1 << 22) && tn.solve > 0 && !S.base) {
+    if (m > (1 << 23) && tn.solve > 0 && !S.base) {
         solve_mem = (int32_t *)S.get(B_SOLVE, kSolveMemBytes);
         if (!solve_mem) return set_err(c, PMS_ERR_OOM, "scratch allocation failed");
     }

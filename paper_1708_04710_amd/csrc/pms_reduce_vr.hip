@@ -441,14 +441,16 @@ __global__ void __launch_bounds__(kBlock) k_vr_cand(VeView v, DualState s, const
 }
 
 // Claims into columns (an edge's key by its table, a triangle's is its
-// column), births marked, deaths and essentials counted per tile.
+// column), births marked, deaths and essentials counted per tile.  Most births
+// lie in the tile of their death: those are counted in registers (an atomic
+// each: 28 M columns of 512 clouds 220 us, now 75; 100 points 25 and 6).
 __global__ void __launch_bounds__(kBlock) k_vr_count(int32_t *low_star, int64_t m, const int8_t *dim,
                                                      const int32_t *face_col, uint32_t *bits, int32_t *tile_d,
                                                      int32_t *tile_e)
 {
     const int64_t tiles = (m + kFinTile - 1) / kFinTile;
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-        int32_t nd = 0;
+        int32_t nd = 0, nb = 0;  // deaths; births among this tile's columns
 #pragma unroll
         for (int u = 0; u < kFinTile / kBlock; u++) {
             const int64_t j = tile * kFinTile + u * kBlock + threadIdx.x;
@@ -462,12 +464,13 @@ __global__ void __launch_bounds__(kBlock) k_vr_count(int32_t *low_star, int64_t 
             }
             nd++;
             atomicOr(&bits[x >> 5], 1u << (x & 31));
-            atomicSub(&tile_e[x / kFinTile], 1);
+            if (x / kFinTile == tile) nb++;
+            else atomicSub(&tile_e[x / kFinTile], 1);
         }
-        const int64_t t = block_sum64(nd);
+        const int64_t t = block_sum64((int64_t)nd | (int64_t)nb << 32);
         if (threadIdx.x == 0) {
             tile_d[tile] = (int32_t)t;
-            atomicAdd(&tile_e[tile], (int32_t)(min((int64_t)kFinTile, m - tile * kFinTile) - t));
+            atomicAdd(&tile_e[tile], (int32_t)(min((int64_t)kFinTile, m - tile * kFinTile) - (t & 0xFFFFFFFF) - (t >> 32)));
         }
     }
 }

@@ -1,5 +1,5 @@
 """The sweep kernel's larger sizes (columns that overfill its list in LDS, in
-matrices of more than 2^22 columns) against the oracle, at list lengths of each
+matrices of more than 2^23 columns) against the oracle, at list lengths of each
 size and beyond the last, and the capped walks of a round that hands over more
 columns than the sweeps take."""
 import numpy as np
@@ -15,13 +15,13 @@ pytestmark = pytest.mark.gpu
 
 def _touches(base, pivots, entries, seed):
     """`pivots` pivots of `entries` entries each among `base` rows, and three
-    columns whose chains add them all; empty columns up to 2^22 + 1."""
+    columns whose chains add them all; empty columns up to 2^23 + 1."""
     rng = np.random.default_rng(seed)
     tail = [sorted(rng.choice(base, entries, replace=False).tolist()) + [base + a] for a in range(pivots)]
     seen = np.unique(np.concatenate([np.asarray(t[:-1]) for t in tail])).size + pivots
     for x in (3, 7, 11):
         tail.append([x] + [base + a for a in range(pivots)])
-    cols = [[] for _ in range((1 << 22) + 1)]
+    cols = [[] for _ in range((1 << 23) + 1)]
     return *_csc(cols + tail), seen
 
 

@@ -43,3 +43,11 @@ def test_clouds_that_are_views(gpu):
     assert all(torch.equal(a[k], b[k]) for k in a)
     with pytest.raises((RuntimeError, ValueError)):
         api.build_vr([wide, wide.cpu()], thr[:2], 2)
+
+
+@pytest.mark.parametrize("edges", [1023, 1024, 1025, 2048, 2049, 4095, 4096, 4097, 8191, 8192, 8193, 16383, 16384, 16385])
+def test_edges_around_a_sort(gpu, edges):
+    """One, two, four, eight and sixteen keys a thread, and the device-wide sort."""
+    p = np.random.default_rng(edges).integers(0, 1 << 14, (190, 4)).astype(np.int32)
+    d = ((p[:, None].astype(np.int64) - p[None]) ** 2).sum(2)[np.triu_indices(190, 1)]
+    _same_as_oracle([p], [int(np.sort(d)[edges - 1])], 1, gpu)
