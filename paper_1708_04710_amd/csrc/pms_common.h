@@ -438,6 +438,15 @@ __device__ inline T block_seg_scan(T *a, int64_t n, T ident, Op op)
     return carry;
 }
 
+// Orders one wavefront's LDS operations (they are performed in issue order)
+// without waiting for its loads from memory.
+__device__ inline void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Block-wide exclusive max-scan of I4 (identity -1); *total = block max.
 template <int kThreads = kBlock>
 __device__ inline I4 block_excl_max4(I4 v, I4 *total)

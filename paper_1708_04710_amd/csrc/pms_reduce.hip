@@ -1181,13 +1181,6 @@ constexpr int kChainWaves = 4;
 constexpr int kCapW = 1520;  // LDS entries per working buffer (two per wave); two blocks fit a CU
 constexpr int kCapS = 512;   // LDS entries for the pivot column
 
-__device__ inline void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ inline int32_t lower_bound_i32(const int32_t *a, int32_t n, int32_t x)
 {
     int32_t lo = 0, hi = n;
