@@ -185,10 +185,7 @@ __global__ void __launch_bounds__(kBlock) k_graph_apply(Dev d, int32_t top, int 
             const int32_t e = (int32_t)(x >> 32);
             d.piv[j] = e;
             d.low_star[e] = (int32_t)j;
-            if (compression) {
-                d.prec[e].k = -1;
-                atomicOr(&d.neg[e >> 5], 1u << (e & 31));
-            }
+            if (compression) atomicOr(&d.neg[e >> 5], 1u << (e & 31));
         } else if (dj == top && gt) {
             const unsigned long long x = d.T[j];
             if (x == kGraphEmpty) continue;
@@ -325,10 +322,7 @@ __global__ void __launch_bounds__(kBlock) k_dual_apply(Dev d, int32_t b, int ok,
         d.piv[i] = (int32_t)j;
         d.state[i] = ST_ZERO;
         d.len[i] = 0;
-        if (compression) {
-            d.prec[j].k = -1;
-            atomicOr(&d.neg[j >> 5], 1u << (j & 31));
-        }
+        if (compression) atomicOr(&d.neg[j >> 5], 1u << (j & 31));
     }
 }
 
@@ -346,29 +340,93 @@ __device__ inline int32_t mix_solved(const Dev &d, int32_t top, int do_top, int3
     return dual | (bad & kNotGraph0 ? 0 : 2) | (do_top && !(bad & kNotGraphTop) ? 1 << top : 0);
 }
 
+// A column of an unsolved block whose low, its known-negative rows dropped, is
+// its beta: no other column has that low further left, so it is a pivot as it
+// is.  (Only where the block below is solved: the row's own column is then not
+// in the list, and need not be cleared.)
+__device__ inline bool mix_pivot(const Dev &d, int64_t j, int32_t solved)
+{
+    const int dj = d.dim[j];
+    return (dj == 1 || ((solved >> (dj - 1)) & 1)) && d.low[j] >= 0 && d.low[j] == d.beta[j];
+}
+
+// Before the first round, in tiles of kMixTile: the records of the rows of the
+// unsolved blocks (only those are ever looked up: a 128^3 field's 54 M rows
+// have 15 M of them, and 32 bytes each are most of what k_init writes); the
+// lows of their columns; and the number of those that go into the rounds.
+// The columns that are pivots as they are (11.3 of 12.4 M of that field) are
+// made pivots by k_mix_compact instead of passing through the first round,
+// whose five kernels took 2.3 ms.
+constexpr int kMixPer = 4, kMixTile = kMixPer * kBlock;
 __global__ void __launch_bounds__(kBlock) k_mix_count(Dev d, int32_t *keep_cnt, int32_t top, int do_top, int32_t dual)
 {
     const int32_t solved = mix_solved(d, top, do_top, dual);
-    const int64_t tiles = (d.m + kBlock - 1) / kBlock;
+    const int64_t tiles = (d.m + kMixTile - 1) / kMixTile;
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-        const int64_t j = tile * kBlock + threadIdx.x;
-        int32_t tk;
-        block_excl_sum32(j < d.m && mix_keep(d, j, solved) ? 1 : 0, &tk);
-        if (threadIdx.x == 0) keep_cnt[tile] = tk;
+        int32_t n = 0;
+        for (int u = 0; u < kMixPer; u++) {
+            const int64_t j = tile * kMixTile + u * kBlock + threadIdx.x;
+            if (j >= d.m) continue;
+            const int dj = d.dim[j];
+            if (dj < top && !((solved >> (dj + 1)) & 1)) {
+                int4 *pr = reinterpret_cast<int4 *>(&d.prec[j]);
+                pr[0] = make_int4(-1, is_neg(d.neg, (int32_t)j) ? -1 : 0, 0, 0);
+                pr[1] = make_int4(0, 0, 0, 0);
+            }
+            if (!mix_keep(d, j, solved)) continue;
+            int32_t low = d.low[j];
+            if (low >= 0 && is_neg(d.neg, low)) {
+                const int32_t *c = d.rows + d.col_ptr[j];
+                int32_t k = d.len[j] - 1;
+                while (k > 0 && is_neg(d.neg, c[k - 1])) k--;
+                low = k > 0 ? c[k - 1] : -1;
+                d.len[j] = k;
+                d.low[j] = low;
+                if (k == 0) d.state[j] = ST_ZERO;
+            }
+            n += low >= 0 && !mix_pivot(d, j, solved);
+        }
+        const int64_t t = block_sum64(n);
+        if (threadIdx.x == 0) keep_cnt[tile] = (int32_t)t;
     }
 }
 
 __global__ void __launch_bounds__(kBlock) k_mix_compact(Dev d, const int32_t *keep_off, int32_t *act, int32_t top,
-                                                        int do_top, int32_t dual)
+                                                        int do_top, int32_t dual, int compression)
 {
     const int32_t solved = mix_solved(d, top, do_top, dual);
-    const int64_t tiles = (d.m + kBlock - 1) / kBlock;
+    const int64_t tiles = (d.m + kMixTile - 1) / kMixTile;
+    int64_t np = 0, pb = 0;
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-        const int64_t j = tile * kBlock + threadIdx.x;
-        const int keep = j < d.m && mix_keep(d, j, solved);
-        int32_t tot;
-        const int32_t pos = block_excl_sum32(keep, &tot);
-        if (keep) act[keep_off[tile] + pos] = (int32_t)j;
+        int32_t at = keep_off[tile];
+        for (int u = 0; u < kMixPer; u++) {
+            const int64_t j = tile * kMixTile + u * kBlock + threadIdx.x;
+            bool keep = j < d.m && mix_keep(d, j, solved);
+            if (keep && mix_pivot(d, j, solved)) {
+                pb += make_pivot(d, (int32_t)j, d.low[j], compression);  // (known negative already, by its beta)
+                np++;
+                keep = false;
+            }
+            int32_t tot;
+            const int32_t pos = at + block_excl_sum32(keep ? 1 : 0, &tot);
+            if (keep) act[pos] = (int32_t)j;
+            at += tot;
+        }
+    }
+    const int64_t t = block_sum64(np), tb = block_sum64(pb);
+    if (threadIdx.x == 0) {
+        stat_add(d, S_NEWPIV, (unsigned long long)t, blockIdx.x);
+        stat_add(d, S_PBYTES, (unsigned long long)tb, blockIdx.x);
+    }
+}
+
+// The records of all rows, when no block is solved apart after all.
+__global__ void __launch_bounds__(kBlock) k_all_records(Dev d)
+{
+    for (int64_t j = blockIdx.x * (int64_t)kBlock + threadIdx.x; j < d.m; j += (int64_t)gridDim.x * kBlock) {
+        int4 *pr = reinterpret_cast<int4 *>(&d.prec[j]);
+        pr[0] = make_int4(-1, is_neg(d.neg, (int32_t)j) ? -1 : 0, 0, 0);
+        pr[1] = make_int4(0, 0, 0, 0);
     }
 }
 

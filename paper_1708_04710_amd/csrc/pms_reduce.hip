@@ -316,7 +316,8 @@ __global__ void k_iota(int32_t *p, int64_t n)
 // given = 1: left and beta come with the boundary (a builder made them), so
 // the atomics on left are skipped and beta's consequences (a known-negative
 // row's record, its bit in neg) are written here instead of in k_beta.
-__global__ void k_init(Dev d, int64_t nnz, int validate, int given, int compression)
+// records = 0: the rows' records are written later (k_mix_count).
+__global__ void k_init(Dev d, int64_t nnz, int validate, int given, int compression, int records)
 {
     int top = 0;
     const int lane = threadIdx.x & (kWave - 1);
@@ -373,9 +374,11 @@ __global__ void k_init(Dev d, int64_t nnz, int validate, int given, int compress
         d.state[j] = n ? ST_ACTIVE : ST_ZERO;
         // row j: no pivot, not known negative (the whole 32-byte record, so
         // the stores fill whole memory sectors)
-        int4 *pr = reinterpret_cast<int4 *>(&d.prec[j]);
-        pr[0] = make_int4(-1, negb ? -1 : 0, 0, 0);  // with beta given: known negative rows marked here
-        pr[1] = make_int4(0, 0, 0, 0);
+        if (records) {
+            int4 *pr = reinterpret_cast<int4 *>(&d.prec[j]);
+            pr[0] = make_int4(-1, negb ? -1 : 0, 0, 0);  // with beta given: known negative rows marked here
+            pr[1] = make_int4(0, 0, 0, 0);
+        }
         if (d.dim && d.dim[j] > top) top = d.dim[j];
     }
     if (d.dim) {
@@ -388,7 +391,7 @@ __global__ void k_init(Dev d, int64_t nnz, int validate, int given, int compress
 
 // beta_j = max{i : left(i) = j} (Def. "beta"); beta_j >= 0 marks column j as
 // negative (Thm. "Properties of beta_j" P.3), so its row can be compressed.
-__global__ void k_beta(Dev d, int compression)
+__global__ void k_beta(Dev d, int compression, int records)
 {
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < d.m; j += (int64_t)gridDim.x * blockDim.x) {
         const int64_t s = d.col_ptr[j];
@@ -398,7 +401,7 @@ __global__ void k_beta(Dev d, int compression)
             if (d.left[r] == (int32_t)j) { b = r; break; }  // rows ascending: first hit from the end is the max
         }
         d.beta[j] = b;
-        if (compression && b >= 0) d.prec[j].k = -1;  // a negative row never gets a pivot record
+        if (compression && records && b >= 0) d.prec[j].k = -1;  // a negative row never gets a pivot record
         if (compression) mark_neg(d.neg, j, b >= 0);
     }
 }
@@ -3133,20 +3136,23 @@ __global__ void k_defrag(Dev d, int32_t *dst, unsigned long long *dst_top)
 }
 
 // ---------------------------------------------------------------- finalize
+// In tiles of kFinTile columns (one scan of 52 K tiles' counts by one workgroup
+// takes 50 us at 128^3; of 256 columns each it took 187).
+constexpr int kFinPer = 4, kFinTile = kFinPer * kBlock;
 __global__ void __launch_bounds__(kBlock) k_fin_count(Dev d, int32_t *cnt_pairs, int32_t *cnt_ess)
 {
-    const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    int dp = 0, de = 0;
-    if (j < d.m) {
-        dp = d.low_star[j] >= 0;
-        de = d.low_star[j] < 0 && d.piv[j] < 0;
+    int64_t n = 0;  // pairs, essentials << 32
+#pragma unroll
+    for (int u = 0; u < kFinPer; u++) {
+        const int64_t j = (int64_t)blockIdx.x * kFinTile + u * kBlock + threadIdx.x;
+        if (j >= d.m) continue;
+        const bool dp = d.low_star[j] >= 0, de = !dp && d.piv[j] < 0;
+        n += (dp ? 1ll : 0ll) + (de ? 1ll << 32 : 0ll);
     }
-    int32_t tp, te;
-    block_excl_sum32(dp, &tp);
-    block_excl_sum32(de, &te);
+    n = block_sum64(n);
     if (threadIdx.x == 0) {
-        cnt_pairs[blockIdx.x] = tp;
-        cnt_ess[blockIdx.x] = te;
+        cnt_pairs[blockIdx.x] = (int32_t)n;
+        cnt_ess[blockIdx.x] = (int32_t)(n >> 32);
     }
 }
 
@@ -3155,22 +3161,28 @@ __global__ void __launch_bounds__(kBlock) k_fin_scatter(Dev d, const int32_t *of
                                                         int64_t cap_ess)
 {
     if ((birth && d.cnt->n_pairs > cap_pairs) || (ess && d.cnt->n_ess > cap_ess)) return;  // the host refuses
-    const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    int dp = 0, de = 0;
-    int32_t ls = -1;
-    if (j < d.m) {
-        ls = d.low_star[j];
-        dp = ls >= 0;
-        de = ls < 0 && d.piv[j] < 0;
+    int32_t op = off_pairs[blockIdx.x], oe = off_ess[blockIdx.x];
+    int32_t ls[kFinPer], pv[kFinPer];
+#pragma unroll
+    for (int u = 0; u < kFinPer; u++) {
+        const int64_t j = (int64_t)blockIdx.x * kFinTile + u * kBlock + threadIdx.x;
+        ls[u] = j < d.m ? d.low_star[j] : -1;
+        pv[u] = j < d.m ? d.piv[j] : 0;
     }
-    int32_t tp, te;
-    const int32_t pp = block_excl_sum32(dp, &tp);
-    const int32_t pe = block_excl_sum32(de, &te);
-    if (dp && birth) {
-        birth[off_pairs[blockIdx.x] + pp] = ls;
-        death[off_pairs[blockIdx.x] + pp] = (int32_t)j;
+#pragma unroll
+    for (int u = 0; u < kFinPer; u++) {
+        const int64_t j = (int64_t)blockIdx.x * kFinTile + u * kBlock + threadIdx.x;
+        const int dp = ls[u] >= 0, de = ls[u] < 0 && pv[u] < 0;
+        int32_t tot;  // both sums in one scan: at most kBlock each
+        const int32_t pre = block_excl_sum32(dp | de << 16, &tot);
+        if (dp && birth) {
+            birth[op + (pre & 0xFFFF)] = ls[u];
+            death[op + (pre & 0xFFFF)] = (int32_t)j;
+        }
+        if (de && ess) ess[oe + (pre >> 16)] = (int32_t)j;
+        op += tot & 0xFFFF;
+        oe += tot >> 16;
     }
-    if (de && ess) ess[off_ess[blockIdx.x] + pe] = (int32_t)j;
 }
 
 // Partition bump pointers after (re)allocation: partition p starts at
@@ -3520,6 +3532,9 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     hipStream_t st = c->stream;
     const unsigned gm = grid_for(m, kBlock, 65536);
     const double dm = (double)m, dz = (double)nnz;
+    // blocks solved apart from the rounds, which then hold the columns of the others
+    const bool blocks = bnd->dim && blocks_ok(c, *opt) && d.arena_cap * sizeof(int32_t) >= (size_t)m * 8;
+    const int records = blocks ? 0 : 1;
     // left, piv, low*, T, the active list; the negative bitmask
     PMS_LAUNCH(c, K_FILL, (given_lb ? 20 : 24) * dm + 4.0 * nwords, k_setup, gm, kBlock, d, act0, (int64_t)nwords,
                (int64_t)S_NUM * kStripe * 16, given_lb ? 0 : 1);
@@ -3527,15 +3542,15 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     // + the 32-byte record of every row (no pivot, not known negative); with
     // left and beta given, no left updates (rows read only to check them) but beta read
     if (given_lb)
-        PMS_LAUNCH(c, K_INIT, 8 * dm + (opt->validate ? 4 * dz + (bnd->dim ? dm + dz : 0) : 4 * dm) + 25 * dm + 32 * dm +
+        PMS_LAUNCH(c, K_INIT, 8 * dm + (opt->validate ? 4 * dz + (bnd->dim ? dm + dz : 0) : 4 * dm) + 25 * dm + 32 * dm * records +
                                   4 * dm + dm / 8,
-                   k_init, gm, kBlock, d, nnz, opt->validate, 1, opt->compression);
+                   k_init, gm, kBlock, d, nnz, opt->validate, 1, opt->compression, records);
     else
-        PMS_LAUNCH(c, K_INIT, 8 * dm + 8 * dz + (bnd->dim ? dm + dz : 0) + 25 * dm + 32 * dm, k_init, gm, kBlock, d,
-                   nnz, opt->validate, 0, opt->compression);
+        PMS_LAUNCH(c, K_INIT, 8 * dm + 8 * dz + (bnd->dim ? dm + dz : 0) + 25 * dm + 32 * dm * records, k_init, gm, kBlock, d,
+                   nnz, opt->validate, 0, opt->compression, records);
     // col_ptr, len, rows, left, beta out, neg bits
     if (!given_lb)
-        PMS_LAUNCH(c, K_BETA, 12 * dm + 8 * dz + 4 * dm + dm / 8, k_beta, gm, kBlock, d, opt->compression);
+        PMS_LAUNCH(c, K_BETA, 12 * dm + 8 * dz + 4 * dm + dm / 8, k_beta, gm, kBlock, d, opt->compression, records);
     // priority with a budget: the key histogram (and threshold) and, for
     // priority 1, the sizes of the sets N per low
     const bool budget = opt->round_budget > 0;
@@ -3576,8 +3591,6 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     }
     const char *tr_env = getenv("PMS_TRACE");
     const int trace = tr_env && tr_env[0] == '1';
-    // blocks solved apart from the rounds, which then hold the columns of the others
-    const bool blocks = bnd->dim && blocks_ok(c, *opt) && d.arena_cap * sizeof(int32_t) >= (size_t)m * 8;
     if (blocks) PMS_LAUNCH(c, K_GRAPH, dm, k_dim_count, grid_for(m, kBlock, 1024), kBlock, d);
     PMS_HIP(hipGetLastError());
 
@@ -3914,13 +3927,17 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
         }
         block_rounds = 1 + dual_r;
         block_active = dual_active;
-        PMS_LAUNCH(c, K_COMPACT, 2 * dm, k_mix_count, gm, kBlock, d, keep, top, do_top, dual);
-        PMS_LAUNCH(c, K_SCAN, 8.0 * nblk, k_scan_sum, 1, kScanThreads, keep, nblk, nullptr, &d.cnt->n_next);
-        PMS_LAUNCH(c, K_COMPACT, 2 * dm, k_mix_compact, gm, kBlock, d, keep, act0, top, do_top, dual);
+        const int64_t mt = (m + kMixTile - 1) / kMixTile;
+        const unsigned gx = grid_for(m, kMixTile, 65536);
+        PMS_LAUNCH(c, K_COMPACT, 14 * dm, k_mix_count, gx, kBlock, d, keep, top, do_top, dual);
+        PMS_LAUNCH(c, K_SCAN, 8.0 * mt, k_scan_sum, 1, kScanThreads, keep, mt, nullptr, &d.cnt->n_next);
+        PMS_LAUNCH(c, K_COMPACT, 10 * dm, k_mix_compact, gx, kBlock, d, keep, act0, top, do_top, dual, opt->compression);
         PMS_LAUNCH(c, K_FILL, 0, k_mix_start, 1, kWave, d, top, do_top, dual, h);
         PMS_HIP(hipGetLastError());
         PMS_HIP(hipStreamSynchronize(st));
         nA = h->n_cur;
+    } else if (blocks) {
+        PMS_LAUNCH(c, K_FILL, 32 * dm, k_all_records, gm, kBlock, d);
     }
     for (;;) {
     if (graph_k > 0 && nA > 0) {
@@ -4160,11 +4177,12 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     int32_t *cp = keep, *ce = keep2;
     const bool want_pairs = res->pair_birth && res->pair_death;
     const bool want_ess = res->essential != nullptr;
-    PMS_LAUNCH(c, K_FINAL, 8 * dm, k_fin_count, (unsigned)nblk, kBlock, d, cp, ce);
-    PMS_LAUNCH(c, K_SCAN, 16.0 * nblk, k_scan_sum2, 2, kScanThreads, cp, ce, nblk, &d.cnt->n_pairs, &d.cnt->n_ess);
+    const int64_t ft = (m + kFinTile - 1) / kFinTile;
+    PMS_LAUNCH(c, K_FINAL, 8 * dm, k_fin_count, (unsigned)ft, kBlock, d, cp, ce);
+    PMS_LAUNCH(c, K_SCAN, 16.0 * ft, k_scan_sum2, 2, kScanThreads, cp, ce, ft, &d.cnt->n_pairs, &d.cnt->n_ess);
     size_t fin_slot = 0;
     if (want_pairs || want_ess) {
-        PMS_LAUNCH(c, K_FINAL, -1.0, k_fin_scatter, (unsigned)nblk, kBlock, d, cp, ce,
+        PMS_LAUNCH(c, K_FINAL, -1.0, k_fin_scatter, (unsigned)ft, kBlock, d, cp, ce,
                    want_pairs ? res->pair_birth : nullptr, want_pairs ? res->pair_death : nullptr, res->cap_pairs,
                    res->essential, res->cap_essential);
         fin_slot = c->pend.size() - 1;
