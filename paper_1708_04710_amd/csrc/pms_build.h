@@ -25,8 +25,10 @@ struct Filtration {
     int32_t *verts = nullptr;    // [4m] ascending vertex ids, -1 padded
     int32_t *left = nullptr;     // [m] Def. "left" (2^31 - 1: no column holds the row), when has_left_beta
     int32_t *beta = nullptr;     // [m] Def. "beta" (-1: none), when has_left_beta
+    int32_t *second = nullptr;   // [m] the other coface of the faces of the top simplices (2^31 - 1: none), when has_second
     int value_is_f32 = 1;
     int has_left_beta = 0;       // the builder wrote left and beta
+    int has_second = 0;          // the builder wrote second: no such face has more than two cofaces
     Buf vr[VR_NUM];              // valid while vr_count > 0
     int32_t vr_count = 0;        // clouds, when built by edge order (else 0)
     int32_t vr_maxdim = 0;

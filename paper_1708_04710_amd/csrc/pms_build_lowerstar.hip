@@ -480,10 +480,11 @@ constexpr int kLeftPer = (kLeftPlane + kBlock - 1) / kBlock;
 
 // The smallest staged index among the cofaces of (v0 + vl, s), kN >= the
 // shape's coface count (a vertex has 14, an edge at most 6, a triangle 2);
-// the LDS reads are issued together.
+// *second: the largest of two and more (2^31 - 1: fewer).  The LDS reads are
+// issued together.
 template <int kN>
 __device__ inline int32_t ls_first_coface(const ShapeTab &t, int s, int vl, int back, int fwd,
-                                          const int32_t (*seg)[(kLeftV + 1) * kLeftRow])
+                                          const int32_t (*seg)[(kLeftV + 1) * kLeftRow], int32_t *second)
 {
     const int nc = t.ncof[s];
     int32_t got[kN];
@@ -496,16 +497,20 @@ __device__ inline int32_t ls_first_coface(const ShapeTab &t, int s, int vl, int 
         ok[c] = c < nc && !(e & ~back) && !(t.ext[sp] & ~e & ~fwd);
         got[c] = seg[(e >> 1) & 3][(vl + 1 - (e & 1)) * kLeftRow + sp];
     }
-    int32_t best = 0x7FFFFFFF;
+    int32_t best = 0x7FFFFFFF, last = -1;
 #pragma unroll
     for (int c = 0; c < kN; c++)
-        if (ok[c]) best = min(best, got[c]);
+        if (ok[c]) {
+            best = min(best, got[c]);
+            last = max(last, got[c]);
+        }
+    *second = last > best ? last : 0x7FFFFFFF;  // (best stays 2^31 - 1 without a coface)
     return best;
 }
 
 __global__ void __launch_bounds__(kBlock) k_ls_left(ShapeTab t, int64_t nv, int64_t m,
                                                     const int32_t *__restrict__ idx_tab, int32_t *left,
-                                                    const int32_t *__restrict__ err)
+                                                    int32_t *second, int face_dim, const int32_t *__restrict__ err)
 {
     if (err[0] || err[1]) return;
     static_assert(kLeftV == 64 && kBlock % kLeftV == 0, "one shape per wavefront");
@@ -550,14 +555,17 @@ __global__ void __launch_bounds__(kBlock) k_ls_left(ShapeTab t, int64_t nv, int6
             const int bits = nb[vl], back = bits & 7, fwd = bits >> 3;
             if (v0 + vl >= nv || (t.ext[s] & ~fwd)) continue;  // past the end, or the shape leaves the grid
             const int32_t p = seg[0][(vl + 1) * kLeftRow + s];
-            int32_t best = 0x7FFFFFFF;
+            int32_t best = 0x7FFFFFFF, other = 0x7FFFFFFF;
             switch (t.dim[s]) {
-            case 0: best = ls_first_coface<14>(t, s, vl, back, fwd, seg); break;
-            case 1: best = ls_first_coface<6>(t, s, vl, back, fwd, seg); break;
-            case 2: best = ls_first_coface<2>(t, s, vl, back, fwd, seg); break;
+            case 0: best = ls_first_coface<14>(t, s, vl, back, fwd, seg, &other); break;
+            case 1: best = ls_first_coface<6>(t, s, vl, back, fwd, seg, &other); break;
+            case 2: best = ls_first_coface<2>(t, s, vl, back, fwd, seg, &other); break;
             default: break;
             }
-            if ((uint64_t)(uint32_t)p < (uint64_t)m) left[p] = best;
+            if ((uint64_t)(uint32_t)p < (uint64_t)m) {
+                left[p] = best;
+                if (t.dim[s] == face_dim) second[p] = other;
+            }
         }
         __syncthreads();
     }
@@ -773,10 +781,12 @@ pms_status build_lowerstar(Ctx *c, const float *grid, int32_t nx, int32_t ny, in
         PMS_LAUNCH(c, K_LS_INDEX, 24.0 * nv + 45.0 * m, k_ls_emit<32>, (unsigned)vtiles, kBlock, t, ct, vkey, vid, mask,
                    (int32_t)nv, m, tsum, idx, (int32_t *)code, f->dim, (float *)f->value, f->crit, f->verts, f->col_ptr,
                    err);
+    // the dimension of the top simplices' faces: at most two cofaces each
+    const int face_dim = (nx > 1) + (ny > 1) + (nz > 1) - 1;
     auto rest = [&](const uint32_t *cd) {
         // the simplex's and its cofaces' table entries, left out
         PMS_LAUNCH(c, K_LS_LEFT, 4.0 * m + 4.0 * nnz + 4.0 * m, k_ls_left, grid_for(nv, kLeftV, 65536), kBlock, t, nv, m,
-                   idx, f->left, err);
+                   idx, f->left, f->second, face_dim, err);
         // + the facets' left, beta out
         PMS_LAUNCH(c, K_LS_ROWS, 12.0 * m + 4.0 * nnz + 4.0 * nnz + 4.0 * nnz + 4.0 * m, k_ls_rows, (unsigned)tiles,
                    kBlock, t, (const int32_t *)cd, m, nnz, idx, f->col_ptr, f->rows, f->left, f->beta, err);
@@ -808,7 +818,7 @@ pms_status build_lowerstar(Ctx *c, const float *grid, int32_t nx, int32_t ny, in
         PMS_HIP(hipMemcpyAsync(herr, err, 8, hipMemcpyDeviceToHost, s));
         PMS_HIP(hipStreamSynchronize(s));
     }
-    f->has_left_beta = 1;
+    f->has_left_beta = f->has_second = 1;
     if (c->prof_on) prof_flush(c);
     if (herr[0] == 1) return set_err(c, PMS_ERR_INVALID_ARG, "grid holds NaN");
     if (herr[0]) return set_err(c, PMS_ERR_HIP, "internal: simplex count mismatch in the lower-star builder");

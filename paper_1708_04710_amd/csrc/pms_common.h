@@ -86,6 +86,7 @@ struct Ctx {
     // the batch instances of the reduction in progress (device column
     // offsets, n_inst + 1 entries; null: one complex)
     const int64_t *inst_off = nullptr;
+    const int32_t *second = nullptr;  // the second cofaces of the filtration being reduced (during the call)
     int32_t n_inst = 1;
     // profiler
     bool prof_on = false;

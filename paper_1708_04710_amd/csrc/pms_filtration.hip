@@ -19,7 +19,8 @@ static void filtration_release(Filtration *f)
     (void)hipFree(f->verts);
     (void)hipFree(f->left);
     (void)hipFree(f->beta);
-    f->left = f->beta = nullptr;
+    (void)hipFree(f->second);
+    f->left = f->beta = f->second = nullptr;
     f->col_ptr = nullptr;
     f->rows = nullptr;
     f->dim = nullptr;
@@ -98,7 +99,7 @@ pms_status filtration_reserve(Ctx *c, Filtration **pf, int64_t m, int64_t nnz, i
 {
     Filtration *f = filtration_get(c, pf);
     if (!f) return set_err(c, PMS_ERR_OOM, "filtration");
-    f->has_left_beta = 0;  // until a builder writes them
+    f->has_left_beta = f->has_second = 0;  // until a builder writes them
     f->vr_count = 0;
     if (f->cap_m >= m && f->cap_nnz >= nnz && f->device == c->device) return PMS_OK;
     (void)hipStreamSynchronize(c->stream);
@@ -113,6 +114,7 @@ pms_status filtration_reserve(Ctx *c, Filtration **pf, int64_t m, int64_t nnz, i
     PMS_HIP(hipMalloc(&f->verts, M * 16));
     PMS_HIP(hipMalloc(&f->left, M * 4));
     PMS_HIP(hipMalloc(&f->beta, M * 4));
+    PMS_HIP(hipMalloc(&f->second, M * 4));
     f->cap_m = M;
     f->cap_nnz = Z;
     (void)f32;

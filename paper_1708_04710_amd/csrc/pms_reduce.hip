@@ -178,6 +178,7 @@ struct Dev {
     unsigned long long *part;
     unsigned long long part_base, part_size;
     PivRec *prec;      // [m] pivot records by row
+    const int32_t *second;  // [m] the faces' second cofaces (Filtration::second), or null
     int32_t *cq;       // chain queue, kPart slices of cq_slice entries
     int32_t *cq_n;     // entries per slice, one cache line each: cq_n[p*32]; cq_n[kPart*32] = wq entries,
                        // cq_n[(kPart+1)*32] = wq2 entries, cq_n[(kPart+2)*32] = wq2 entries k_chain_solve
@@ -3464,6 +3465,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     d.state = (uint8_t *)S.get(B_STATE, m);
     // left and beta: the caller's when a builder gave them (read only), else computed in Phase 0
     const bool given_lb = bnd->left && bnd->beta;
+    d.second = given_lb ? c->second : nullptr;
     d.beta = given_lb ? const_cast<int32_t *>(bnd->beta) : (int32_t *)S.get(B_BETA, m * 4);
     d.left = given_lb ? const_cast<int32_t *>(bnd->left) : (int32_t *)S.get(B_LEFT, m * 4);
     d.piv = (int32_t *)S.get(B_PIV, m * 4);
@@ -3864,9 +3866,12 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
         PMS_LAUNCH(c, K_GRAPH, dm + 20.0 * d1, k_graph0_seed, gm, kBlock, d);
         PMS_LAUNCH(c, K_GRAPH, dm + 28.0 * d1, k_graph0_walk, gm, kBlock, d);
         if (do_top) {
-            unsigned long long *S2 = (unsigned long long *)d.arena;  // (no column has moved there yet)
-            PMS_LAUNCH(c, K_GRAPH, 8.0 * dm, k_fill_u64, gm, kBlock, S2, m, 0ull);
-            PMS_LAUNCH(c, K_GRAPH, dm + (12.0 + 12.0 * (top + 1)) * dt, k_cof_sum, gm, kBlock, d, S2, top);
+            unsigned long long *S2 = nullptr;
+            if (!d.second) {
+                S2 = (unsigned long long *)d.arena;  // (no column has moved there yet)
+                PMS_LAUNCH(c, K_GRAPH, 8.0 * dm, k_fill_u64, gm, kBlock, S2, m, 0ull);
+                PMS_LAUNCH(c, K_GRAPH, dm + (12.0 + 12.0 * (top + 1)) * dt, k_cof_sum, gm, kBlock, d, S2, top);
+            }
             PMS_LAUNCH(c, K_GRAPH, dm + 28.0 * df, k_graph_top_seed, gm, kBlock, d, S2, top);
             PMS_LAUNCH(c, K_GRAPH, dm + 28.0 * df, k_graph_top_walk, gm, kBlock, d, S2, top);
         }
@@ -4729,6 +4734,11 @@ pms_status pms_reduce_filtration(pms_ctx *c, const pms_filtration *fh, int32_t c
         const pms_status s = pms::reduce_vr(c, f, res, count, inst_col_off, inst_pair_off, inst_ess_off, pair_inst, &done);
         if (s != PMS_OK || done) return s;
     }
+    c->second = f->has_second ? f->second : nullptr;
+    struct Reset {
+        pms_ctx *c;
+        ~Reset() { c->second = nullptr; }
+    } reset{c};
     return inst_col_off ? pms_reduce_batched(c, count, inst_col_off, &bnd, opt, res, inst_pair_off, inst_ess_off, pair_inst)
                         : pms_reduce(c, &bnd, opt, res);
 }
