@@ -32,6 +32,7 @@
 #pragma once
 
 constexpr int32_t kNotGraph0 = 1, kNotGraphTop = 2;
+constexpr int kMixPer = 4, kMixTile = kMixPer * kBlock;
 
 // Columns per dimension (7: that dimension and above).
 __global__ void __launch_bounds__(kBlock) k_dim_count(Dev d)
@@ -80,10 +81,14 @@ __global__ void __launch_bounds__(kBlock) k_graph0_seed(Dev d)
     for (int64_t j = blockIdx.x * (int64_t)kBlock + threadIdx.x; j < d.m; j += (int64_t)gridDim.x * kBlock) {
         const int32_t b = d.beta[j];
         if (b >= 0) {
-            const int32_t *c = d.rows + d.col_ptr[j];
-            int32_t n = d.len[j];
-            while (n > 0 && is_neg(d.neg, c[n - 1])) n--;
-            nb += n > 0 && c[n - 1] == b;
+            int32_t low = d.low[j];  // the last row, still
+            if (low >= 0 && is_neg(d.neg, low)) {
+                const int32_t *c = d.rows + d.col_ptr[j];
+                int32_t n = d.len[j] - 1;
+                while (n > 0 && is_neg(d.neg, c[n - 1])) n--;
+                low = n > 0 ? c[n - 1] : -1;
+            }
+            nb += low == b;
         }
         if (d.dim[j] != 1) continue;
         int32_t u, v;
@@ -100,14 +105,18 @@ __global__ void __launch_bounds__(kBlock) k_graph0_seed(Dev d)
 
 // Block 0, the others: walked to their places, except the births of the
 // pairs (i, left(i)) with i the last row of its first coface (they are
-// positive: their columns reduce to zero).
+// positive: their columns reduce to zero).  (Every column's low is its last row
+// before the rounds: read from there instead of through len, col_ptr and rows
+// this kernel takes 0.90 ms instead of 1.00 at 128^3, the seeds of both blocks
+// 0.76 instead of 0.98; the top block's walk, bound by its atomics, is the
+// faster for the longer look-up, 2.05 against 2.2.)
 __global__ void __launch_bounds__(kBlock) k_graph0_walk(Dev d)
 {
     if (d.cnt->not_graph & kNotGraph0) return;
     for (int64_t j = blockIdx.x * (int64_t)kBlock + threadIdx.x; j < d.m; j += (int64_t)gridDim.x * kBlock) {
         if (d.dim[j] != 1) continue;
         const int32_t t = d.left[j];
-        if (t != 0x7FFFFFFF && last_row(d, t) == (int32_t)j) continue;
+        if (t != 0x7FFFFFFF && d.low[t] == (int32_t)j) continue;
         int32_t u, v;
         graph_edge(d, j, &u, &v);
         const int32_t hi = max(u, v);
@@ -155,7 +164,7 @@ __global__ void __launch_bounds__(kBlock) k_graph_top_seed(Dev d, const unsigned
             atomicOr(&d.cnt->not_graph, kNotGraphTop);
             continue;
         }
-        if (t0 != kGraphOut && last_row(d, t0) == (int32_t)i)
+        if (t0 != kGraphOut && d.low[t0] == (int32_t)i)
             d.T[t0] = ((unsigned long long)(0x7FFFFFFFu - (uint32_t)i) << 32) | (uint32_t)t1;
     }
 }
@@ -227,6 +236,35 @@ __global__ void __launch_bounds__(kBlock) k_cof_fill(Dev d, int32_t dims, int32_
         const int32_t n = d.len[j];
         const int64_t s = d.col_ptr[j];
         for (int32_t k = 0; k < n; k++) cof[atomicAdd(&end[d.rows[s + k]], 1)] = (int32_t)j;
+    }
+}
+
+// Exclusive sums of n counts in tiles of kMixTile: each tile's sum, (a scan of
+// the sums,) then every entry.  (One workgroup over all m counts of a 400-point
+// torus to dimension 2 took 277 us.)
+__global__ void __launch_bounds__(kBlock) k_tile_total(const int32_t *a, int64_t n, int32_t *tile)
+{
+    int32_t t = 0;
+#pragma unroll
+    for (int u = 0; u < kMixPer; u++) {
+        const int64_t j = (int64_t)blockIdx.x * kMixTile + u * kBlock + threadIdx.x;
+        t += j < n ? a[j] : 0;
+    }
+    const int64_t s = block_sum64(t);
+    if (threadIdx.x == 0) tile[blockIdx.x] = (int32_t)s;
+}
+
+__global__ void __launch_bounds__(kBlock) k_tile_sums32(int32_t *a, int64_t n, const int32_t *tile)
+{
+    int32_t at = tile[blockIdx.x];
+#pragma unroll
+    for (int u = 0; u < kMixPer; u++) {
+        const int64_t j = (int64_t)blockIdx.x * kMixTile + u * kBlock + threadIdx.x;
+        const int32_t x = j < n ? a[j] : 0;
+        int32_t tot;
+        const int32_t e = at + block_excl_sum32(x, &tot);
+        if (j < n) a[j] = e;
+        at += tot;
     }
 }
 
@@ -364,7 +402,6 @@ __device__ inline bool mix_pivot(const Dev &d, int64_t j, int32_t solved)
 // The columns that are pivots as they are (11.3 of 12.4 M of that field) are
 // made pivots by k_mix_compact instead of passing through the first round,
 // whose five kernels took 2.3 ms.
-constexpr int kMixPer = 4, kMixTile = kMixPer * kBlock;
 __global__ void __launch_bounds__(kBlock) k_mix_count(Dev d, int32_t *keep_cnt, int32_t top, int do_top, int32_t dual)
 {
     const int32_t solved = mix_solved(d, top, do_top, dual);

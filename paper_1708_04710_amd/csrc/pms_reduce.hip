@@ -3913,7 +3913,10 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
                 s.entries = &d.stats[(unsigned)S_XE * kStripe * 16];
                 PMS_LAUNCH(c, K_FILL, 4 * dm, k_fill_i32, gm, kBlock, ar + a_end, m + 1, 0);
                 PMS_LAUNCH(c, K_DUAL, dm + 8 * dz, k_cof_count, gm, kBlock, d, dual, ar + a_end);
-                PMS_LAUNCH(c, K_SCAN, 8 * dm, k_scan_sum, 1, kScanThreads, ar + a_end, m, nullptr, ar + a_end + m);
+                const int64_t mt = (m + kMixTile - 1) / kMixTile;
+                PMS_LAUNCH(c, K_SCAN, 4 * dm, k_tile_total, (unsigned)mt, kBlock, ar + a_end, m, keep);
+                PMS_LAUNCH(c, K_SCAN, 8.0 * mt, k_scan_sum, 1, kScanThreads, keep, mt, nullptr, ar + a_end + m);
+                PMS_LAUNCH(c, K_SCAN, 8 * dm, k_tile_sums32, (unsigned)mt, kBlock, ar + a_end, m, keep);
                 PMS_LAUNCH(c, K_DUAL, dm + 12 * dz, k_cof_fill, gm, kBlock, d, dual, ar + a_end, ar + a_cof);
                 for (int32_t b = 1; b < top; b++) {
                     if (!((dual >> (b + 1)) & 1)) continue;
