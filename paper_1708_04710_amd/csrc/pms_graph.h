@@ -108,8 +108,7 @@ __global__ void __launch_bounds__(kBlock) k_graph0_seed(Dev d)
 // positive: their columns reduce to zero).  (Every column's low is its last row
 // before the rounds: read from there instead of through len, col_ptr and rows
 // this kernel takes 0.90 ms instead of 1.00 at 128^3, the seeds of both blocks
-// 0.76 instead of 0.98; the top block's walk, bound by its atomics, is the
-// faster for the longer look-up, 2.05 against 2.2.)
+// 0.76 instead of 0.98; the top block's walk, 2.1 to 2.2, is bound by its atomics.)
 __global__ void __launch_bounds__(kBlock) k_graph0_walk(Dev d)
 {
     if (d.cnt->not_graph & kNotGraph0) return;
@@ -177,7 +176,7 @@ __global__ void __launch_bounds__(kBlock) k_graph_top_walk(Dev d, const unsigned
         if (d.dim[i] != top - 1 || d.beta[i] >= 0) continue;
         int32_t t0, t1;
         graph_face(d, S, i, &t0, &t1);
-        if (t0 == kGraphOut || last_row(d, t0) == (int32_t)i) continue;
+        if (t0 == kGraphOut || d.low[t0] == (int32_t)i) continue;
         graph_place<true>(d.T, 0x7FFFFFFFu - (uint32_t)i, t0, t1);
     }
 }
