@@ -385,7 +385,14 @@ def _slot(kernel_name):
             "k_fill_i32": "k_fill", "k_fill_u64": "k_fill", "k_iota": "k_fill", "k_part_init": "k_fill",
             "k_stats_fold": "k_fill", "k_scan_i64": "k_build_scan", "k_tile_sums": "k_build_scan",
             "k_tile_apply": "k_build_scan", "k_rs_count": "k_sort", "k_rs_offsets": "k_sort",
-            "k_rs_scatter": "k_sort", "k_setup": "k_fill", "k_round_end": "k_fill"}.get(name, name)
+            "k_rs_scatter": "k_sort", "k_setup": "k_fill", "k_round_end": "k_fill", "k_round_open": "k_pivots",
+            "k_round_close": "k_compact", "k_mix_count": "k_compact", "k_mix_compact": "k_compact",
+            "k_mix_start": "k_fill", "k_all_records": "k_fill", "k_dim_count": "k_graph", "k_graph0_seed": "k_graph",
+            "k_graph0_walk": "k_graph", "k_cof_sum": "k_graph", "k_graph_top_seed": "k_graph",
+            "k_graph_top_walk": "k_graph", "k_graph_apply": "k_graph", "k_vr_h0": "k_graph", "k_dual_claim": "k_dual",
+            "k_vr_cocycle": "k_dual", "k_vr_cand": "k_dual", "k_cof_fill": "k_dual", "k_dual_cand": "k_dual",
+            "k_dual_apply": "k_dual", "k_ls_vkeys": "k_ls_keys", "k_ls_rank": "k_ls_keys", "k_ls_masks": "k_ls_keys",
+            "k_ls_sums": "k_ls_index", "k_ls_emit": "k_ls_index"}.get(name, name)
 
 
 def rocprof_summary(tdir, fdir, wdir, out_md, bench_json=None):

@@ -198,8 +198,15 @@ typedef struct {
     /* host-visible outputs */
     int64_t n_pairs;
     int64_t n_essential;
+    /* With the default options and tuning, blocks of the matrix (rows of one
+     * dimension, columns of the next) that are graphs, or that have many more
+     * columns than rows, are reduced apart from the rounds (the lows of a
+     * reduced matrix are unique): the graphs count as one round and no
+     * additions, a block reduced from its rows by the rounds and additions that
+     * took (pivots and sums of rows' cofaces). */
     int32_t rounds;         /* outer iterations run (Sec. 4: one Phase I + Phase II) */
-    int32_t phase0_pivots;  /* pivots known from beta before any addition (Phase 0) */
+    int32_t phase0_pivots;  /* pivots known before any addition: from beta (Phase 0); in a
+                               filtration reduced from its rows, the apparent pairs */
     int64_t additions;      /* column additions performed (the paper's cost unit) */
     int64_t xor_entries;    /* entries read by those additions */
     int64_t active_sum;     /* sum over rounds of the round's active columns (the columns

@@ -3,14 +3,15 @@
 // tetrahedron is written straight to its place.
 //
 //   k_ve_edges   one workgroup per cloud: squared distances, threshold, the
-//                present edges sorted in LDS (bitonic, keys (value, a, b)), ranks
+//                present edges sorted by the workgroup (bitonic, keys (value, a, b)), ranks
 //                and tie groups; clouds with more than kLdsEdges edges are
 //                sorted by the device-wide radix sort instead (k_ve_keys, k_ve_ranks)
-//   k_ve_masks   one wavefront per edge: the third vertices whose two other
-//                edges come earlier (a ballot per 64 points), its apparent triangle
+//   k_ve_masks   one wavefront per edge (a ballot per 64 points), or k_ve_masks_lds
+//                one lane per edge: the third vertices whose two other edges come
+//                earlier, its apparent triangle
 //   k_ve_scan    one workgroup per cloud: prefix counts of the triangles
-//   k_ve_emit    one lane per edge: its index and column, the first index of each mask word
-//   k_ve_tris    one lane per triangle: its column
+//   k_ve_emit    one lane per edge: its index, the first index of each mask word
+//   k_ve_tris    one lane per triangle: its column; the vertices' and edges' columns
 //   k_ve_tmasks, k_ve_tets, k_ve_appt   the same for tetrahedra (dimension 3)
 //
 // The sorted build wrote and read every simplex's 64-bit key 8 to 10 times;

@@ -24,9 +24,10 @@
 //
 // What this replaces: on a smooth 64^3 field a tetrahedron's column adds up
 // to 11 758 pivots one after the other (each addition about 1 us in k_chain),
-// while the longest walk from the triangles' side is 78 nodes.  Measured:
-// build + reduce + backward of 64^3 fields 42.0 -> 4.8 ms, build + reduce of
-// 128^3 399 -> 41.9 ms, of 32^3 white noise 9.3 -> 3.9 ms.  The kernels here
+// while the longest walk from the triangles' side is 78 nodes.  Measured, by
+// these kernels alone: build + reduce + backward of 64^3 fields 42.0 -> 4.8 ms
+// (3.5 with what came after), build + reduce of 128^3 399 -> 41.9 ms (17.7), of
+// 32^3 white noise 9.3 -> 3.9 ms (3.1).  The kernels here
 // are bound by scattered 4- and 8-byte accesses (a node's word, a face's two
 // cofaces), not by the walks.
 #pragma once
