@@ -1047,8 +1047,12 @@ struct XorJob {
     int32_t tlen, slen, k, last;
 };
 
+// direct: columns that chain on go straight to the queue of the sweep and
+// wavefront kernels.  With few columns queued the lane passes would only hand
+// them on (their lows have pivots, and lanes take no steps then), and two
+// launches of 7 and 8 us a round are saved (32^3 noise: 3127 to 2782 us a pass).
 __global__ void __launch_bounds__(kBlock) k_xor(Dev d, const int32_t *act, int variant, int compression, int chain,
-                                                int tail)
+                                                int tail, int direct)
 {
     __shared__ int32_t s_x[kXorPiece + 2], s_y[kXorPiece + 2];
     __shared__ XorJob s_job[kXorJobs];
@@ -1163,9 +1167,12 @@ __global__ void __launch_bounds__(kBlock) k_xor(Dev d, const int32_t *act, int v
     int32_t npush;
     const int32_t qpos = block_excl_sum32(push ? 1 : 0, &npush);
     const unsigned qp = (unsigned)((tile * cols) / kBlock) & (kPart - 1);  // its slice takes whole tiles of kBlock
-    if (threadIdx.x == 0) s_q = npush ? atomicAdd(&d.cq_n[qp * 32], npush) : 0;
+    if (threadIdx.x == 0) s_q = npush ? atomicAdd(&d.cq_n[(direct ? (unsigned)kPart : qp) * 32], npush) : 0;
     __syncthreads();
-    if (push) d.cq[(int64_t)qp * d.cq_slice + s_q + qpos] = j;
+    if (push) {
+        if (direct) d.wq[s_q + qpos] = j;
+        else d.cq[(int64_t)qp * d.cq_slice + s_q + qpos] = j;
+    }
     const int64_t badds = block_sum64(adds);
     const int64_t bxe = block_sum64(xe);
     const int64_t bby = block_sum64(by);
@@ -3637,6 +3644,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     // The kernels read the round's active count and number from the device
     // (they loop over tiles), so `grid_tiles` only bounds their grids: the
     // exact tile count when the host knows it, a fixed size in a graph.
+    constexpr size_t kNoSlot = ~(size_t)0;  // not launched
     size_t xor_slot = 0, lane_slot = 0, wide_slot = 0, chain_slot = 0, solve_slot = 0, pivots_slot = 0;
     double pivots_base = 0;
     const pms_tuning tn = c->tune;
@@ -3708,22 +3716,28 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
             PMS_LAUNCH(c, K_BUDGET, 0, k_bud_apply, gT, kBlock, d, a, va, pr, bud_n, bud_h, keep2);
             if (pr == 1) PMS_LAUNCH(c, K_BUDGET, 0, k_bud_ncount, gA, kBlock, d, a, va, bud_n, -1);
         }
+        // the lane passes' step limit is tn.lane_steps_few below tn.lane_many queued columns, and dA bounds
+        // those (0 inside a captured graph); a caller's own settings keep the passes that they tune
+        const bool direct = tuning_builtin(tn) && tn.lane_steps_few == 0 && dA > 0 && dA < (double)tn.lane_many && !dbg;
         PMS_LAUNCH(c, K_XOR, -1.0, k_xor, std::max(gT, kXorBlocks), kBlock, d, a, opt->variant, opt->compression, opt->chain,
-                   opt->tail_active);
+                   opt->tail_active, direct ? 1 : 0);
         xor_slot = c->pend.size() - 1;
         if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
-        if (trace)
-            PMS_LAUNCH(c, K_CHAIN_LANE, -1.0, k_chain_lane<true>, g_lane, kLaneThreads, d, opt->compression, tn);
-        else
-            PMS_LAUNCH(c, K_CHAIN_LANE, -1.0, k_chain_lane<false>, g_lane, kLaneThreads, d, opt->compression, tn);
-        lane_slot = c->pend.size() - 1;
-        if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
-        if (trace)
-            PMS_LAUNCH(c, K_CHAIN_WIDE, -1.0, k_chain_wide<true>, g_wide, kWideThreads, d, opt->compression, tn);
-        else
-            PMS_LAUNCH(c, K_CHAIN_WIDE, -1.0, k_chain_wide<false>, g_wide, kWideThreads, d, opt->compression, tn);
-        wide_slot = c->pend.size() - 1;
-        if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
+        lane_slot = wide_slot = kNoSlot;
+        if (!direct) {
+            if (trace)
+                PMS_LAUNCH(c, K_CHAIN_LANE, -1.0, k_chain_lane<true>, g_lane, kLaneThreads, d, opt->compression, tn);
+            else
+                PMS_LAUNCH(c, K_CHAIN_LANE, -1.0, k_chain_lane<false>, g_lane, kLaneThreads, d, opt->compression, tn);
+            lane_slot = c->pend.size() - 1;
+            if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
+            if (trace)
+                PMS_LAUNCH(c, K_CHAIN_WIDE, -1.0, k_chain_wide<true>, g_wide, kWideThreads, d, opt->compression, tn);
+            else
+                PMS_LAUNCH(c, K_CHAIN_WIDE, -1.0, k_chain_wide<false>, g_wide, kWideThreads, d, opt->compression, tn);
+            wide_slot = c->pend.size() - 1;
+            if (dbg) PMS_LAUNCH(c, K_FILL, 0, k_dbg_writes, gm, kBlock, d);
+        }
         if (solve_max > 0) {  // few handed-over columns: by sweeps; what does not fit, serially
             if (trace)
                 PMS_LAUNCH(c, K_SOLVE, -1.0, (k_chain_solve<true, 0>), g_solve, SolveSize<0>::kThreads, d,
@@ -4110,9 +4124,9 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
             pivot_bytes_prev = h->pivot_bytes;
             c->pend[chain_slot].bytes = (double)(h->chain_bytes - chain_bytes_prev);
             chain_bytes_prev = h->chain_bytes;
-            c->pend[lane_slot].bytes = (double)(h->lane_bytes - lane_bytes_prev);
+            if (lane_slot != kNoSlot) c->pend[lane_slot].bytes = (double)(h->lane_bytes - lane_bytes_prev);
             lane_bytes_prev = h->lane_bytes;
-            c->pend[wide_slot].bytes = (double)(h->wide_bytes - wide_bytes_prev);
+            if (wide_slot != kNoSlot) c->pend[wide_slot].bytes = (double)(h->wide_bytes - wide_bytes_prev);
             wide_bytes_prev = h->wide_bytes;
             const unsigned long long abn[5] = {h->abytes_xor, h->abytes_lane, h->abytes_wide, h->abytes_chain,
                                                h->abytes_solve};
@@ -4123,7 +4137,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
                 solve_bytes_prev = h->solve_bytes;
             }
             for (int q = 0; q < nslots; q++) {
-                c->pend[slots[q]].abytes = (double)(abn[q] - ab_prev[q]);
+                if (slots[q] != kNoSlot) c->pend[slots[q]].abytes = (double)(abn[q] - ab_prev[q]);
                 ab_prev[q] = abn[q];
             }
             prof_flush(c);
