@@ -738,7 +738,9 @@ pms_status build_lowerstar(Ctx *c, const float *grid, int32_t nx, int32_t ny, in
     uint32_t *vkey = (uint32_t *)grow_scratch(c, B_BUILD0, nv * 16);  // the vertices' values and ids, twice
     ulonglong2 *mask = (ulonglong2 *)grow_scratch(c, B_BUILD1, nv * 16);
     int32_t *idx = (int32_t *)grow_scratch(c, B_BUILD2, nk * 4);
-    int64_t *tsum = (int64_t *)grow_scratch(c, B_BUILD3, (tiles + 1) * 8);  // (m >= nv)
+    // sums per tile of vertices, or (many vertices of one value) of simplices: a flat
+    // grid has 6 simplices a vertex, fewer tiles of kBlock than of 32 vertices
+    int64_t *tsum = (int64_t *)grow_scratch(c, B_BUILD3, (std::max(tiles, vtiles) + 1) * 8);
     int32_t *err = (int32_t *)grow_scratch(c, B_BUILD4, 64);
     uint32_t *code = (uint32_t *)grow_scratch(c, B_BUILD7, nk * 4);
     int32_t *rk = (int32_t *)grow_scratch(c, B_BUILD8, nv * 4);
