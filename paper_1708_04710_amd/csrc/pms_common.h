@@ -87,6 +87,7 @@ struct Ctx {
     // offsets, n_inst + 1 entries; null: one complex)
     const int64_t *inst_off = nullptr;
     const int32_t *second = nullptr;  // the second cofaces of the filtration being reduced (during the call)
+    bool builder = false;             // the matrix being reduced is a builder's (during the call)
     int32_t n_inst = 1;
     // profiler
     bool prof_on = false;

@@ -123,6 +123,8 @@ struct Counters {
     int32_t n_dim[8];    // columns of dimension 0..6, and of 7 or more (with dim)
     int32_t not_graph;   // kGraph0 / kGraphTop: that block has a node set larger than two
     int32_t beta_counted; // the pivots known from beta are counted (k_graph0_seed)
+    int32_t unfit;       // the matrix is not what solving blocks apart relies on (k_fit)
+    int32_t pad;
     unsigned long long trace[S_NUM];  // folded stripes (trace output)
 };
 
@@ -312,11 +314,13 @@ __global__ void k_iota(int32_t *p, int64_t n)
 // ---------------------------------------------------------------- Phase 0
 // Column headers, input checks, and left(i) (Def. "left") by atomicMin.
 // The structural checks (slice inside rows[0, nnz), rows strictly ascending
-// and in [0, j)) always run, so no later kernel can index out of bounds;
-// `validate` adds the dimension check.
-// given = 1: left and beta come with the boundary (a builder made them), so
-// the atomics on left are skipped and beta's consequences (a known-negative
-// row's record, its bit in neg) are written here instead of in k_beta.
+// and in [0, j)) always run unless given, so the rounds cannot index out of
+// bounds: there dim only chooses a slot.  `validate` adds the dimension check;
+// the blocks solved apart, which index by dimension, need it or k_fit's.
+// given = 1: left and beta come with the boundary, so the atomics on left are
+// skipped, the rows are read for `validate` only, and beta's consequences (a
+// known-negative row's record, its bit in neg) are written here instead of in
+// k_beta.
 // records = 0: the rows' records are written later (k_mix_count).
 __global__ void k_init(Dev d, int64_t nnz, int validate, int given, int compression, int records)
 {
@@ -388,6 +392,48 @@ __global__ void k_init(Dev d, int64_t nnz, int validate, int given, int compress
         if ((threadIdx.x & (kWave - 1)) == 0 && top > *(volatile int32_t *)&d.cnt->topdim)
             atomicMax(&d.cnt->topdim, top);
     }
+}
+
+// What the blocks solved apart rely on, for a matrix that is no builder's and
+// that k_init has not checked for it: slices inside rows, rows ascending and
+// above the diagonal, dim(row) = dim(column) - 1 >= 0 (so every table they
+// index by a row or a column of one dimension holds an entry of the other's),
+// and left and beta, when given, as defined.  A matrix that differs (a
+// coboundary matrix with its simplices' own dimensions, say) takes the rounds.
+__global__ void __launch_bounds__(kBlock) k_fit(Dev d, int64_t nnz, int given)
+{
+    auto slice = [&](int64_t j, int64_t *s, int64_t *e) {
+        *s = d.col_ptr[j];
+        *e = d.col_ptr[j + 1];
+        return *s >= 0 && *e >= *s && *e <= nnz;
+    };
+    bool ok = true;
+    for (int64_t j = blockIdx.x * (int64_t)kBlock + threadIdx.x; j < d.m; j += (int64_t)gridDim.x * kBlock) {
+        int64_t s, e;
+        const int dj = d.dim[j];
+        ok = ok && slice(j, &s, &e) && dj >= 0;
+        int32_t prev = -1, b = -1;
+        for (int64_t p = s; ok && p < e; p++) {
+            const int32_t r = d.rows[p];
+            ok = r > prev && (int64_t)r < j && d.dim[r] == dj - 1;
+            if (ok && given) {
+                const int32_t l = d.left[r];
+                ok = l <= (int32_t)j;  // the first column with row r
+                if (l == (int32_t)j) b = r;
+            }
+            prev = r;
+        }
+        if (!ok) break;
+        if (!given) continue;
+        const int32_t t = d.left[j];
+        ok = d.beta[j] == b;
+        if (!ok || t == 0x7FFFFFFF) continue;
+        ok = t > (int32_t)j && (int64_t)t < d.m && slice(t, &s, &e);
+        bool has = false;  // and column left(j) holds row j
+        for (int64_t p = s; ok && p < e; p++) has = has || d.rows[p] == (int32_t)j;
+        ok = ok && has;
+    }
+    if (__ballot(!ok) != 0 && (threadIdx.x & (kWave - 1)) == 0) d.cnt->unfit = 1;  // (any writer writes the same)
 }
 
 // beta_j = max{i : left(i) = j} (Def. "beta"); beta_j >= 0 marks column j as
@@ -3542,7 +3588,8 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     const unsigned gm = grid_for(m, kBlock, 65536);
     const double dm = (double)m, dz = (double)nnz;
     // blocks solved apart from the rounds, which then hold the columns of the others
-    const bool blocks = bnd->dim && blocks_ok(c, *opt) && d.arena_cap * sizeof(int32_t) >= (size_t)m * 8;
+    // (the caller's own matrix: if it is fit for that)
+    bool blocks = bnd->dim && blocks_ok(c, *opt) && d.arena_cap * sizeof(int32_t) >= (size_t)m * 8;
     const int records = blocks ? 0 : 1;
     // left, piv, low*, T, the active list; the negative bitmask
     PMS_LAUNCH(c, K_FILL, (given_lb ? 20 : 24) * dm + 4.0 * nwords, k_setup, gm, kBlock, d, act0, (int64_t)nwords,
@@ -3601,6 +3648,8 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     const char *tr_env = getenv("PMS_TRACE");
     const int trace = tr_env && tr_env[0] == '1';
     if (blocks) PMS_LAUNCH(c, K_GRAPH, dm, k_dim_count, grid_for(m, kBlock, 1024), kBlock, d);
+    if (blocks && !c->builder && (given_lb || !opt->validate))
+        PMS_LAUNCH(c, K_INIT, 9 * dm + 5 * dz + (given_lb ? 8 * dm + 8 * dz : 0), k_fit, gm, kBlock, d, nnz, given_lb ? 1 : 0);
     PMS_HIP(hipGetLastError());
 
     Counters *h = (Counters *)c->host_pinned;
@@ -3608,6 +3657,10 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     PMS_HIP(hipStreamSynchronize(st));
     if (h->error) return set_err(c, PMS_ERR_NOT_COMPATIBLE, "boundary matrix is not that of a compatible filtration "
                                                             "(rows must ascend, lie above the diagonal and be facets)");
+    if (blocks && h->unfit) {  // by the rounds alone
+        PMS_LAUNCH(c, K_FILL, 32 * dm, k_all_records, gm, kBlock, d);
+        blocks = false;
+    }
     // debug_invariants: the first broken property, by name
     auto dbg_check = [&](const char *where, int32_t r) -> pms_status {
         if (!h->dbg_flags) return PMS_OK;
@@ -4752,9 +4805,14 @@ pms_status pms_reduce_filtration(pms_ctx *c, const pms_filtration *fh, int32_t c
         if (s != PMS_OK || done) return s;
     }
     c->second = f->has_second ? f->second : nullptr;
+    c->builder = true;
     struct Reset {
         pms_ctx *c;
-        ~Reset() { c->second = nullptr; }
+        ~Reset()
+        {
+            c->second = nullptr;
+            c->builder = false;
+        }
     } reset{c};
     return inst_col_off ? pms_reduce_batched(c, count, inst_col_off, &bnd, opt, res, inst_pair_off, inst_ess_off, pair_inst)
                         : pms_reduce(c, &bnd, opt, res);

@@ -1,8 +1,14 @@
 """Inputs at the edge of what scratch, views and tables are sized for."""
+import ctypes
+
 import numpy as np
 import pytest
+import torch
 
-from paper_1708_04710_amd import synth
+import oracle
+from paper_1708_04710_amd import _binding as B
+from paper_1708_04710_amd import api, synth
+from tests import brute
 from tests.test_gpu_build import _compare_lowerstar
 
 pytestmark = pytest.mark.gpu
@@ -17,3 +23,73 @@ def test_flat_grids(gpu, shape, levels):
     if levels:
         g = np.floor(g * levels).astype(np.float32)
     _compare_lowerstar(g, gpu)
+
+
+def _reduce_as_given(gpu, cols, dim, **kw):
+    cp = np.cumsum([0] + [len(c) for c in cols]).astype(np.int64)
+    rows = np.array([r for c in cols for r in sorted(c)], np.int32)
+    want = oracle.reduce_standard(cp, rows)
+    args = torch.as_tensor(cp, device=gpu), torch.as_tensor(rows, device=gpu)
+    for d in (torch.as_tensor(np.asarray(dim, np.int8), device=gpu), None):
+        for noalloc in (False, True):
+            res = api.reduce(*args, d, validate=False, noalloc=noalloc, **kw)
+            assert np.array_equal(res.low_star.cpu().numpy(), want)
+            b, e = oracle.pairs(want)
+            assert np.array_equal(res.pair_birth.cpu().numpy(), b) and np.array_equal(res.pair_death.cpu().numpy(), e)
+            assert np.array_equal(res.essential.cpu().numpy(), oracle.essential(want))
+    return want
+
+
+@pytest.mark.parametrize("cols,dim", [
+    ([[], [0], [0]], [2, 1, 1]),             # dimensions falling: a top column named by an edge's row
+    ([[], [], [0, 1]], [0, 0, 3]),           # a gap
+    ([[], [], [0, 1]], [-1, -1, 0]),         # the empty simplex counted
+    ([[], [0], [0], []], [1, 1, 1, 1]),      # one dimension for all
+    ([[], [], [0, 1], [0, 1]], [0, 1, 1, 1]),
+    ([[], [], [0, 1]], [0, -128, 127]),
+])
+def test_dimensions_that_are_not_those_of_facets(gpu, cols, dim):
+    """Without the input check any dim is taken, and chooses slots only."""
+    _reduce_as_given(gpu, cols, dim)
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_coboundary_matrix_with_its_simplices_dimensions(gpu, seed):
+    """The anti-transpose of a boundary matrix: dim(row) = dim(column) + 1."""
+    rng = np.random.default_rng(seed)
+    if seed < 4:
+        cp, rows, dim, _, _ = brute.random_filtration(rng, n_vertices=12, n_facets=14, max_dim=3)
+    else:
+        f = oracle.build_lowerstar(synth.random_grid(seed, (3, 4, 5)))
+        cp, rows, dim = f.col_ptr, f.rows, f.dim
+    m = len(dim)
+    cols = [[] for _ in range(m)]
+    for j in range(m):
+        for r in rows[cp[j]:cp[j + 1]]:
+            cols[m - 1 - int(r)].append(m - 1 - j)
+    want = _reduce_as_given(gpu, cols, np.asarray(dim)[::-1].copy())
+    assert (want >= 0).sum() == (oracle.reduce_standard(np.asarray(cp, np.int64), np.asarray(rows, np.int32)) >= 0).sum()
+
+
+@pytest.mark.parametrize("what", ["as built", "left", "beta"])
+def test_left_and_beta_from_the_caller(gpu, what):
+    """A caller's own left and beta reach the blocks only when they are as
+    defined: with others that are in range, and that the rounds do not read
+    (left) or read as a bound only (beta: fewer pivots known), the pairs are the same."""
+    f = api.build_lowerstar(torch.as_tensor(synth.random_grid(9, (5, 6, 7)), device=gpu))
+    t = f.to_torch()
+    left, beta = f.left_beta()
+    want = api.reduce_filtration(f).low_star
+    if what == "left":
+        left = torch.full_like(left, f.m - 1)
+    if what == "beta":
+        beta = torch.full_like(beta, -1)
+    low = torch.empty_like(want)
+    bnd = B.PmsBoundary(f.m, t["col_ptr"].data_ptr(), t["rows"].data_ptr(), t["dim"].data_ptr(), left.data_ptr(),
+                        beta.data_ptr())
+    opt = api._options(validate=False)
+    res = B.PmsResult()
+    res.low_star = low.data_ptr()
+    ctx = api._ctx(f.device)
+    B.check(ctx, B.load().pms_reduce(ctx, ctypes.byref(bnd), ctypes.byref(opt), ctypes.byref(res)))
+    assert torch.equal(low, want)
