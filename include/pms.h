@@ -367,7 +367,9 @@ pms_status pms_autotune(pms_ctx *ctx, const pms_boundary *bnd, int32_t n, const 
  * ordered by the key (value, dimension, lexicographic vertex tuple), with its
  * boundary matrix (eq. "def:boundary_matrix").  Pass *f = NULL to allocate a
  * new one, or an existing one to rebuild in place (its buffers are reused
- * when large enough).  Free it with pms_filtration_free.
+ * when large enough).  A build that fails leaves *f as it was (NULL may have
+ * become a new one) or, once it has written over it, empty (m = 0); either
+ * can be reduced, rebuilt and freed.  Free it with pms_filtration_free.
  * ------------------------------------------------------------------------ */
 typedef struct pms_filtration pms_filtration;
 

@@ -117,8 +117,13 @@ class Filtration:
         self.handle = ctypes.c_void_p()
         self.view = B.PmsFiltrationView()
 
-    def _refresh(self):
-        B.check(None, B.load().pms_filtration_view_get(self.handle, ctypes.byref(self.view)))
+    def _built(self, ctx, status):
+        """After a build into this filtration: its view as the library has it
+        now, also when the build was refused (its buffers may then be empty or
+        others), and the build's error if any."""
+        if self.handle:
+            B.load().pms_filtration_view_get(self.handle, ctypes.byref(self.view))
+        B.check(ctx, status)
 
     @property
     def m(self) -> int:
@@ -182,8 +187,7 @@ def build_lowerstar(grid: torch.Tensor, out: Filtration | None = None) -> Filtra
     nz, ny, nx = grid.shape
     f = out if out is not None else Filtration(grid.device)
     ctx = _ctx(grid.device)
-    B.check(ctx, B.load().pms_build_lowerstar(ctx, grid.data_ptr(), nx, ny, nz, ctypes.byref(f.handle)))
-    f._refresh()
+    f._built(ctx, B.load().pms_build_lowerstar(ctx, grid.data_ptr(), nx, ny, nz, ctypes.byref(f.handle)))
     return f
 
 
@@ -226,14 +230,8 @@ def build_vr(clouds, thresholds=None, maxdim: int = 2, out: Filtration | None = 
     f = out if out is not None else Filtration(dev)
     ctx = _ctx(dev)
     fn = B.load().pms_build_vr_f32 if f32 else B.load().pms_build_vr_i32
-    st = fn(ctx, base or None, nb, n, D, pt_off, thr, maxdim, ctypes.byref(f.handle), col_off)
-    _binding_check(ctx, st)
-    f._refresh()
+    f._built(ctx, fn(ctx, base or None, nb, n, D, pt_off, thr, maxdim, ctypes.byref(f.handle), col_off))
     return f, list(col_off)
-
-
-def _binding_check(ctx, st):
-    B.check(ctx, st)
 
 
 def _dptr(t):

@@ -726,9 +726,6 @@ pms_status build_lowerstar(Ctx *c, const float *grid, int32_t nx, int32_t ny, in
     pms_status st = filtration_reserve(c, &f, m, nnz, /*f32*/ 1);
     if (st != PMS_OK) return st;
     *out = f;
-    f->m = m;
-    f->nnz = nnz;
-    f->value_is_f32 = 1;
     hipStream_t s = c->stream;
     const int64_t nk = nv * kShapes;
     const int64_t tiles = (m + kBlock - 1) / kBlock, kV = nv >= kLsManyV ? kBlock : 32,
@@ -820,10 +817,13 @@ pms_status build_lowerstar(Ctx *c, const float *grid, int32_t nx, int32_t ny, in
         PMS_HIP(hipMemcpyAsync(herr, err, 8, hipMemcpyDeviceToHost, s));
         PMS_HIP(hipStreamSynchronize(s));
     }
-    f->has_left_beta = f->has_second = 1;
     if (c->prof_on) prof_flush(c);
     if (herr[0] == 1) return set_err(c, PMS_ERR_INVALID_ARG, "grid holds NaN");
     if (herr[0]) return set_err(c, PMS_ERR_HIP, "internal: simplex count mismatch in the lower-star builder");
+    f->m = m;
+    f->nnz = nnz;
+    f->value_is_f32 = 1;
+    f->has_left_beta = f->has_second = 1;
     return PMS_OK;
 }
 

@@ -520,9 +520,6 @@ static pms_status build_vr(Ctx *c, const void *pts, bool f32, const int32_t *n, 
     st = filtration_reserve(c, &f, m, nnz, f32 ? 1 : 0);
     if (st != PMS_OK) return st;
     *out = f;
-    f->m = m;
-    f->nnz = nnz;
-    f->value_is_f32 = f32 ? 1 : 0;
     const int64_t M = m > 0 ? m : 1;
     unsigned long long *keys = (unsigned long long *)grow_scratch(c, B_BUILD0, M * 8);
     unsigned long long *keys2 = (unsigned long long *)grow_scratch(c, B_BUILD1, M * 8);
@@ -538,6 +535,7 @@ static pms_status build_vr(Ctx *c, const void *pts, bool f32, const int32_t *n, 
         int64_t zero = 0;
         PMS_HIP(hipMemcpyAsync(f->col_ptr, &zero, 8, hipMemcpyHostToDevice, s));
         PMS_HIP(hipStreamSynchronize(s));
+        f->value_is_f32 = f32 ? 1 : 0;
         return PMS_OK;
     }
     const dim3 g3((unsigned)((maxnn + kBlock - 1) / kBlock > 0 ? (maxnn + kBlock - 1) / kBlock : 1), (unsigned)B);
@@ -648,6 +646,9 @@ static pms_status build_vr(Ctx *c, const void *pts, bool f32, const int32_t *n, 
     PMS_HIP(hipStreamSynchronize(s));
     if (c->prof_on) prof_flush(c);
     if (herr == 3) return set_err(c, PMS_ERR_HIP, "internal: a tetrahedron's face was not found");
+    f->m = m;
+    f->nnz = nnz;
+    f->value_is_f32 = f32 ? 1 : 0;
     return PMS_OK;
 }
 

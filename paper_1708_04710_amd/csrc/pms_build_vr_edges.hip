@@ -1033,9 +1033,6 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
     if (m >= 0x7FFFFFFF) return set_err(c, PMS_ERR_INVALID_ARG, "too many simplices for 32-bit indices");
     st = filtration_reserve(c, &f, m, nnz, f32 ? 1 : 0);
     if (st != PMS_OK) return st;
-    f->m = m;
-    f->nnz = nnz;
-    f->value_is_f32 = f32 ? 1 : 0;
     if (maxdim >= 3 && (st = filtration_vr_reserve(c, &f, VR_APPT, (size_t)m * 4)) != PMS_OK) return st;
     if (maxdim >= 3 && (st = filtration_vr_reserve(c, &f, VR_TRIP, (size_t)T * 4)) != PMS_OK) return st;
     f->vr_max_t = tmax;
@@ -1065,6 +1062,9 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
     }
     PMS_HIP(hipStreamSynchronize(s));
     if (c->prof_on) prof_flush(c);
+    f->m = m;
+    f->nnz = nnz;
+    f->value_is_f32 = f32 ? 1 : 0;
     f->vr_count = B;
     f->vr_edges = E;
     *done = 1;

@@ -99,7 +99,9 @@ pms_status filtration_reserve(Ctx *c, Filtration **pf, int64_t m, int64_t nnz, i
 {
     Filtration *f = filtration_get(c, pf);
     if (!f) return set_err(c, PMS_ERR_OOM, "filtration");
-    f->has_left_beta = f->has_second = 0;  // until a builder writes them
+    // empty until a builder is done: what was in it is written over
+    f->m = f->nnz = 0;
+    f->has_left_beta = f->has_second = 0;
     f->vr_count = 0;
     if (f->cap_m >= m && f->cap_nnz >= nnz && f->device == c->device) return PMS_OK;
     (void)hipStreamSynchronize(c->stream);
@@ -241,7 +243,8 @@ pms_status pms_filtration_copy_out(pms_ctx *ctx, const pms_filtration *fh, int64
     c->err.clear();
     if (hipSetDevice(c->device) != hipSuccess) return pms::set_err(c, PMS_ERR_HIP, "hipSetDevice failed");
     const hipMemcpyKind k = hipMemcpyDeviceToDevice;
-    if (col_ptr) PMS_HIP(hipMemcpyAsync(col_ptr, f->col_ptr, (f->m + 1) * 8, k, c->stream));
+    if (col_ptr && f->m == 0) PMS_HIP(hipMemsetAsync(col_ptr, 0, 8, c->stream));  // (a refused build wrote none)
+    else if (col_ptr) PMS_HIP(hipMemcpyAsync(col_ptr, f->col_ptr, (f->m + 1) * 8, k, c->stream));
     if (rows && f->nnz) PMS_HIP(hipMemcpyAsync(rows, f->rows, f->nnz * 4, k, c->stream));
     if (dim && f->m) PMS_HIP(hipMemcpyAsync(dim, f->dim, f->m, k, c->stream));
     if (value && f->m) PMS_HIP(hipMemcpyAsync(value, f->value, f->m * (f->value_is_f32 ? 4 : 8), k, c->stream));

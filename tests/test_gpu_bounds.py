@@ -93,3 +93,62 @@ def test_left_and_beta_from_the_caller(gpu, what):
     ctx = api._ctx(f.device)
     B.check(ctx, B.load().pms_reduce(ctx, ctypes.byref(bnd), ctypes.byref(opt), ctypes.byref(res)))
     assert torch.equal(low, want)
+
+
+def _workspace_is_consistent(gpu, f, before):
+    """After a refused build: the filtration of before, or an empty one."""
+    t = f.to_torch()
+    res = api.reduce_filtration(f)
+    if f.m == 0:
+        assert t["col_ptr"].tolist() == [0] and res.low_star.numel() == 0 and res.pair_birth.numel() == 0
+        assert f.left_beta() is None
+    else:
+        assert f.m == before.m and np.array_equal(t["rows"].cpu().numpy(), before.rows)
+        assert np.array_equal(res.low_star.cpu().numpy(), oracle.reduce_twist(before.col_ptr, before.rows, before.dim))
+
+
+@pytest.mark.parametrize("first", ["grid", "cloud"])
+@pytest.mark.parametrize("refused", ["grid", "cloud", "far", "arguments"])
+def test_refused_build_of_a_workspace(gpu, first, refused):
+    """A kept workspace built small, refused something larger, reduced, and
+    built again: what it says it holds is what is reduced."""
+    g = synth.random_grid(3, (4, 5, 6))
+    pts = np.random.default_rng(3).integers(0, 50, (20, 3)).astype(np.int32)
+    if first == "grid":
+        f = api.build_lowerstar(torch.as_tensor(g, device=gpu))
+        before = oracle.build_lowerstar(g)
+    else:
+        f, _ = api.build_vr(torch.as_tensor(pts, device=gpu))
+        before = oracle.build_vr_i32(pts)
+    with pytest.raises(B.PmsError) as e:
+        if refused == "grid":
+            bad = synth.random_grid(4, (16, 17, 18))
+            bad[3, 3, 3] = np.nan
+            api.build_lowerstar(torch.as_tensor(bad, device=gpu), out=f)
+        elif refused == "cloud":
+            bad = np.random.default_rng(5).normal(size=(90, 3)).astype(np.float32)
+            bad[7, 1] = np.inf
+            api.build_vr(torch.as_tensor(bad, device=gpu), out=f)
+        elif refused == "far":
+            api.build_vr(torch.tensor([[0], [1 << 20]], dtype=torch.int32, device=gpu), out=f)
+        else:
+            api.build_vr(torch.as_tensor(pts, device=gpu), maxdim=4, out=f)
+    assert e.value.status == B.PMS_ERR_INVALID_ARG
+    _workspace_is_consistent(gpu, f, before)
+    api.build_lowerstar(torch.as_tensor(g, device=gpu), out=f)
+    ref = oracle.build_lowerstar(g)
+    assert np.array_equal(api.reduce_filtration(f).low_star.cpu().numpy(), oracle.reduce_twist(ref.col_ptr, ref.rows, ref.dim))
+    f, off = api.build_vr([torch.as_tensor(pts, device=gpu)] * 2, out=f)
+    ref = oracle.build_vr_i32(pts)
+    want = oracle.reduce_twist(ref.col_ptr, ref.rows, ref.dim)
+    low = api.reduce_batched(f, off).low_star.cpu().numpy()
+    assert np.array_equal(low[:ref.m], want)
+    assert np.array_equal(low[ref.m:], np.where(want >= 0, want + ref.m, -1))
+
+
+def test_refused_first_build(gpu):
+    """The same for a filtration that held nothing before."""
+    f = api.Filtration(gpu)
+    with pytest.raises(B.PmsError):
+        api.build_lowerstar(torch.full((5, 5, 5), float("nan"), device=gpu), out=f)
+    assert f.m == 0 and api.reduce_filtration(f).low_star.numel() == 0
