@@ -890,8 +890,7 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
         int32_t cap = kVeThreads;  // (a sort has at least one key a thread)
         while (cap < kLdsEdges && cap < maxpairs) cap <<= 1;
         const size_t bytes = (size_t)cap * 8;
-        const void *fn = f32 ? (const void *)k_ve_edges<true> : (const void *)k_ve_edges<false>;
-        PMS_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+        PMS_ALLOW_LDS(f32 ? k_ve_edges<true> : k_ve_edges<false>, kLdsEdges * sizeof(unsigned long long));
         hipEvent_t e0 = nullptr;
         if (c->prof_on) { e0 = prof_event(c); (void)hipEventRecord(e0, s); }
         if (f32) k_ve_edges<true><<<B, kVeThreads, bytes, s>>>(dcl, pts, lexb, cap, ev_s, eval, erank, gst_s, gend_s, err);
@@ -972,7 +971,7 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
         const size_t bytes = maxdim >= 2 ? (size_t)nmax * ve_rank_row((int)nmax) * 4 : 0;
         const unsigned parts = (unsigned)std::max<int64_t>(
             1, std::min<int64_t>((emax + kVeMaskThreads - 1) / kVeMaskThreads, std::max(1, 1024 / B)));
-        PMS_HIP(hipFuncSetAttribute((const void *)k_ve_masks_lds, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+        PMS_ALLOW_LDS(k_ve_masks_lds, kLdsPoints * ve_rank_row(kLdsPoints) * 4);
         hipEvent_t e0 = nullptr;
         if (c->prof_on) { e0 = prof_event(c); (void)hipEventRecord(e0, s); }
         k_ve_masks_lds<<<dim3(parts, (unsigned)B), kVeMaskThreads, bytes, s>>>(cl, maxdim, ev_s, gst_s, gend_s, erank, ev,

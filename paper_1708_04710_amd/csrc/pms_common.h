@@ -160,6 +160,12 @@ hipEvent_t prof_event(Ctx *c);
 // Fold finished launches into the per-kernel totals (call after a sync).
 void prof_flush(Ctx *c);
 
+// Allows `kernel` dynamic LDS of up to `most` bytes, the largest that any call
+// launches it with: the attribute is the process's, so a call's own size would
+// be another thread's limit between its setting and its launch.
+#define PMS_ALLOW_LDS(kernel, most) \
+    PMS_HIP(hipFuncSetAttribute((const void *)(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(most)))
+
 // Launch `kernel` on the context's stream; with the profiler on, bracket it
 // with events and remember its algorithmic bytes.
 #define PMS_LAUNCH(c, kid, bytes, kernel, grid, block, ...)                                    \

@@ -359,10 +359,9 @@ static __global__ void k_dual_counters(DualState s, int first, int32_t n)
 
 // k_dual's LDS, allowed and launched.
 template <class P>
-inline pms_status dual_map_lds(Ctx *c, const P &, const DualState &s)
+inline pms_status dual_map_lds(Ctx *c, const P &)
 {
-    PMS_HIP(hipFuncSetAttribute((const void *)k_dual<P>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)((s.nw1 + s.nw0) * 4)));
+    PMS_ALLOW_LDS(k_dual<P>, (dual_words(kDualLdsBits) + dual_summary_words(kDualLdsBits)) * 4);
     return PMS_OK;
 }
 template <class P>

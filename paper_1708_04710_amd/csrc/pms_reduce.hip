@@ -3990,7 +3990,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
                     PMS_LAUNCH(c, K_FILL, 0, k_dual_counters, 1, kBlock, s, 1, 0);
                     PMS_LAUNCH(c, K_DUAL, 5 * dm, k_dual_cand, gm, kBlock, d, s, b);
                     int ok = 0;
-                    pms_status sr = dual_map_lds(c, pv, s);
+                    pms_status sr = dual_map_lds(c, pv);
                     if (sr == PMS_OK)
                         sr = dual_rounds(c, pv, s, [&](int r) { dual_launch(c, pv, s, nb, r); }, K_DUAL, &dual_r,
                                          &dual_active, &ok);

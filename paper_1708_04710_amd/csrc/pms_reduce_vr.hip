@@ -674,7 +674,7 @@ pms_status reduce_vr(Ctx *c, const Filtration *f, pms_result *res, int32_t count
         const size_t lds = (size_t)f->vr_max_n * ((f->vr_max_n + 63) / 64) * 8;
         const int words = (f->vr_max_n + 63) / 64;
         auto *fn = words <= 1 ? k_vr_cocycle<1> : words <= 2 ? k_vr_cocycle<2> : words <= 4 ? k_vr_cocycle<4> : words <= 8 ? k_vr_cocycle<8> : k_vr_cocycle<0>;
-        PMS_HIP(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        PMS_ALLOW_LDS(fn, 1023 * 16 * 8);  // (the most points of a cloud)
         const pms_status sd = dual_rounds(
             c, pe, s, [&](int r) { fn<<<blocks_of[0], kWave, lds, st>>>(v, s, kedge, r); }, K_DUAL, &rounds, &active, &ok);
         if (sd != PMS_OK) return sd;
@@ -685,7 +685,7 @@ pms_status reduce_vr(Ctx *c, const Filtration *f, pms_result *res, int32_t count
         const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>((f->vr_max_m + kBlock - 1) / kBlock, std::max(16, 16384 / B)));
         PMS_LAUNCH(c, K_DUAL, 5 * dm, k_vr_cand, dim3(gx, (unsigned)B), kBlock, v, s, f->dim, tot);
         VrTriProv pt{v, (const int4 *)f->verts, {}};
-        pms_status sd = dual_map_lds(c, pt, s);
+        pms_status sd = dual_map_lds(c, pt);
         if (sd == PMS_OK)
             sd = dual_rounds(c, pt, s, [&](int r) { dual_launch(c, pt, s, blocks_of[1], r); }, K_DUAL, &rounds, &active, &ok);
         if (sd != PMS_OK) return sd;

@@ -1,5 +1,6 @@
 """Inputs at the edge of what scratch, views and tables are sized for."""
 import ctypes
+import threading
 
 import numpy as np
 import pytest
@@ -152,3 +153,46 @@ def test_refused_first_build(gpu):
     with pytest.raises(B.PmsError):
         api.build_lowerstar(torch.full((5, 5, 5), float("nan"), device=gpu), out=f)
     assert f.m == 0 and api.reduce_filtration(f).low_star.numel() == 0
+
+
+def test_threads_with_clouds_of_other_sizes(gpu):
+    """Each thread on its own stream: kernels whose dynamic LDS depends on the
+    clouds are launched with 8 KB to 148 KB at once."""
+    rng = np.random.default_rng(8)
+    work = [(torch.as_tensor(rng.integers(0, 1 << 14, (n, 3)).astype(np.int32), device=gpu), d)
+            for n, d in ((12, 2), (181, 2), (511, 2), (40, 3))]
+    thr = [None, None, [1 << 22], None]
+
+    def once(k):
+        f, off = api.build_vr(work[k][0], thr[k], work[k][1])
+        res = api.reduce_batched(f, off)
+        return f.m, res.low_star, res.pair_birth, res.essential
+
+    def csc(k):
+        f, _ = api.build_vr(work[k][0], thr[k], work[k][1])
+        t = f.to_torch()
+        return f.m, api.reduce(t["col_ptr"], t["rows"], t["dim"]).low_star
+
+    jobs = [(once, 0), (once, 1), (once, 2), (once, 3), (csc, 0), (csc, 3)]
+    want = [fn(k) for fn, k in jobs]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def loop(i):
+        fn, k = jobs[i]
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(25):
+                    got = fn(k)
+                    if got[0] != want[i][0] or not all(torch.equal(a, b) for a, b in zip(got[1:], want[i][1:])):
+                        wrong.append((i, "differs"))
+                        return
+        except Exception as e:  # noqa: BLE001
+            wrong.append((i, repr(e)))
+
+    threads = [threading.Thread(target=loop, args=(i,)) for i in range(len(jobs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong, wrong
