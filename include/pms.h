@@ -66,8 +66,9 @@ const char *pms_last_error(const pms_ctx *ctx);
 /* Library version string (static). */
 const char *pms_version(void);
 /* Checks the device's wave-level primitives (DPP reductions) against
- * reference shuffles on ctx's device, and the debug_invariants detectors on
- * fabricated states that each break one property; PMS_OK when all agree. */
+ * reference shuffles on ctx's device, the number of steps that repeated walks
+ * of the graph blocks take, and the debug_invariants detectors on fabricated
+ * states that each break one property; PMS_OK when all agree. */
 pms_status pms_selftest(pms_ctx *ctx);
 
 /* Boundary matrix d of a filtration in filtration order, CSC:

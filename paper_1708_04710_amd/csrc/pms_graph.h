@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(kBlock) k_graph0_seed(Dev d)
             continue;
         }
         const int32_t hi = max(u, v), lo = min(u, v);
-        if (hi >= 0 && d.left[hi] == (int32_t)j) d.T[hi] = ((unsigned long long)j << 32) | (uint32_t)(lo + 1);
+        if (hi >= 0 && d.left[hi] == (int32_t)j) d.T[hi] = ((unsigned long long)j << 32) | graph_code<false>(lo);
     }
     const int64_t t = block_sum64(nb);
     if (threadIdx.x == 0) stat_add(d, S_BETAPIV, (unsigned long long)t, blockIdx.x);
@@ -109,7 +109,7 @@ __global__ void __launch_bounds__(kBlock) k_graph0_seed(Dev d)
 // positive: their columns reduce to zero).  (Every column's low is its last row
 // before the rounds: read from there instead of through len, col_ptr and rows
 // this kernel takes 0.90 ms instead of 1.00 at 128^3, the seeds of both blocks
-// 0.76 instead of 0.98; the top block's walk, 2.1 to 2.2, is bound by its atomics.)
+// 0.76 instead of 0.98.)
 __global__ void __launch_bounds__(kBlock) k_graph0_walk(Dev d)
 {
     if (d.cnt->not_graph & kNotGraph0) return;
@@ -165,7 +165,7 @@ __global__ void __launch_bounds__(kBlock) k_graph_top_seed(Dev d, const unsigned
             continue;
         }
         if (t0 != kGraphOut && d.low[t0] == (int32_t)i)
-            d.T[t0] = ((unsigned long long)(0x7FFFFFFFu - (uint32_t)i) << 32) | (uint32_t)t1;
+            d.T[t0] = ((unsigned long long)(0x7FFFFFFFu - (uint32_t)i) << 32) | graph_code<true>(t1);
     }
 }
 

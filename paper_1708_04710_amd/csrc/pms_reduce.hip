@@ -3334,6 +3334,33 @@ __global__ void k_selftest(int32_t *bad)
     if (lane == 0) atomicAdd(bad, nbad);
 }
 
+// Steps of kSelfWalks walks along one path of kSelfNodes nodes, each earlier in
+// the order than the one before it, in each kind of graph block: a walked path
+// is shortened, so all of them together take a few times the path and a bounded
+// number each, not kSelfWalks times the path.
+constexpr int kSelfNodes = 512, kSelfWalks = 64;
+__global__ void __launch_bounds__(kWave) k_selftest_walks(int32_t *bad)
+{
+    __shared__ unsigned long long P[kSelfNodes + 1];
+    for (int top = 0; top < 2; top++) {
+        for (int k = threadIdx.x; k <= kSelfNodes; k += kWave) P[k] = kGraphEmpty;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int k = 0; k < kSelfNodes; k++) {
+                if (top) graph_place<true>(P, (uint32_t)(kSelfNodes - 1 - k), k, k + 1);
+                else graph_place<false>(P, (uint32_t)k, k, k + 1);
+            }
+            int32_t steps = 0;
+            for (int k = 0; k < kSelfWalks; k++) {
+                const uint32_t ord = (uint32_t)(kSelfNodes + k);
+                steps += top ? graph_place<true>(P, ord, 0, kSelfNodes) : graph_place<false>(P, ord, 0, kSelfNodes);
+            }
+            if (steps < kSelfNodes || steps > 4 * kSelfNodes + 20 * kSelfWalks) atomicAdd(bad + 1, 1);
+        }
+        __syncthreads();
+    }
+}
+
 // ---------------------------------------------------------------- host
 void *grow_scratch(Ctx *c, int id, size_t bytes)
 {
@@ -4549,13 +4576,15 @@ pms_status pms_selftest(pms_ctx *c)
     if (hipSetDevice(c->device) != hipSuccess) return pms::set_err(c, PMS_ERR_HIP, "hipSetDevice failed");
     int32_t *bad = (int32_t *)pms::grow_scratch(c, pms::B_TMP1, 64);
     if (!bad) return pms::set_err(c, PMS_ERR_OOM, "scratch");
-    PMS_HIP(hipMemsetAsync(bad, 0, 4, c->stream));
+    PMS_HIP(hipMemsetAsync(bad, 0, 8, c->stream));
     pms::k_selftest<<<4, 256, 0, c->stream>>>(bad);
+    pms::k_selftest_walks<<<1, pms::kWave, 0, c->stream>>>(bad);
     PMS_HIP(hipGetLastError());
-    int32_t h = -1;
-    PMS_HIP(hipMemcpyAsync(&h, bad, 4, hipMemcpyDeviceToHost, c->stream));
+    int32_t h[2] = {-1, -1};
+    PMS_HIP(hipMemcpyAsync(h, bad, 8, hipMemcpyDeviceToHost, c->stream));
     PMS_HIP(hipStreamSynchronize(c->stream));
-    if (h != 0) return pms::set_err(c, PMS_ERR_HIP, "wave reduction self-test failed");
+    if (h[0] != 0) return pms::set_err(c, PMS_ERR_HIP, "wave reduction self-test failed");
+    if (h[1] != 0) return pms::set_err(c, PMS_ERR_HIP, "graph walk self-test failed: walked paths are not shortened");
     return debug_selftest(c);
 }
 

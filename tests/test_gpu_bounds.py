@@ -196,3 +196,29 @@ def test_threads_with_clouds_of_other_sizes(gpu):
     for t in threads:
         t.join()
     assert not wrong, wrong
+
+
+@pytest.mark.parametrize("n,reverse", [(40, False), (3001, False), (30_000, False), (30_000, True)])
+def test_long_strip_in_adverse_order(gpu, n, reverse):
+    """Triangles (i, i+1, i+2) whose shared edges come after the boundary edges:
+    they make one path through all triangles, which every boundary edge walks to
+    its end.  Walked along earlier faces in one of the directions, so that the
+    path is shortened (``pms_selftest`` counts the steps), along later ones in
+    the other."""
+    tri = np.stack([np.arange(n), np.arange(n) + 1, np.arange(n) + 2], 1)
+    outer = [(0, 1), (n, n + 1)] + [(i, i + 2) for i in range(n)]
+    inner = [(i + 1, i + 2) for i in range(n - 1)]
+    if reverse:
+        tri, inner = tri[::-1], inner[::-1]
+    edges = outer + inner
+    at = {e: n + 2 + k for k, e in enumerate(edges)}
+    cols = [[] for _ in range(n + 2)] + [list(e) for e in edges]
+    cols += [[at[(int(a), int(b))], at[(int(a), int(c))], at[(int(b), int(c))]] for a, b, c in tri]
+    dim = [0] * (n + 2) + [1] * len(edges) + [2] * n
+    cp = np.cumsum([0] + [len(c) for c in cols]).astype(np.int64)
+    rows = np.array([r for c in cols for r in sorted(c)], np.int32)
+    res = api.reduce(torch.as_tensor(cp, device=gpu), torch.as_tensor(rows, device=gpu),
+                     torch.as_tensor(np.asarray(dim, np.int8), device=gpu))
+    want = oracle.reduce_twist(cp, rows, np.asarray(dim, np.int8))
+    assert np.array_equal(res.low_star.cpu().numpy(), want) and res.rounds == 1
+    api.selftest(gpu)
