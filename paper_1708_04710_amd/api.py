@@ -273,45 +273,46 @@ def _result(res, t, **extra) -> ReduceResult:
                         addition_bytes=res.addition_bytes, **extra)
 
 
-def _reduce_ptrs(dev, m, col_ptr_p, rows_p, dim_p, *, outputs=True, noalloc=False, left_p=None, beta_p=None,
-                 **kw) -> ReduceResult:
-    lib = B.load()
-    ctx = _ctx(dev)
-    bnd = B.PmsBoundary(m, col_ptr_p, rows_p, dim_p, left_p, beta_p)
-    opt = _options(**kw)
-    res, t = _outputs(dev, m, outputs)
-    fn = lib.pms_reduce_noalloc if noalloc else lib.pms_reduce
-    B.check(ctx, fn(ctx, ctypes.byref(bnd), ctypes.byref(opt), ctypes.byref(res)))
-    extra = {}
-    if kw.get("diagnostics"):
-        extra.update(round_stats=round_stats(dev), essential_estimate=essential_estimate(m, dev))
-    return _result(res, t, **extra)
-
-
-def _reduce_built(f: Filtration, inst_col_off=None, *, outputs=True, **kw) -> ReduceResult:
-    """``pms_reduce_filtration``: the filtration itself rather than its
-    arrays, so that the library can use what its builder knows."""
-    lib = B.load()
-    dev, m = f.device, f.m
+def _call_reduce(dev, m, reduce_one, reduce_batch, *, outputs=True, inst_col_off=None, **kw) -> ReduceResult:
+    """The outputs of one reduction of ``m`` columns: ``reduce_one(ctx, opt,
+    res)``, or with the instances' offsets ``reduce_batch(ctx, count, offsets,
+    opt, res, pair_off, ess_off, pair_inst)``."""
     ctx = _ctx(dev)
     opt = _options(**kw)
     res, t = _outputs(dev, m, outputs)
     extra = {}
     if inst_col_off is None:
-        st = lib.pms_reduce_filtration(ctx, f.handle, 0, None, ctypes.byref(opt), ctypes.byref(res), None, None, None)
+        st = reduce_one(ctx, ctypes.byref(opt), ctypes.byref(res))
     else:
         nb = inst_col_off.numel() - 1
         poff = torch.empty(nb + 1, dtype=torch.int64, device=dev)
         eoff = torch.empty(nb + 1, dtype=torch.int64, device=dev)
         pinst = torch.empty(max(res.cap_pairs, 1), dtype=torch.int32, device=dev)
-        st = lib.pms_reduce_filtration(ctx, f.handle, nb, inst_col_off.data_ptr(), ctypes.byref(opt),
-                                       ctypes.byref(res), poff.data_ptr(), eoff.data_ptr(),
-                                       pinst.data_ptr() if outputs else None)
+        st = reduce_batch(ctx, nb, inst_col_off.data_ptr(), ctypes.byref(opt), ctypes.byref(res), poff.data_ptr(),
+                          eoff.data_ptr(), pinst.data_ptr() if outputs else None)
         extra = dict(inst_pair_off=poff, inst_ess_off=eoff, pair_inst=pinst[:res.n_pairs] if outputs else None)
     B.check(ctx, st)
     if kw.get("diagnostics"):
         extra.update(round_stats=round_stats(dev), essential_estimate=essential_estimate(m, dev))
     return _result(res, t, **extra)
+
+
+def _reduce_ptrs(dev, m, col_ptr_p, rows_p, dim_p, *, noalloc=False, left_p=None, beta_p=None, **kw) -> ReduceResult:
+    lib = B.load()
+    bnd = ctypes.byref(B.PmsBoundary(m, col_ptr_p, rows_p, dim_p, left_p, beta_p))
+    if noalloc and kw.get("inst_col_off") is not None:
+        raise ValueError("the allocation-free entry point reduces one matrix")
+    one = lib.pms_reduce_noalloc if noalloc else lib.pms_reduce
+    return _call_reduce(dev, m, lambda c, o, r: one(c, bnd, o, r),
+                        lambda c, nb, off, *a: lib.pms_reduce_batched(c, nb, off, bnd, *a), **kw)
+
+
+def _reduce_built(f: Filtration, inst_col_off=None, **kw) -> ReduceResult:
+    """``pms_reduce_filtration``: the filtration itself rather than its
+    arrays, so that the library can use what its builder knows."""
+    fn = B.load().pms_reduce_filtration
+    return _call_reduce(f.device, f.m, lambda c, o, r: fn(c, f.handle, 0, None, o, r, None, None, None),
+                        lambda c, nb, off, *a: fn(c, f.handle, nb, off, *a), inst_col_off=inst_col_off, **kw)
 
 
 def round_stats(device=None) -> list:

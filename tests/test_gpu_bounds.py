@@ -222,3 +222,22 @@ def test_long_strip_in_adverse_order(gpu, n, reverse):
     want = oracle.reduce_twist(cp, rows, np.asarray(dim, np.int8))
     assert np.array_equal(res.low_star.cpu().numpy(), want) and res.rounds == 1
     api.selftest(gpu)
+
+
+def test_instances_of_a_callers_matrix(gpu):
+    """``reduce`` and ``reduce_filtration`` pass instance offsets on, to the
+    results of ``reduce_batched``; the allocation-free entry point takes none."""
+    rng = np.random.default_rng(17)
+    f, off = api.build_vr([torch.as_tensor(rng.integers(0, 99, (n, 3)).astype(np.int32), device=gpu) for n in (9, 0, 14)])
+    want = api.reduce_batched(f, off)
+    t = f.to_torch()
+    dev_off = torch.as_tensor(off, dtype=torch.int64, device=gpu)
+    for got in (api.reduce(t["col_ptr"], t["rows"], t["dim"], inst_col_off=dev_off),
+                api.reduce_filtration(f, inst_col_off=dev_off)):
+        for k in ("low_star", "pair_birth", "pair_death", "essential", "inst_pair_off", "inst_ess_off", "pair_inst"):
+            assert torch.equal(getattr(got, k), getattr(want, k)), k
+    for call in (lambda: api.reduce(t["col_ptr"], t["rows"], t["dim"], inst_col_off=dev_off, noalloc=True),
+                 lambda: api.reduce_filtration(f, inst_col_off=dev_off, noalloc=True),
+                 lambda: api.reduce_batched(f, off, noalloc=True)):
+        with pytest.raises(ValueError):
+            call()
