@@ -4371,7 +4371,10 @@ __global__ void k_pair_inst(int32_t count, const int64_t *col_off, const int32_t
 
 extern "C" {
 
-const char *pms_version(void) { return "pms-gfx950 0.2"; }
+// Saved tunings are kept under it: raised when what a reduction does as built
+// in has changed, so that settings found against the one before are searched
+// anew (0.2 had no blocks solved apart, which any other setting turns off).
+const char *pms_version(void) { return "pms-gfx950 0.3"; }
 
 pms_options pms_default_options(void)
 {
