@@ -349,6 +349,14 @@ pms_tuning pms_default_tuning(void);
 pms_status pms_set_tuning(pms_ctx *ctx, const pms_tuning *t);
 /* The context's current setting into *t (host). */
 pms_status pms_get_tuning(pms_ctx *ctx, pms_tuning *t);
+/* Limits of the blocks that are reduced from their rows, for tests of what
+ * happens beyond them (0 = as built in; larger values than that have no
+ * effect): faces in one column's sum, faces remembered in all, cofaces beyond
+ * the bitmap, bits of the bitmap (1024..1150000), rounds between two resets of
+ * the counters (even, <= 256).  Every setting gives the same low*, pairs and
+ * essential simplices: a block that outgrows a list is left to the rounds.
+ * PMS_ERR_INVALID_ARG, limits unchanged, when one is out of range. */
+pms_status pms_set_dual_limits(pms_ctx *ctx, int32_t sum, int32_t arena, int32_t beyond, int32_t bits, int32_t rounds);
 /* Time n candidates on one boundary matrix and keep the fastest.
  * Candidate i is (opts[i], tunes[i]) (host arrays of n; opts NULL = the
  * default options for all); each runs pms_reduce once untimed, then `reps`

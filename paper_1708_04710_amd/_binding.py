@@ -34,7 +34,7 @@ STATUS_NAMES = {
 # every symbol include/pms.h declares (checked by the CPU test suite)
 EXPORTED = [
     "pms_create", "pms_destroy", "pms_last_error", "pms_version", "pms_selftest", "pms_default_options",
-    "pms_reduce", "pms_reduce_noalloc", "pms_reduce_batched", "pms_reduce_filtration", "pms_round_stats_read", "pms_essential_estimate", "pms_default_tuning", "pms_set_tuning", "pms_get_tuning", "pms_autotune",
+    "pms_reduce", "pms_reduce_noalloc", "pms_reduce_batched", "pms_reduce_filtration", "pms_round_stats_read", "pms_essential_estimate", "pms_default_tuning", "pms_set_tuning", "pms_get_tuning", "pms_set_dual_limits", "pms_autotune",
     "pms_profile_enable", "pms_profile_kernels", "pms_profile_kernel_name",
     "pms_profile_read", "pms_profile_read_addition_bytes", "pms_build_lowerstar", "pms_build_vr_i32", "pms_build_vr_f32", "pms_filtration_view_get", "pms_filtration_copy_out",
     "pms_filtration_copy_left_beta", "pms_filtration_free", "pms_gather", "pms_backward_lowerstar", "pms_backward_vr_f32",
@@ -141,6 +141,8 @@ def load(path: str = LIB_PATH):
     lib.pms_set_tuning.restype = ctypes.c_int
     lib.pms_get_tuning.argtypes = [P, ctypes.POINTER(PmsTuning)]
     lib.pms_get_tuning.restype = ctypes.c_int
+    lib.pms_set_dual_limits.argtypes = [P] + [ctypes.c_int32] * 5
+    lib.pms_set_dual_limits.restype = ctypes.c_int
     lib.pms_autotune.argtypes = [P, ctypes.POINTER(PmsBoundary), ctypes.c_int32, ctypes.POINTER(PmsOptions),
                                  ctypes.POINTER(PmsTuning), ctypes.c_int32, ctypes.POINTER(PmsResult),
                                  ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int32)]

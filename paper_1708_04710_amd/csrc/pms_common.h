@@ -79,6 +79,15 @@ inline bool tuning_builtin(const pms_tuning &t)
     return memcmp(&t, &b, sizeof(t)) == 0;
 }
 
+// Limits of a block reduced from its rows (pms_dual.h); 0: as built in.
+struct DualLimits {
+    int32_t sum = 0;     // faces of one column's sum
+    int32_t arena = 0;   // faces remembered in all
+    int32_t beyond = 0;  // cofaces beyond the bitmap
+    int32_t bits = 0;    // bits of the bitmap
+    int32_t rounds = 0;  // rounds the counters have room for
+};
+
 struct Ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -114,6 +123,7 @@ struct Ctx {
     hipGraphExec_t graph_exec = nullptr;
     std::vector<unsigned char> graph_key;
     // launch shapes and thresholds of the chaining kernels
+    DualLimits dual;
     pms_tuning tune = default_tuning();
     // the last reduction's diagnostics (pms_options.diagnostics): one entry
     // per recorded round, and the size of the problem its estimate covers

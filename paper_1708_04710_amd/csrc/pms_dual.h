@@ -381,9 +381,10 @@ inline pms_status dual_rounds(Ctx *c, const P &prov, const DualState &s, L launc
     *ok = 1;
     static_assert((kDualRounds + 3) * 4 <= 2048, "the pinned buffer holds the counters");
     const volatile int32_t *h = (const int32_t *)c->host_pinned;  // fail, arena_top, counts
+    const int most = c->dual.rounds ? c->dual.rounds : kDualRounds;
     for (int r = 0;;) {
         // a few rounds per host synchronisation (a round without faces returns at once)
-        const int r1 = r + 4 < kDualRounds ? r + 4 : kDualRounds;
+        const int r1 = r + 4 < most ? r + 4 : most;
         hipEvent_t e0 = nullptr;
         if (c->prof_on) { e0 = prof_event(c); (void)hipEventRecord(e0, c->stream); }
         for (int q = r; q < r1; q++) {
@@ -409,7 +410,7 @@ inline pms_status dual_rounds(Ctx *c, const P &prov, const DualState &s, L launc
             return PMS_OK;
         }
         if (h[2 + r] == 0) return PMS_OK;
-        if (r == kDualRounds) {  // room for more rounds: their list keeps its parity (kDualRounds is even)
+        if (r == most) {  // room for more rounds: their list keeps its parity (an even number)
             const int32_t left = h[2 + r];
             k_dual_counters<<<1, kBlock, 0, c->stream>>>(s, 0, left);
             r = 0;

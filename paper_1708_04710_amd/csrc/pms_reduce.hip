@@ -3976,7 +3976,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
         // cofaces, list entries, sums; the rest of the arena remembers the sums
         int32_t dual = 0, dual_r = 0;
         int64_t dual_active = 0;
-        if (m <= kDualLdsBits) {
+        if (m <= (c->dual.bits ? c->dual.bits : kDualLdsBits)) {
             for (int32_t b = 1; b < top; b++)
                 if ((int64_t)h->n_dim[b + 1] >= 2LL * h->n_dim[b] && h->n_dim[b] > 0) dual |= 2 << b;
         }
@@ -3984,6 +3984,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
             const unsigned nb = 256;
             DualState s{};
             s.vcap = 4096;
+            if (c->dual.sum) s.vcap = std::min(s.vcap, c->dual.sum);
             const int64_t a_end = 0, a_cof = a_end + m + 1, a_list = (a_cof + nnz + 2) & ~1ll, a_keys = a_list + 4 * m,
                           a_cnt = a_keys + 3 * m, a_tmp = a_cnt + kDualCounters, a_sum = a_tmp + (int64_t)nb * s.vcap;
             s.arena_cap = std::min<int64_t>((int64_t)d.arena_cap - a_sum, 1 << 28);
@@ -3992,6 +3993,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
             } else {
                 int32_t *ar = d.arena;
                 const CsrProv pv{ar + a_end, ar + a_cof};
+                if (c->dual.arena) s.arena_cap = std::min<int64_t>(s.arena_cap, c->dual.arena);
                 s.low_star = d.low_star;
                 s.list[0] = (int2 *)(ar + a_list);
                 s.list[1] = s.list[0] + m;
@@ -4713,6 +4715,17 @@ pms_status pms_get_tuning(pms_ctx *c, pms_tuning *t)
     c->err.clear();
     if (!t) return pms::set_err(c, PMS_ERR_INVALID_ARG, "null tuning");
     *t = c->tune;
+    return PMS_OK;
+}
+
+pms_status pms_set_dual_limits(pms_ctx *c, int32_t sum, int32_t arena, int32_t beyond, int32_t bits, int32_t rounds)
+{
+    if (!c) return PMS_ERR_INVALID_ARG;
+    c->err.clear();
+    if (sum < 0 || arena < 0 || beyond < 0 || (bits != 0 && (bits < 1024 || bits > pms::kDualLdsBits)) || rounds < 0 ||
+        rounds > pms::kDualRounds || (rounds & 1))
+        return pms::set_err(c, PMS_ERR_INVALID_ARG, "limit out of range");
+    c->dual = pms::DualLimits{sum, arena, beyond, bits, rounds};
     return PMS_OK;
 }
 

@@ -628,17 +628,19 @@ pms_status reduce_vr(Ctx *c, const Filtration *f, pms_result *res, int32_t count
     unsigned blocks_of[2] = {1, 1};
     blocks_of[0] = (unsigned)std::min<int64_t>(resident((int64_t)f->vr_max_n * ((f->vr_max_n + 63) / 64) * 8),
                                                std::max<int64_t>(f->vr_edges, 1));
+    const DualLimits &lim = c->dual;
     if (maxdim >= 3) {
-        const int64_t bits = std::min<int64_t>(f->vr_max_m, kDualLdsBits);
+        const int64_t bits = std::min<int64_t>(f->vr_max_m, lim.bits ? lim.bits : kDualLdsBits);
         s.nw0 = dual_words(bits);
         s.nw1 = dual_summary_words(bits);
         blocks_of[1] = (unsigned)std::min<int64_t>(std::min<int64_t>(resident((s.nw1 + s.nw0) * 4), 1024),
                                                    std::max<int64_t>(nkey, 1));
-        if (f->vr_max_m > kDualLdsBits) s.ovf_cap = 1 << 18;
+        if (f->vr_max_m > bits) s.ovf_cap = lim.beyond ? std::min(lim.beyond, 1 << 18) : 1 << 18;
     }
     const unsigned blocks = blocks_of[1];
-    s.vcap = 8192;
+    s.vcap = lim.sum ? std::min(lim.sum, 8192) : 8192;
     s.arena_cap = std::max<int64_t>(1 << 20, 16 * f->vr_edges);
+    if (lim.arena) s.arena_cap = std::min<int64_t>(s.arena_cap, lim.arena);
     s.low_star = res->low_star;
     int32_t *cnt = (int32_t *)grow_scratch(c, B_DUAL0, (size_t)kDualCounters * 4 + sizeof(VrTotals));
     s.list[0] = (int2 *)grow_scratch(c, B_DUAL1, (size_t)nkey * 8);
