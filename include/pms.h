@@ -217,7 +217,8 @@ typedef struct {
                                by itself.  Exact for a column's first addition in a round;
                                for the chained additions after it, len t counts the
                                column's pending toggles, and len(t + s) = len t + len s - 2
-                               (only the low is known to cancel) */
+                               (only the low is known to cancel).  Blocks reduced from their
+                               rows toggle entries in place: 8 bytes per entry read */
 } pms_result;
 
 /* Reduce one boundary matrix (Alg. "Parallel multi-scale reduction":

@@ -96,7 +96,9 @@ class ReduceResult:
     additions: int
     xor_entries: int
     active_sum: int = 0      # sum over rounds of the round's active columns
-    addition_bytes: int = 0  # sum over additions of 4 (len t + len s + len t+s)
+    # sum over additions of 4 (len t + len s + len t+s); of the blocks reduced from
+    # their rows 8 per entry read
+    addition_bytes: int = 0
     # batched reductions only (reduce_batched): per-instance starts in the
     # pair / essential lists ([count+1] int64) and the instance of each pair
     inst_pair_off: torch.Tensor | None = None

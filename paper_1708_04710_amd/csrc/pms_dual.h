@@ -58,6 +58,7 @@ struct DualState {
     int32_t ovf_cap;
     int64_t nw0, nw1;          // words of a bitmap and of its summary
     unsigned long long *adds, *entries;
+    unsigned long long *abytes;  // 8 per entry read (a list word, a bit toggled), or null
 };
 
 inline void dual_counters(DualState &s, int32_t *p)
@@ -318,6 +319,7 @@ __global__ void __launch_bounds__(P::kT) k_dual(P prov, DualState s, int round)
     if ((tid & (kWave - 1)) == 0) {
         if (adds) atomicAdd(s.adds, adds);
         if (e) atomicAdd(s.entries, (unsigned long long)e);
+        if (e && s.abytes) atomicAdd(s.abytes, 8ull * (unsigned long long)e);
     }
 }
 

@@ -79,6 +79,8 @@ enum StatId {
     S_T_SINIT, S_T_SA, S_T_SB, S_T_SC, S_T_SOUT, S_T_SDELTA, S_T_SLONG, S_T_SLONGE, S_T_SDEFER,
     // k_pivots: bytes a new pivot moves (its record, the column entries it copies, the tables)
     S_PBYTES,
+    // bytes of the additions of the blocks reduced from their rows (k_dual)
+    S_ABYTES_DUAL,
     S_NUM
 };
 
@@ -97,6 +99,7 @@ struct Counters {
     unsigned long long pivot_bytes;  // bytes k_pivots moves for its new pivots
     // its additions as multi-way sums: 4 (len c + the pivots' lengths + len out) per column
     unsigned long long abytes_solve;
+    unsigned long long abytes_dual;  // blocks reduced from their rows: 8 per entry read
     unsigned long long active_sum;   // sum over rounds of the round's active columns
     unsigned long long diag_low_l1;  // diagnostics: sum_j (low(j) + 1)
     unsigned long long diag_ess;     // diagnostics: |E|
@@ -3298,6 +3301,7 @@ __global__ void k_stats_fold(Dev d, Counters *host)
         d.cnt->solve_bytes = s_sum[S_SBYTES];
         d.cnt->pivot_bytes = s_sum[S_PBYTES];
         d.cnt->abytes_solve = s_sum[S_ABYTES_SOLVE];
+        d.cnt->abytes_dual = s_sum[S_ABYTES_DUAL];
         d.cnt->new_pivots = (int32_t)s_sum[S_NEWPIV];
         d.cnt->beta_pivots = (int32_t)s_sum[S_BETAPIV];
         for (int q = 0; q < S_NUM; q++) d.cnt->trace[q] = s_sum[q];
@@ -4007,6 +4011,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
                 s.nw1 = dual_summary_words(m);
                 s.adds = &d.stats[(unsigned)S_ADDS * kStripe * 16];
                 s.entries = &d.stats[(unsigned)S_XE * kStripe * 16];
+                s.abytes = &d.stats[(unsigned)S_ABYTES_DUAL * kStripe * 16];
                 PMS_LAUNCH(c, K_FILL, 4 * dm, k_fill_i32, gm, kBlock, ar + a_end, m + 1, 0);
                 PMS_LAUNCH(c, K_DUAL, dm + 8 * dz, k_cof_count, gm, kBlock, d, dual, ar + a_end);
                 const int64_t mt = (m + kMixTile - 1) / kMixTile;
@@ -4299,7 +4304,7 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     res->xor_entries = (int64_t)h->xor_entries;
     res->active_sum = (int64_t)h->active_sum + block_active;
     res->addition_bytes =
-        (int64_t)(h->abytes_xor + h->abytes_lane + h->abytes_wide + h->abytes_chain + h->abytes_solve);
+        (int64_t)(h->abytes_xor + h->abytes_lane + h->abytes_wide + h->abytes_chain + h->abytes_solve + h->abytes_dual);
     res->phase0_pivots = h->beta_pivots;
     res->n_pairs = h->n_pairs;
     res->n_essential = h->n_ess;

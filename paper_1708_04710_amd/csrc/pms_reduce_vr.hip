@@ -741,7 +741,7 @@ pms_status reduce_vr(Ctx *c, const Filtration *f, pms_result *res, int32_t count
     res->additions = (int64_t)h.adds;
     res->xor_entries = (int64_t)h.entries;
     res->active_sum = active;
-    res->addition_bytes = (int64_t)(8 * h.entries);
+    res->addition_bytes = (int64_t)(8 * h.entries);  // (as k_dual's abytes)
     if ((want_pairs && res->cap_pairs < res->n_pairs) || (want_ess && res->cap_essential < res->n_essential))
         return set_err(c, PMS_ERR_CAPACITY, "output capacity too small (n_pairs / n_essential hold the sizes)");
     return PMS_OK;

@@ -110,3 +110,14 @@ def test_limits_out_of_range_are_refused(gpu):
         with pytest.raises(B.PmsError) as e, _limits(gpu, **bad):
             pass
         assert e.value.status == B.PMS_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("maxdim,n", [(2, 60), (3, 30)])
+def test_bytes_of_the_additions(gpu, maxdim, n):
+    """Of these clouds nothing is left to the rounds, so every entry read is one
+    toggled in place (8 bytes), as a filtration and as a matrix."""
+    cloud = _clouds(8, n, 1, "circle" if maxdim == 2 else "sphere")[0]
+    f, _ = api.build_vr(torch.as_tensor(cloud, device=gpu), None, maxdim)
+    t = f.to_torch()
+    for res in (api.reduce_filtration(f), api.reduce(t["col_ptr"], t["rows"], t["dim"])):
+        assert res.xor_entries > 0 and res.addition_bytes == 8 * res.xor_entries
