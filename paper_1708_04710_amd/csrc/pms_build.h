@@ -9,7 +9,7 @@ namespace pms {
 // Arrays a Vietoris-Rips filtration built by edge order keeps (pms_vr_edges.h)
 enum VrBuf {
     VR_CLOUDS = 0, VR_EV, VR_ERANK, VR_EIDX, VR_REC, VR_GST, VR_GEND, VR_TSCAN, VR_Q2, VR_APP, VR_RECD, VR_REC2,
-    VR_APPT, VR_TRIP, VR_MASK, VR_APC, VR_NUM
+    VR_APPT, VR_MASK, VR_APC, VR_NUM
 };
 
 // Device arrays of one filtration in compatible order (owned by the library).
@@ -34,7 +34,6 @@ struct Filtration {
     int32_t vr_maxdim = 0;
     int64_t vr_edges = 0;        // entries of its edge arrays
     int64_t vr_max_m = 0;        // simplices of its largest cloud
-    int64_t vr_max_t = 0;        // most triangles of a cloud
     int32_t vr_max_n = 0;        // most points of a cloud
 };
 

@@ -480,15 +480,12 @@ __device__ inline int ve_select(const uint2 *w, int W, int k)
     return q * 32 + __ffs((int)m) - 1;
 }
 
-// Edges of a workgroup of k_ve_emit and k_ve_tris: their mask words pass
-// through LDS (kTileWords of them, fewer edges when a cloud has more words).
+// Edges of a workgroup of k_ve_emit and k_ve_tris: their mask words (32 each
+// for 1 023 points, the most) pass through LDS.
 // Few edges in all: 8 a workgroup (an edge of 100 points has up to 98 triangles;
 // 64 of the last ones hold a launch of 4 950 edges for 27 us, 8 for 7.6).
-constexpr int kVeTile = 64, kVeFewTile = 8, kTileWords = 2048;
-inline int ve_tile(int W, int64_t E)
-{
-    return std::min(E >= kVeManyEdges ? kVeTile : kVeFewTile, W <= 1 ? kVeTile : W < kTileWords ? kTileWords / W : 1);
-}
+constexpr int kVeTile = 64, kVeFewTile = 8, kTileWords = 32 * kVeTile;
+inline int ve_tile(int64_t E) { return E >= kVeManyEdges ? kVeTile : kVeFewTile; }
 
 // One lane per edge: its index, rec's indices.  The mask words are read and
 // written by the whole workgroup in their order.
@@ -498,14 +495,11 @@ __global__ void __launch_bounds__(kBlock) k_ve_emit(VeView v, int maxdim, int pe
     __shared__ uint32_t s_w[kTileWords], s_run[kTileWords];
     const VeCloud I = v.cl[blockIdx.y];
     const int W = maxdim >= 2 ? I.W : 0;
-    const bool lds = W <= kTileWords;
     for (int32_t e0 = blockIdx.x * per; e0 < I.E; e0 += gridDim.x * per) {
         const int32_t ne = min(per, I.E - e0);
         uint2 *r0 = rec + I.woff + (int64_t)e0 * I.W;
-        if (lds) {
-            for (int32_t k = threadIdx.x; k < ne * W; k += kBlock) s_w[k] = r0[k].x;
-            __syncthreads();
-        }
+        for (int32_t k = threadIdx.x; k < ne * W; k += kBlock) s_w[k] = r0[k].x;
+        __syncthreads();
         if ((int32_t)threadIdx.x < ne) {
             const int32_t e = e0 + (int32_t)threadIdx.x;
             const int64_t oe = I.eoff + e;
@@ -519,25 +513,20 @@ __global__ void __launch_bounds__(kBlock) k_ve_emit(VeView v, int maxdim, int pe
             eidx[I.slot_base + (int64_t)a * I.n + b] = pe;
             eidx[I.slot_base + (int64_t)b * I.n + a] = pe;
             const int apc = v.apc[oe];
-            uint2 *r = r0 + (int64_t)threadIdx.x * I.W;
             uint32_t *rd = recd ? recd + I.woff + (int64_t)e * I.W : nullptr;
             int32_t run = 0, at = -1;
             for (int w = 0; w < W; w++) {
-                const uint32_t m = lds ? s_w[threadIdx.x * W + w] : r[w].x;
-                const uint32_t y = tied ? kTied : (uint32_t)(tb + run);
-                if (lds) s_run[threadIdx.x * W + w] = y;
-                else r[w].y = y;
+                const uint32_t m = s_w[threadIdx.x * W + w];
+                s_run[threadIdx.x * W + w] = tied ? kTied : (uint32_t)(tb + run);
                 if (rd) rd[w] = (uint32_t)(own + run);
                 if (apc >= 0 && (apc >> 5) == w) at = tb + run + __popc(m & below(apc));
                 run += __popc(m);
             }
             app[oe] = apc >= 0 && tied ? tb + ve_tie_rank(v, I, e, apc) : at;
         }
-        if (lds) {
-            __syncthreads();
-            for (int32_t k = threadIdx.x; k < ne * W; k += kBlock) r0[k].y = s_run[k];
-            __syncthreads();
-        }
+        __syncthreads();
+        for (int32_t k = threadIdx.x; k < ne * W; k += kBlock) r0[k].y = s_run[k];
+        __syncthreads();
     }
 }
 
@@ -551,7 +540,7 @@ __global__ void __launch_bounds__(kBlock) k_ve_emit(VeView v, int maxdim, int pe
 // ms, 22 M of 64 clouds 0.58; now 0.68 and 0.37, 2.5 TB/s of writes.)
 template <bool F32>
 __global__ void __launch_bounds__(kBlock) k_ve_tris(VeView v, VeOut o, int maxdim, int per, const unsigned long long *eval,
-                                                    int32_t *trip, int32_t *appt)
+                                                    int32_t *appt)
 {
     __shared__ uint32_t s_w[kTileWords];
     __shared__ int32_t s_ts[kVeTile + 1], s_ab[kVeTile], s_g0[kVeTile], s_g1[kVeTile], s_tg[kVeTile], s_qs[kVeTile];
@@ -563,7 +552,6 @@ __global__ void __launch_bounds__(kBlock) k_ve_tris(VeView v, VeOut o, int maxdi
     for (int32_t x = blockIdx.x * kBlock + threadIdx.x; x < I.n; x += gridDim.x * kBlock)
         ve_put<F32>(o, I.col_base + x, I.nnz_base, 0, 0, 0, make_int2(-1, -1), make_int4(pb + x, -1, -1, -1));
     const int W = maxdim >= 2 ? I.W : 0;
-    const bool lds = W <= kTileWords;
     for (int32_t e0 = blockIdx.x * per; e0 < I.E; e0 += gridDim.x * per) {
         const int32_t ne = min(per, I.E - e0);
         const uint2 *rec = v.rec + I.woff + (int64_t)e0 * W;
@@ -587,8 +575,7 @@ __global__ void __launch_bounds__(kBlock) k_ve_tris(VeView v, VeOut o, int maxdi
             o.rows[cp] = cb + a;
             o.rows[cp + 1] = cb + b;
         }
-        if (lds)
-            for (int32_t k = threadIdx.x; k < ne * W; k += kBlock) s_w[k] = rec[k].x;
+        for (int32_t k = threadIdx.x; k < ne * W; k += kBlock) s_w[k] = rec[k].x;
         __syncthreads();
         const int32_t t1 = s_ts[ne];
         for (int32_t t = s_ts[0] + (int32_t)threadIdx.x; t < t1; t += kBlock) {
@@ -600,11 +587,11 @@ __global__ void __launch_bounds__(kBlock) k_ve_tris(VeView v, VeOut o, int maxdi
             }
             const int32_t e = e0 + i;
             int k = t - s_ts[i], q = 0;
-            uint32_t m = lds ? s_w[i * W] : rec[(int64_t)i * W].x;
+            uint32_t m = s_w[i * W];
             while (__popc(m) <= k) {  // (the edge has more than k)
                 k -= __popc(m);
                 q++;
-                m = lds ? s_w[i * W + q] : rec[(int64_t)i * W + q].x;
+                m = s_w[i * W + q];
             }
             int c = q * 32;  // the k-th bit of m
 #pragma unroll
@@ -629,10 +616,7 @@ __global__ void __launch_bounds__(kBlock) k_ve_tris(VeView v, VeOut o, int maxdi
             o.rows[cp] = cb + min(ra, rb);
             o.rows[cp + 1] = cb + max(ra, rb);
             o.rows[cp + 2] = cb + I.n + e + tg + qs;
-            if (appt) {
-                trip[I.toff + tg + r] = (int32_t)(p - cb);
-                appt[p] = -1;
-            }
+            if (appt) appt[p] = -1;
         }
         __syncthreads();
     }
@@ -1033,8 +1017,6 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
     st = filtration_reserve(c, &f, m, nnz, f32 ? 1 : 0);
     if (st != PMS_OK) return st;
     if (maxdim >= 3 && (st = filtration_vr_reserve(c, &f, VR_APPT, (size_t)m * 4)) != PMS_OK) return st;
-    if (maxdim >= 3 && (st = filtration_vr_reserve(c, &f, VR_TRIP, (size_t)T * 4)) != PMS_OK) return st;
-    f->vr_max_t = tmax;
     f->vr_max_n = (int32_t)nmax;
     PMS_HIP(hipMemcpyAsync(cl, h.data(), (size_t)B * sizeof(VeCloud), hipMemcpyHostToDevice, s));
     if (m == 0) {
@@ -1045,12 +1027,11 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
         const VeOut o{m, nnz, f->col_ptr, f->rows, f->dim, f->value, f->crit, f->verts};
         uint2 *rec2 = (uint2 *)f->vr[VR_REC2].p;
         int32_t *appt = maxdim >= 3 ? (int32_t *)f->vr[VR_APPT].p : nullptr;
-        int32_t *trip = maxdim >= 3 ? (int32_t *)f->vr[VR_TRIP].p : nullptr;
         const double pb = f32 ? 37.0 : 41.0;
-        const int tile = ve_tile(maxdim >= 2 ? (int)((nmax + 31) / 32) : 0, E);
+        const int tile = ve_tile(E);
         PMS_LAUNCH(c, K_VR_INDEX, 8.0 * words + 40.0 * E, k_ve_emit, grid(emax, tile), kBlock, v, maxdim, tile, eidx, rec, app, recd);
-        if (f32) PMS_LAUNCH(c, K_VR_ROWS, (pb + 8) * E + (pb + 12) * T, k_ve_tris<true>, grid(std::max(emax, nmax), tile), kBlock, v, o, maxdim, tile, eval, trip, appt);
-        else PMS_LAUNCH(c, K_VR_ROWS, (pb + 8) * E + (pb + 12) * T, k_ve_tris<false>, grid(std::max(emax, nmax), tile), kBlock, v, o, maxdim, tile, eval, trip, appt);
+        if (f32) PMS_LAUNCH(c, K_VR_ROWS, (pb + 8) * E + (pb + 12) * T, k_ve_tris<true>, grid(std::max(emax, nmax), tile), kBlock, v, o, maxdim, tile, eval, appt);
+        else PMS_LAUNCH(c, K_VR_ROWS, (pb + 8) * E + (pb + 12) * T, k_ve_tris<false>, grid(std::max(emax, nmax), tile), kBlock, v, o, maxdim, tile, eval, appt);
         if (maxdim >= 3 && T > 0) {
             PMS_LAUNCH(c, K_VR_INDEX, 8.0 * words2, k_ve_tindex, grid(tmax, kBlock), kBlock, v, tri, rec2, appt);
             if (f32) PMS_LAUNCH(c, K_VR_ROWS, (pb + 16) * Q, k_ve_tets<true>, grid(qmax, 2 * kBlock), kBlock, v, o, eval, tri);

@@ -89,7 +89,6 @@ VeView filtration_vr_view(const Filtration *f)
         v.q2 = (const int64_t *)f->vr[VR_Q2].p;
         v.recd = (const uint32_t *)f->vr[VR_RECD].p;
         v.rec2 = (const uint2 *)f->vr[VR_REC2].p;
-        v.trip = (const int32_t *)f->vr[VR_TRIP].p;
         v.appt = (const int32_t *)f->vr[VR_APPT].p;
     }
     return v;

@@ -617,11 +617,10 @@ pms_status reduce_vr(Ctx *c, const Filtration *f, pms_result *res, int32_t count
     const int64_t tiles = (m + kFinTile - 1) / kFinTile, nwords = (m + 31) / 32;
     const int64_t nkey = std::max<int64_t>(f->vr_edges, maxdim >= 3 ? m : 0);
 
-    // the bitmaps: in LDS when the largest cloud's fits (as many workgroups as
-    // a CU's LDS holds), else in memory
     DualState s{};
     // workgroups: as many as the CUs' LDS holds.  Edges: a bit matrix of the
-    // points.  Triangles: a bitmap of the cloud, or of as much as fits.
+    // points.  Triangles: a bitmap of the cloud, or of as much of it as fits,
+    // moving on (what lies beyond waits in the overflow list).
     auto resident = [&](int64_t lds_bytes) {
         return 256 * std::max<int64_t>(1, std::min<int64_t>(16, 160 * 1024 / (lds_bytes + 512)));
     };

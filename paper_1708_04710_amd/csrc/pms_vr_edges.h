@@ -59,7 +59,6 @@ struct VeView {
     const int32_t *app;       // [edge] index of the triangle it forms an apparent pair with, -1: none
     const uint32_t *recd;     // [edge W + c / 32] dense number of the first triangle of the word (dimension 3)
     const uint2 *rec2;        // [(toff + dense) W2 + d / 32] like rec for the tetrahedra (e, c, d), d > c
-    const int32_t *trip;      // [toff + k] index within the cloud of its k-th triangle (dimension 3)
     const int32_t *appt;      // [column] index of the tetrahedron a triangle is apparent with, -1: none
 };
 
