@@ -102,7 +102,7 @@ pms_status filtration_reserve(Ctx *c, Filtration **pf, int64_t m, int64_t nnz, i
     f->m = f->nnz = 0;
     f->has_left_beta = f->has_second = 0;
     f->vr_count = 0;
-    if (f->cap_m >= m && f->cap_nnz >= nnz && f->device == c->device) return PMS_OK;
+    if (f->col_ptr && f->cap_m >= m && f->cap_nnz >= nnz && f->device == c->device) return PMS_OK;
     (void)hipStreamSynchronize(c->stream);
     filtration_release(f);
     f->device = c->device;

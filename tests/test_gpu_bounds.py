@@ -241,3 +241,16 @@ def test_instances_of_a_callers_matrix(gpu):
                  lambda: api.reduce_batched(f, off, noalloc=True)):
         with pytest.raises(ValueError):
             call()
+
+
+@pytest.mark.parametrize("dtype", [torch.int32, torch.float32])
+def test_a_batch_of_empty_clouds(gpu, dtype):
+    """An empty filtration, in a new object as in a kept one, and no error left
+    behind for the next call."""
+    empty = [torch.zeros((0, 3), dtype=dtype, device=gpu)] * 2
+    kept, _ = api.build_vr(torch.arange(6, device=gpu).reshape(3, 2).to(dtype))
+    for out in (None, kept):
+        f, off = api.build_vr(empty, out=out)
+        assert f.m == 0 and off == [0, 0, 0] and f.to_torch()["col_ptr"].tolist() == [0]
+        assert api.reduce_batched(f, off).low_star.numel() == 0
+        assert api.build_vr(torch.arange(6, device=gpu).reshape(3, 2).to(dtype), out=f)[0].m == 7
