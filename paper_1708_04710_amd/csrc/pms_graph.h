@@ -25,11 +25,11 @@
 // What this replaces: on a smooth 64^3 field a tetrahedron's column adds up
 // to 11 758 pivots one after the other (each addition about 1 us in k_chain),
 // while the longest walk from the triangles' side is 78 nodes.  Measured, by
-// these kernels alone: build + reduce + backward of 64^3 fields 42.0 -> 4.8 ms
-// (3.5 with what came after), build + reduce of 128^3 399 -> 41.9 ms (17.7), of
-// 32^3 white noise 9.3 -> 3.9 ms (3.1).  The kernels here
-// are bound by scattered 4- and 8-byte accesses (a node's word, a face's two
-// cofaces), not by the walks.
+// these kernels alone: build + reduce + backward of a 64^3 field 42.0 -> 4.8 ms
+// (3.4 to 5.3 with what came after, by the field), build + reduce of a 128^3 one
+// 399 -> 41.9 ms (15.0 to 16.7), of 32^3 white noise 9.3 -> 3.9 ms (2.6 to 2.8).
+// The kernels here are bound by scattered 4- and 8-byte accesses (a node's
+// word, a face's two cofaces), not by the walks.
 #pragma once
 
 constexpr int32_t kNotGraph0 = 1, kNotGraphTop = 2;

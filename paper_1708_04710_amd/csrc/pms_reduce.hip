@@ -3732,10 +3732,13 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     size_t xor_slot = 0, lane_slot = 0, wide_slot = 0, chain_slot = 0, solve_slot = 0, pivots_slot = 0;
     double pivots_base = 0;
     const pms_tuning tn = c->tune;
-    // Columns that overfill the sweep kernel's list come with large matrices:
-    // of three 64^3 fields (m = 6.6 M, 1.5 M in the rounds) no column does, and
-    // the two empty launches a round cost 3% there (5.28 against 5.12 ms); of a
-    // 128^3 field (m = 54 M) two or three a round do.
+    // Columns that overfill the sweep kernel's list come with large matrices, and
+    // the two launches a round that nothing needs cost 5 to 9%.  Reductions of
+    // fields with the larger sizes and without them (ms): 48^3 (m = 2.7 M) 1.56 and
+    // 1.43, 64^3 (6.6 M) 2.47 and 2.31, no column of six fields needing them;
+    // 72^3 (9.4 M) 3.94 and 8.88, 3.50 and 3.34, 2.82 and 2.67 with three seeds; 96^3
+    // (22 M) 6.49 and 11.65; 128^3 (54 M) 13.1 and 29.9.  White noise never needs
+    // them: 96^3 12.7 and 12.1.
     int32_t *solve_mem = nullptr;
     if (m > (1 << 23) && tn.solve > 0 && !S.base) {
         solve_mem = (int32_t *)S.get(B_SOLVE, kSolveMemBytes);
@@ -3743,8 +3746,11 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
     }
     // With blocks apart a round hands on fewer columns, and longer chains:
     // sweeps up to twice the built-in number, and beyond it walks of 64 at most.
-    // At 128^3 with the larger sizes 25.1 ms, 39.3 before (k_chain 23 ms of the
-    // kernels' 48, one column of 4 760 additions at 1 us each): k_chain none left.
+    // Both matter where a round hands on some 500 to 2 000 columns (fields
+    // smoothed little: sigma 1.5, 96^3: 6.95 ms, 7.94 with sweeps up to the built-in
+    // number, 7.04 up to four times it; walks of any length 8.31, of 256 8.23, of 16
+    // 7.59; 128^3: 13.2, walks of any length 14.1); nine smooth fields of 48^3 to
+    // 128^3 and white noise to 96^3 stay within 2% either way.
     const int32_t solve_max = blocks ? 2 * tn.solve : tn.solve, busy_cap = blocks ? 64 : 0x7FFFFFFF;
     auto launch_round = [&](const int32_t *a, int32_t *an, int64_t grid_tiles, double dA, Counters *hout) -> pms_status {
         const unsigned gT = (unsigned)(grid_tiles > 0 ? grid_tiles : 1);
@@ -3977,7 +3983,12 @@ static pms_status reduce_impl(Ctx *c, const pms_boundary *bnd, const pms_options
                    do_top, opt->compression);
         // blocks with many more cofaces than faces, from their rows, while the
         // bitmap fits LDS and the lists the arena (nothing has moved there yet):
-        // cofaces, list entries, sums; the rest of the arena remembers the sums
+        // cofaces, list entries, sums; the rest of the arena remembers the sums.
+        // Twice as many: a full cloud's triangles are n / 3 times its edges, a
+        // volume's middle block (12 triangles to 7 edges) is better left to the
+        // rounds, its faces' chains being long: by rounds and from its rows 16^3
+        // noise 1.16 and 3.2 ms, 32^3 noise 2.6 and 5.9, smooth 32^3 0.94 and 2.6,
+        // 37 x 50 x 23 0.87 and 2.5, smooth 16^3 0.54 and 0.72 or 0.50 and 0.46.
         int32_t dual = 0, dual_r = 0;
         int64_t dual_active = 0;
         if (m <= (c->dual.bits ? c->dual.bits : kDualLdsBits)) {
