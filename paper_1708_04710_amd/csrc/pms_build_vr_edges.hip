@@ -808,6 +808,7 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
     if (!h.first) return set_err(c, PMS_ERR_OOM, "pinned host memory");
     int32_t &herr = *(int32_t *)(h.first + B);
     int64_t slots = 0, pairs = 0, pbase = 0, nmax = 1, maxpairs = 0;
+    double work = 0, maxwork = 0;  // coordinates of all pairs' distances; of one cloud's
     for (int b = 0; b < B; b++) {
         VeCloud &I = h[(size_t)b];
         memset(&I, 0, sizeof(I));
@@ -833,6 +834,8 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
         slots += (int64_t)n[b] * n[b];
         pairs += n[b] > 0 ? np : 0;
         maxpairs = std::max(maxpairs, np);
+        work += (double)np * D[b];
+        maxwork = std::max(maxwork, (double)np * D[b]);
         nmax = std::max<int64_t>(nmax, n[b]);
     }
     int lexb = 1, cbits = 0;
@@ -867,8 +870,15 @@ pms_status build_vr_edges(Ctx *c, const void *pts, bool f32, const int32_t *n, c
     };
     // In LDS when every cloud's edges fit (a full cloud of 181 points, a larger
     // truncated one: tried while an eighth of its pairs would fit); the
-    // device-wide sort takes the batch when one cloud's do not.
-    bool lds = maxpairs <= 8 * kLdsEdges;
+    // device-wide sort takes the batch when one cloud's do not, or when its
+    // distances are too much for the one workgroup it has here.  That takes 0.49 us
+    // per 1 000 coordinates of its pairs, the device-wide keys 4.3 us per million of
+    // all clouds', and their sort some 100 us more.  Builds to dimension 1 in us,
+    // here and device-wide: 181 points of 512 coordinates 4153 and 263; 100 of 64 271
+    // and 208, of 32 192 and 204; 60 of 128 200 and 182; 30 of 512 190 and 219; 128
+    // clouds of 100 points of 64 435 and 627, of 512 1553 and 1871; 16 of 300 points of
+    // 512 10.9 ms and 1.8.
+    bool lds = maxpairs <= 8 * kLdsEdges && maxwork <= (double)(1 << 18) + work / 110;
     for (auto &I : h) lds = lds && (I.has_thr || (int64_t)I.n * (I.n - 1) / 2 <= kLdsEdges);
     if (lds) {
         int32_t cap = kVeThreads;  // (a sort has at least one key a thread)

@@ -254,3 +254,24 @@ def test_a_batch_of_empty_clouds(gpu, dtype):
         assert f.m == 0 and off == [0, 0, 0] and f.to_torch()["col_ptr"].tolist() == [0]
         assert api.reduce_batched(f, off).low_star.numel() == 0
         assert api.build_vr(torch.arange(6, device=gpu).reshape(3, 2).to(dtype), out=f)[0].m == 7
+
+
+@pytest.mark.parametrize("n,D,count", [(40, 335, 1), (40, 337, 1), (40, 340, 30), (90, 500, 3), (181, 20, 2), (190, 16, 2)])
+@pytest.mark.parametrize("f32", [False, True])
+def test_clouds_of_many_coordinates(gpu, n, D, count, f32):
+    """Either side of the line from which one workgroup's distances are too many
+    (2^18 coordinates of a cloud's pairs, and more in a batch)."""
+    rng = np.random.default_rng(n + D)
+    clouds = [rng.normal(size=(n, D)) for _ in range(count)]
+    clouds = [c.astype(np.float32) if f32 else np.rint(c * 999).astype(np.int32) for c in clouds]
+    maxdim = 2 if n < 100 else 1
+    f, off = api.build_vr([torch.as_tensor(c, device=gpu) for c in clouds], None, maxdim)
+    t = f.to_torch()
+    low = api.reduce_batched(f, off).low_star.cpu().numpy()
+    for c, a, b in zip(clouds, off, off[1:]):
+        ref = (oracle.build_vr_f32 if f32 else oracle.build_vr_i32)(c, maxdim=maxdim)
+        s, e = int(t["col_ptr"][a]), int(t["col_ptr"][b])
+        assert b - a == ref.m and np.array_equal(t["rows"][s:e].cpu().numpy(), ref.rows + a)
+        assert np.array_equal(t["value"][a:b].cpu().numpy().astype(np.float64), ref.value.astype(np.float64))
+        want = oracle.reduce_twist(ref.col_ptr, ref.rows, ref.dim)
+        assert np.array_equal(low[a:b], np.where(want >= 0, want + a, -1))
